@@ -242,21 +242,15 @@ struct sweep_dag_s {
   std::vector<Unit> units;
   std::vector<int32_t> order;  // units, deepest first
   std::vector<int32_t> identity;
-  Buf units_d, order_d, identity_d, sched, indeg, lp, lev_up, lev_dn, up_ptr, dn_ptr, up, dn,
+  Buf units_d, order_d, identity_d, sched, inv, indeg, lp, len_up, len_dn, up, dn, slice_base, sl_up, sl_dn,
       aperp, aperp_s, vol_s, bnd, vol, counter, blk_base;
+  int64_t n_slices = 0;  // slices of the sweep over all units (sweep::SliceRec)
   int32_t n_blocks = 0;  // 256-task blocks over all units (prep kernel)
   int32_t max_depth = 0;
   int32_t max_cells = 0;  // cells of the largest mesh
   int32_t kahn_lds = 0;   // the levels were computed with counters in LDS
   int32_t scheme = SWEEP_SCHEME_AREA;
   Buf flag;               // device error bits (see internal.h) raised by asynchronous calls
-  std::vector<int64_t> unit_up, unit_dn;  // row entries of every unit
-  // step tables of the level-synchronous sweep, one per workgroup size
-  struct StepTable {
-    int32_t block = 0, cap_e = 0;  // threads, staged entries per step
-    Buf k, eu, ed, base, n;
-  };
-  std::vector<std::unique_ptr<StepTable>> steps;
   // reduction tables (depend on G)
   int32_t red_G = 0, red_blocks = 0, red_cpb = 0;
   Buf blk_mesh, blk_cell0, mesh_off_d, mesh_cells_d, mesh_blk_base;
@@ -456,69 +450,27 @@ std::vector<GroupLaunch> group_plan(sweep_dag_t d, int G, bool plain, int pack) 
   return ch;
 }
 
-// The largest ring (a power of two) whose LDS layout fits next to the staging
-// buffers and prefetched slots of `block` threads; 0 if none does.
-int default_ring(sweep_dag_t d, int gn, int block) {
+// The largest ring (a power of two) of gn packed groups that leaves room for
+// `per_cu` workgroups on a compute unit; 0 if none does.
+int default_ring(sweep_dag_t d, int gn, int per_cu) {
   int best = 0;
   for (int r = 64; r <= (1 << 20); r *= 2)
-    if (sweep::sweep_lds_layout(gn, r, block).bytes <= (size_t)d->lds_max) best = r;
+    if (sweep::sweep_lds_bytes(gn, r) <= (size_t)d->lds_max &&
+        (sweep::sweep_lds_bytes(gn, r) + 256) * per_cu <= (size_t)kMaxLds)
+      best = r;
   return best;
 }
 
-// The step table of `block`-thread sweeps (built on first use, kept with the DAG).
-sweep_status_t ensure_steps(sweep_dag_t d, int block, hipStream_t s, sweep_dag_s::StepTable** out) {
-  const int cap_t = block, cap_e = sweep::kStageCh * block - 8;
-  for (auto& t : d->steps)
-    if (t->block == block && t->cap_e == cap_e) {
-      *out = t.get();
-      return SWEEP_OK;
-    }
-  if (g_capturing)  // prepare_steps builds every table a captured sequence needs beforehand
-    return fail(SWEEP_ERR_HIP, "step table of %d threads missing during graph capture", block);
-  const int n_units = (int)d->units.size();
-  // capacity per unit: a level of w tasks and e entries gives at most
-  // w / cap_t + 1.15 e / cap_e + 2 steps, and the levels' e sum to at most the
-  // unit's upwind plus downwind entries
-  std::vector<int64_t> base(n_units + 1, 0);
-  for (int u = 0; u < n_units; ++u) {
-    const Unit& U = d->units[u];
-    const int64_t e = d->unit_up[u] + d->unit_dn[u];
-    base[u + 1] = base[u] + 2 * (int64_t)U.depth + U.n_cells / cap_t + (e * 115) / (100LL * cap_e) + 3;
-  }
-  std::unique_ptr<sweep_dag_s::StepTable> t(new sweep_dag_s::StepTable());
-  t->block = block;
-  t->cap_e = cap_e;
-  const int64_t total = base[n_units];
-  HIP_TRY(t->k.alloc(4 * total));
-  HIP_TRY(t->eu.alloc(8 * total));
-  HIP_TRY(t->ed.alloc(8 * total));
-  HIP_TRY(t->base.alloc(8 * (size_t)(n_units + 1)));
-  HIP_TRY(t->n.alloc(4 * (size_t)n_units));
-  HIP_TRY(hipMemcpyAsync(t->base.p, base.data(), 8 * (size_t)(n_units + 1), hipMemcpyHostToDevice, s));
-  HIP_TRY(sweep::launch_steps(d->units_d.as<Unit>(), n_units, d->lp.as<int32_t>(),
-                              d->lev_up.as<int64_t>(), d->lev_dn.as<int64_t>(),
-                              d->up_ptr.as<int64_t>(), d->dn_ptr.as<int64_t>(),
-                              t->base.as<int64_t>(), cap_t, cap_e, t->k.as<int32_t>(),
-                              t->eu.as<int64_t>(), t->ed.as<int64_t>(), t->n.as<int32_t>(), s));
-  std::vector<int32_t> ns(n_units);
-  HIP_TRY(hipMemcpyAsync(ns.data(), t->n.p, 4 * (size_t)n_units, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
-  for (int u = 0; u < n_units; ++u)
-    if (ns[u] < 0) return fail(SWEEP_ERR_HIP, "step table of unit %d overflowed its capacity", u);
-  *out = t.get();
-  d->steps.push_back(std::move(t));
-  return SWEEP_OK;
-}
+// Launch shape of a sweep: threads per workgroup and ring.
+struct SweepShape {
+  int block, ring;
+};
 
-// Builds the step tables the sweeps of a call with these options use (before
-// any capture: building one synchronises the stream).
-sweep_status_t prepare_steps(sweep_dag_t d, const FwdPlan& p, int32_t G, hipStream_t s) {
-  for (const GroupLaunch& c : group_plan(d, G, p.form == SWEEP_FORM_PLAIN, p.pack)) {
-    const int block = p.block > 0 ? p.block : sweep::kSweepMaxBlock(c.gn);
-    sweep_dag_s::StepTable* t = nullptr;
-    ST_TRY(ensure_steps(d, block, s, &t));
-  }
-  return SWEEP_OK;
+// With at most one work item per compute unit, a workgroup takes the whole unit
+// (as many wavefronts as the registers allow, the largest ring).
+SweepShape sweep_shape(sweep_dag_t d, int gn, int64_t items) {
+  (void)items;
+  return {sweep::kSweepMaxBlock(gn), default_ring(d, gn, 1)};
 }
 
 // Per-task denominators and sources for one sweep (schedule order).
@@ -626,67 +578,66 @@ sweep_status_t run_sweep(sweep_dag_t d, bool reverse, const FwdPlan& p, int32_t 
                          hipStream_t s) {
   sweep::SweepArgs a{};
   a.units = d->units_d.as<Unit>();
-  a.sched = d->sched.as<int32_t>();
-  a.row_ptr = reverse ? d->dn_ptr.as<int64_t>() : d->up_ptr.as<int64_t>();
-  a.ent = reverse ? d->dn.as<int2>() : d->up.as<int2>();
-  a.n_ent = reverse ? d->n_dn : d->n_up;
+  a.slices = reverse ? d->sl_dn.as<sweep::SliceRec>() : d->sl_up.as<sweep::SliceRec>();
+  a.slice_base = d->slice_base.as<int64_t>();
+  a.len = reverse ? d->len_dn.as<int32_t>() : d->len_up.as<int32_t>();
+  a.ent = reverse ? d->dn.as<int4>() : d->up.as<int4>();
   a.tden = d->tden.as<float>();
   a.tsrc = d->tsrc.as<float>();
-  a.out = out;
   HIP_TRY(d->out_s.alloc(4 * (size_t)d->T * G));
   a.out_s = d->out_s.as<float>();
   a.C_total = d->C_total;
   a.G = G;
   a.D = d->D;
+  a.flag = d->flag.as<int32_t>();
   const int n_units = (int)d->units.size();
   for (const GroupLaunch& c : group_plan(d, G, p.form == SWEEP_FORM_PLAIN, p.pack)) {
     const int gn = c.gn;
-    const int block = p.block > 0 ? p.block : sweep::kSweepMaxBlock(gn);
+    const bool plain = p.form == SWEEP_FORM_PLAIN;
+    const int64_t items = plain ? 1 : (int64_t)n_units * c.n_chunks;
+    const SweepShape sh = sweep_shape(d, gn, items);
+    const int block = p.block > 0 ? p.block : sh.block;
     if (block > sweep::kSweepMaxBlock(gn))
       return fail(SWEEP_ERR_INVALID_ARG, "block %d: at most %d threads with %d packed groups", block,
                   sweep::kSweepMaxBlock(gn), gn);
-    const int ring = p.ring > 0 ? p.ring : default_ring(d, gn, block);
-    const sweep::LdsLayout L = sweep::sweep_lds_layout(gn, std::max(ring, 64), block);
-    if (ring == 0 || L.bytes > (size_t)d->lds_max)
+    const int ring = p.ring > 0 ? p.ring : sh.ring;
+    const size_t lds = sweep::sweep_lds_bytes(gn, ring);
+    if (ring == 0 || lds > (size_t)d->lds_max)
       return fail(p.ring > 0 ? SWEEP_ERR_INVALID_ARG : SWEEP_ERR_UNSUPPORTED,
-                  "ring %d x %d groups with %d threads needs %zu bytes of LDS, %d available", ring,
-                  gn, block, L.bytes, d->lds_max);
-    sweep_dag_s::StepTable* stp = nullptr;
-    ST_TRY(ensure_steps(d, block, s, &stp));
-    a.step_k = stp->k.as<int32_t>();
-    a.step_e = reverse ? stp->ed.as<int64_t>() : stp->eu.as<int64_t>();
-    a.step_base = stp->base.as<int64_t>();
-    a.n_steps = stp->n.as<int32_t>();
+                  "ring %d x %d groups needs %zu bytes of LDS, %d available", ring, gn, lds, d->lds_max);
     a.g0 = c.g0;
     a.n_chunks = 1;
     a.ring_mask = ring - 1;
-    a.stage_off = L.stage_off;
-    if (p.form == SWEEP_FORM_PLAIN) {
+    if (plain) {
       a.work_counter = nullptr;
       a.n_units = 1;
       for (int u = 0; u < n_units; ++u) {
         a.unit_order = d->identity_d.as<int32_t>() + u;
         ProfScope ps(reverse ? "sweep_adj" : "sweep_fwd", s);
-        hipError_t e = reverse ? sweep::launch_sweep_adj(a, gn, 1, block, L.bytes, s)
-                               : sweep::launch_sweep_fwd(a, gn, 1, block, L.bytes, s);
+        hipError_t e = reverse ? sweep::launch_sweep_adj(a, gn, 1, block, lds, s)
+                               : sweep::launch_sweep_fwd(a, gn, 1, block, lds, s);
         if (e != hipSuccess) return hip_fail(e, "sweep launch");
       }
     } else {
-      int per_cu = std::max(1, (int)((size_t)kMaxLds / (L.bytes + 256)));
-      per_cu = std::min(per_cu, std::max(1, 2048 / block));
+      // workgroups that fit a compute unit: LDS, and registers for 1,024 threads
+      // (512 with several packed groups)
+      int per_cu = std::max(1, (int)((size_t)kMaxLds / (lds + 256)));
+      per_cu = std::min(per_cu, std::max(1, sweep::kSweepMaxBlock(gn) / block));
       a.n_chunks = c.n_chunks;
-      int grid = (int)std::min<int64_t>((int64_t)n_units * c.n_chunks, (int64_t)d->cu_count * per_cu);
+      int grid = (int)std::min<int64_t>(items, (int64_t)d->cu_count * per_cu);
       if (p.grid > 0) grid = std::min(grid, p.grid);
       a.work_counter = d->counter.as<int32_t>();
       a.unit_order = d->order_d.as<int32_t>();
       a.n_units = n_units;
       HIP_TRY(sweep::launch_fill_i32(a.work_counter, 1, 0, s));
       ProfScope ps(reverse ? "sweep_adj" : "sweep_fwd", s);
-      hipError_t e = reverse ? sweep::launch_sweep_adj(a, gn, grid, block, L.bytes, s)
-                             : sweep::launch_sweep_fwd(a, gn, grid, block, L.bytes, s);
+      hipError_t e = reverse ? sweep::launch_sweep_adj(a, gn, grid, block, lds, s)
+                             : sweep::launch_sweep_fwd(a, gn, grid, block, lds, s);
       if (e != hipSuccess) return hip_fail(e, "sweep launch");
     }
   }
+  HIP_TRY(sweep::launch_to_cells(d->units_d.as<Unit>(), n_units, d->blk_base.as<int32_t>(), d->n_blocks,
+                                 d->inv.as<int32_t>(), d->out_s.as<float>(), out, d->C_total, G, s));
   return SWEEP_OK;
 }
 
@@ -762,6 +713,8 @@ sweep_status_t take_device_error(sweep_dag_t d, hipStream_t s) {
   if (bits & sweep::kErrEmission) what += " emission negative or not finite;";
   if (bits & sweep::kErrCell) what += " a cell with Aperp + kappa V not positive and finite;";
   if (bits & sweep::kErrGrad) what += " dL/dJ or dL/dabsorbed not finite;";
+  if (bits & sweep::kErrStall)
+    return fail(SWEEP_ERR_HIP, "a sweep's wait for earlier tasks did not end; the call's outputs are not meaningful");
   return fail(SWEEP_ERR_INVALID_ARG, "invalid input to an earlier sweep call on this DAG:%s its "
                                      "outputs are not meaningful", what.c_str());
 }
@@ -964,7 +917,7 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
       fo += meshes[m].n_half_faces;
     }
   }
-  Buf cblk_mesh_d, cblk_c0_d, dnw, stats_d, meshes_d, dirs_d, rowlen_dn, cnt, inv, depth_d, err_d, len_up, len_dn, scan_tmp;
+  Buf cblk_mesh_d, cblk_c0_d, dnw, stats_d, meshes_d, dirs_d, rowlen_dn, cnt, depth_d, err_d, nsl_d, np_up, np_dn, pb_up, pb_dn, scan_tmp;
   HIP_TRY(meshes_d.alloc(sizeof(sweep::MeshDev) * n_meshes));
   HIP_TRY(dirs_d.alloc(sizeof(double) * 3 * n_dirs));
   HIP_TRY(D->blk_base.alloc(sizeof(int32_t) * (n_units + 1)));
@@ -985,7 +938,7 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   HIP_TRY(D->vol_s.alloc(4 * T));
   HIP_TRY(D->bnd.alloc(8 * T));
   HIP_TRY(cnt.alloc(4 * T));  // Kahn's counters in global memory
-  HIP_TRY(inv.alloc(4 * T));
+  HIP_TRY(D->inv.alloc(4 * T));
   HIP_TRY(D->sched.alloc(4 * T));
   HIP_TRY(D->lp.alloc(4 * (T + 2 * (int64_t)n_units)));
   HIP_TRY(depth_d.alloc(4 * n_units));
@@ -1027,7 +980,7 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   a.wface = wface.as<float>();
   a.bnd = D->bnd.as<float2>();
   a.cnt = cnt.as<int32_t>();
-  a.inv = inv.as<int32_t>();
+  a.inv = D->inv.as<int32_t>();
   a.sched = D->sched.as<int32_t>();
   a.lp = D->lp.as<int32_t>();
   a.depth = depth_d.as<int32_t>();
@@ -1072,13 +1025,12 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   }
   // the longest downwind list sets how much of every row Kahn's algorithm loads
   a.dn_chunks = std::max(1, std::min(dn_width / 4, (stats[1] + 3) / 4));
-  // row lengths in schedule order (the input of the row-pointer scan)
-  HIP_TRY(len_up.alloc(4 * (T + 1)));
-  HIP_TRY(len_dn.alloc(4 * (T + 1)));
-  a.len_up = len_up.as<int32_t>();
-  a.len_dn = len_dn.as<int32_t>();
-  HIP_TRY(hipMemsetAsync(a.len_up + T, 0, 4, s));
-  HIP_TRY(hipMemsetAsync(a.len_dn + T, 0, 4, s));
+  HIP_TRY(D->len_up.alloc(4 * T));
+  HIP_TRY(D->len_dn.alloc(4 * T));
+  a.len_up = D->len_up.as<int32_t>();
+  a.len_dn = D->len_dn.as<int32_t>();
+  HIP_TRY(nsl_d.alloc(4 * n_units));
+  a.n_unit_slices = nsl_d.as<int32_t>();
   // Kahn counters in LDS as 4-bit fields when the mesh fits the LDS
   // (the kernel's static LDS holds two frontier copies of 2048 cells); the
   // rows' entries of cells with larger counts are flagged first
@@ -1096,34 +1048,56 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
     ProfScope ps("kahn", s);
     HIP_TRY(sweep::launch_kahn(a, lds_cnt, max_cells, s));
   }
-  // (no synchronisation here: the depths and the cycle flag are read once, at the end)
+  HIP_TRY(sweep::launch_count_slices(a, s));
   // the inverse schedule of cells that a cyclic graph leaves out stays -1
   HIP_TRY(sweep::launch_fill_i32(a.inv, T, -1, s));
   HIP_TRY(sweep::launch_sort_levels(a, s));
-  HIP_TRY(sweep::launch_gather_len(a, n_blocks, s));
-  // row lengths in schedule order -> row pointers
-  HIP_TRY(D->up_ptr.alloc(8 * (T + 1)));
-  HIP_TRY(D->dn_ptr.alloc(8 * (T + 1)));
-  a.up_ptr = D->up_ptr.as<int64_t>();
-  a.dn_ptr = D->dn_ptr.as<int64_t>();
+  // the depths, the slices per unit and the cycle flag
+  std::vector<int32_t> depth(n_units), nsl(n_units);
+  int32_t err = 0;
+  HIP_TRY(hipMemcpyAsync(depth.data(), depth_d.p, 4 * n_units, hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipMemcpyAsync(nsl.data(), nsl_d.p, 4 * n_units, hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipMemcpyAsync(&err, err_d.p, 4, hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipStreamSynchronize(s));
+  if (err) return fail(SWEEP_ERR_CYCLE, "a dependency graph is cyclic: some tasks never become ready");
+  std::vector<int64_t> slice_base(n_units + 1, 0);
+  for (int u = 0; u < n_units; ++u) slice_base[u + 1] = slice_base[u] + nsl[u];
+  const int64_t ns = D->n_slices = slice_base[n_units];
+  HIP_TRY(D->slice_base.alloc(8 * (size_t)(n_units + 1)));
+  HIP_TRY(hipMemcpyAsync(D->slice_base.p, slice_base.data(), 8 * (size_t)(n_units + 1), hipMemcpyHostToDevice, s));
+  HIP_TRY(D->sl_up.alloc(sizeof(sweep::SliceRec) * (size_t)ns));
+  HIP_TRY(D->sl_dn.alloc(sizeof(sweep::SliceRec) * (size_t)ns));
+  HIP_TRY(np_up.alloc(4 * (size_t)(ns + 1)));
+  HIP_TRY(np_dn.alloc(4 * (size_t)(ns + 1)));
+  HIP_TRY(pb_up.alloc(8 * (size_t)(ns + 1)));
+  HIP_TRY(pb_dn.alloc(8 * (size_t)(ns + 1)));
+  a.slice_base = D->slice_base.as<int64_t>();
+  a.n_slices = ns;
+  a.sl_up = D->sl_up.as<sweep::SliceRec>();
+  a.sl_dn = D->sl_dn.as<sweep::SliceRec>();
+  a.np_up = np_up.as<int32_t>();
+  a.np_dn = np_dn.as<int32_t>();
+  a.pb_up = pb_up.as<int64_t>();
+  a.pb_dn = pb_dn.as<int64_t>();
+  HIP_TRY(sweep::launch_slices(a, s));
+  HIP_TRY(sweep::launch_fill_i32(a.np_up + ns, 1, 0, s));
+  HIP_TRY(sweep::launch_fill_i32(a.np_dn + ns, 1, 0, s));
+  HIP_TRY(sweep::launch_gather_tasks(a, s));
+  // entry pairs per slice -> the slices' first pairs
   size_t tmp_bytes = 0;
-  HIP_TRY(sweep::launch_scan_len(a.len_up, a.up_ptr, T + 1, nullptr, &tmp_bytes, s));
+  HIP_TRY(sweep::launch_scan_len(a.np_up, pb_up.as<int64_t>(), ns + 1, nullptr, &tmp_bytes, s));
   HIP_TRY(scan_tmp.alloc(tmp_bytes));
-  HIP_TRY(sweep::launch_scan_len(a.len_up, a.up_ptr, T + 1, scan_tmp.p, &tmp_bytes, s));
-  HIP_TRY(sweep::launch_scan_len(a.len_dn, a.dn_ptr, T + 1, scan_tmp.p, &tmp_bytes, s));
-  HIP_TRY(D->up.alloc(8 * std::max<int64_t>(D->n_up, 1)));
-  HIP_TRY(D->dn.alloc(8 * std::max<int64_t>(D->n_dn, 1)));
-  a.up = D->up.as<int2>();
-  a.dn = D->dn.as<int2>();
+  HIP_TRY(sweep::launch_scan_len(a.np_up, pb_up.as<int64_t>(), ns + 1, scan_tmp.p, &tmp_bytes, s));
+  HIP_TRY(sweep::launch_scan_len(a.np_dn, pb_dn.as<int64_t>(), ns + 1, scan_tmp.p, &tmp_bytes, s));
+  // pairs hold two entries, and an odd row's last one only one
+  HIP_TRY(D->up.alloc(8 * (size_t)(D->n_up + T)));
+  HIP_TRY(D->dn.alloc(8 * (size_t)(D->n_dn + T)));
+  a.up = D->up.as<int4>();
+  a.dn = D->dn.as<int4>();
   {
     ProfScope ps("fill", s);
-    HIP_TRY(sweep::launch_fill(a, n_blocks, s));
+    HIP_TRY(sweep::launch_fill(a, s));
   }
-  HIP_TRY(D->lev_up.alloc(8 * (T + 2 * (int64_t)n_units)));
-  HIP_TRY(D->lev_dn.alloc(8 * (T + 2 * (int64_t)n_units)));
-  a.lev_up = D->lev_up.as<int64_t>();
-  a.lev_dn = D->lev_dn.as<int64_t>();
-  HIP_TRY(sweep::launch_level_entries(a, s));
   HIP_TRY(D->vol.alloc(4 * D->C_total));
   for (int m = 0; m < n_meshes; ++m)
     HIP_TRY(sweep::launch_d2f(meshes[m].cell_volume, D->vol.as<float>() + D->mesh_off[m],
@@ -1182,30 +1156,25 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
       if (md[m].face_shift != nullptr) HIP_TRY(sweep::launch_pdir(a, md[m], m, s));
     HIP_TRY(hipStreamSynchronize(s));  // the local counts and scans are released here
   }
-  std::vector<int32_t> depth(n_units);
-  int32_t err = 0;
-  Buf ue_d;  // row entries per unit (the sweep addresses a unit's rows with 32-bit offsets)
-  HIP_TRY(ue_d.alloc(16 * (size_t)n_units));
-  HIP_TRY(sweep::launch_unit_entries(D->units_d.as<Unit>(), n_units, D->up_ptr.as<int64_t>(),
-                                     D->dn_ptr.as<int64_t>(), ue_d.as<int64_t>(), s));
-  std::vector<int64_t> ue(2 * (size_t)n_units);
-  HIP_TRY(hipMemcpyAsync(ue.data(), ue_d.p, 16 * (size_t)n_units, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(depth.data(), depth_d.p, 4 * n_units, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(&err, err_d.p, 4, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
-  if (err) return fail(SWEEP_ERR_CYCLE, "a dependency graph is cyclic: some tasks never become ready");
-  for (int u = 0; u < n_units; ++u)
-    if (8 * std::max(ue[2 * u], ue[2 * u + 1]) > sweep::kMaxBufBytes)
-      return fail(SWEEP_ERR_UNSUPPORTED, "mesh %d, direction %d: %lld row entries exceed the sweep's "
-                  "32-bit buffer range", D->units[u].mesh, D->units[u].dir,
-                  (long long)std::max(ue[2 * u], ue[2 * u + 1]));
-  D->max_cells = max_cells;
-  D->unit_up.resize(n_units);
-  D->unit_dn.resize(n_units);
-  for (int u = 0; u < n_units; ++u) {
-    D->unit_up[u] = ue[2 * u];
-    D->unit_dn[u] = ue[2 * u + 1];
+  // a unit whose rows are too long for 32-bit offsets (possible only if its mesh has that
+  // many half-faces)
+  int64_t most_faces = 0;
+  for (int m = 0; m < n_meshes; ++m) most_faces = std::max(most_faces, meshes[m].n_half_faces);
+  if (8 * most_faces > sweep::kMaxBufBytes) {
+    Buf ue_d;
+    HIP_TRY(ue_d.alloc(16 * (size_t)n_units));
+    HIP_TRY(sweep::launch_fill_i32(ue_d.as<int32_t>(), 4 * (int64_t)n_units, 0, s));
+    HIP_TRY(sweep::launch_unit_entries(D->units_d.as<Unit>(), n_units, a.len_up, a.len_dn, ue_d.as<int64_t>(), s));
+    std::vector<int64_t> ue(2 * (size_t)n_units);
+    HIP_TRY(hipMemcpyAsync(ue.data(), ue_d.p, 16 * (size_t)n_units, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    for (int u = 0; u < n_units; ++u)
+      if (8 * std::max(ue[2 * u], ue[2 * u + 1]) > sweep::kMaxBufBytes)
+        return fail(SWEEP_ERR_UNSUPPORTED, "mesh %d, direction %d: %lld row entries exceed the sweep's "
+                    "32-bit buffer range", D->units[u].mesh, D->units[u].dir,
+                    (long long)std::max(ue[2 * u], ue[2 * u + 1]));
   }
+  D->max_cells = max_cells;
   HIP_TRY(D->flag.alloc(4));
   HIP_TRY(sweep::launch_fill_i32(D->flag.as<int32_t>(), 1, 0, s));
   for (int u = 0; u < n_units; ++u) {
@@ -1276,8 +1245,8 @@ sweep_status_t sweep_dag_info(sweep_dag_t d, sweep_dag_info_t* info) {
   info->max_depth = mx;
   info->min_depth = mn;
   info->mean_depth = sum / d->units.size();
-  const Buf* bufs[] = {&d->sched, &d->indeg, &d->lp, &d->lev_up, &d->lev_dn,
-                       &d->up_ptr, &d->dn_ptr, &d->up, &d->dn, &d->aperp, &d->aperp_s, &d->vol_s, &d->bnd, &d->vol,
+  const Buf* bufs[] = {&d->sched, &d->inv, &d->indeg, &d->lp, &d->len_up, &d->len_dn,
+                       &d->slice_base, &d->sl_up, &d->sl_dn, &d->up, &d->dn, &d->aperp, &d->aperp_s, &d->vol_s, &d->bnd, &d->vol,
                        &d->pcell, &d->pf_ptr, &d->pnb, &d->pwf, &d->pwa, &d->ptask, &d->pc_map};
   int64_t b = 0;
   for (const Buf* x : bufs) b += (int64_t)x->bytes;
@@ -1395,7 +1364,6 @@ sweep_status_t sweep_forward(sweep_dag_t d, int32_t G, const float* kappa, const
   const int64_t CG = d->C_total * G;
   const int64_t DCG = CG * d->D;
   ST_TRY(ensure_reduce_tables(d, G));
-  ST_TRY(prepare_steps(d, p, G, s));
   if (!saved) HIP_TRY(d->phi_a.alloc(4 * DCG));
   if (periodic && n_inner > 1) HIP_TRY(d->phi_b.alloc(4 * DCG));
   if (warm) HIP_TRY(d->phi_w.alloc(4 * DCG));
@@ -1577,7 +1545,6 @@ sweep_status_t sweep_adjoint(sweep_dag_t d, int32_t G, const float* kappa,
   // are recomputed into phi_a (x^{P-1}) and xpass (the others)
   const int P = merge ? std::max(p.n_pbc, p.n_scat) : periodic ? p.n_pbc : 1;
   ST_TRY(ensure_mesh_tables(d));
-  ST_TRY(prepare_steps(d, p, G, s));
   HIP_TRY(d->lam.alloc(4 * DCG));
   HIP_TRY(d->gsrc.alloc(4 * CG));
   HIP_TRY(d->dk64.alloc(8 * CG));
@@ -1803,7 +1770,7 @@ sweep_status_t sweep_tune(sweep_dag_t d, int32_t G, const float* kappa, const fl
   sweep_status_t st = SWEEP_OK;
   for (int block : {256, 512, 1024}) {
     if (block > sweep::kSweepMaxBlock(gn)) continue;
-    const int r0 = default_ring(d, gn, block);
+    const int r0 = default_ring(d, gn, 1);
     for (int ring : {r0 / 4, r0 / 2, r0}) {
       if (ring < 64) continue;
       FwdPlan q = p;

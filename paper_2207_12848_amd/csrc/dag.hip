@@ -7,9 +7,10 @@
 //   k_count   per task (unit, cell): upwind/downwind counts, Aperp, boundary outflow
 //   k_kahn    per unit, one workgroup: levels by Kahn's algorithm (algorithm 2's
 //             counters), ready cells compacted with wavefront ballots
-//   k_gather_len, k_fill  row lengths and rows of the upwind/downwind lists,
-//             stored in schedule order so a level's rows are contiguous (and
-//             Aperp in schedule order, for the per-call preparation)
+//   k_slices  the sweep's slices: every level in runs of at most 64 tasks
+//   k_gather_tasks, k_fill  row lengths and rows of the upwind/downwind lists,
+//             stored slice by slice in schedule order (and Aperp and the volumes in
+//             schedule order, for the per-call preparation)
 #include <hipcub/hipcub.hpp>
 
 #include <type_traits>
@@ -49,7 +50,6 @@ __device__ __forceinline__ double orient(double ox, double oy, double oz, const 
 // exactly what its neighbour receives.
 __device__ __forceinline__ float face_w(double A, double s) { return (float)(A * fabs(s)); }
 
-// Unit of block b (units own consecutive block ranges).
 // Workgroups are dispatched round-robin over the 8 XCDs, each with its own L2
 // cache: this renumbering gives each XCD one contiguous range of the grid, so
 // the workgroups an XCD runs together belong to few units and share those
@@ -59,15 +59,6 @@ __device__ __forceinline__ int xcd_block(int b, int nb) {
   const int per = nb / kXcd, rem = nb % kXcd;
   const int x = b % kXcd;
   return x * per + min(x, rem) + b / kXcd;
-}
-
-__device__ __forceinline__ int unit_of_block(const int32_t* blk_base, int n_units, int b) {
-  int lo = 0, hi = n_units - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (blk_base[mid] <= b) lo = mid; else hi = mid - 1;
-  }
-  return lo;
 }
 
 // The cell-order kernel stages a tile of kTileCells consecutive cells' faces
@@ -840,23 +831,6 @@ __global__ __launch_bounds__(kSortBlock) void k_sort_levels(DagBuildArgs a) {
   }
 }
 
-// Row lengths of every task at its schedule slot (the input of the row-pointer scan).
-__global__ __launch_bounds__(kCountBlock) void k_gather_len(DagBuildArgs a) {
-  const int blk = xcd_block(blockIdx.x, gridDim.x);
-  const int u = unit_of_block(a.blk_base, a.n_units, blk);
-  const Unit U = a.units[u];
-  const int k = (blk - a.blk_base[u]) * kCountBlock + threadIdx.x;
-  if (k >= U.n_cells) return;
-  const int64_t t = U.task_base + k;
-  // slots past the scheduled tasks (a cyclic graph, reported after the build) get no row
-  const int scheduled = a.lp[U.lp_base + a.depth[u]];
-  const int c = k < scheduled ? a.sched[t] : -1;
-  a.len_up[t] = c >= 0 ? a.indeg[U.task_base + c] : 0;
-  a.len_dn[t] = c >= 0 ? a.rowlen_dn[U.task_base + c] : 0;
-  a.aperp_s[t] = c >= 0 ? a.aperp[U.task_base + c] : 0.0f;
-  a.vol_s[t] = c >= 0 ? (float)a.meshes[U.mesh].cell_volume[c] : 0.0f;
-}
-
 // Per mesh: the largest face count of a cell, and the overflow room the wide
 // rows need ((faces + 2) ints per direction for every cell with more than
 // row_cap faces), accumulated into out[0] (max) and out[1] (sum).
@@ -902,57 +876,241 @@ __global__ void k_face_codes(MeshDev M, int32_t* fcode) {
   fcode[f] = nb < 0 ? -1 : (periodic ? -(nb + 2) : nb);
 }
 
-// Rows of the upwind and downwind lists, which lie in schedule order; the
-// tasks are visited in cell order: each wavefront takes 64 consecutive cells
-// of one unit, so that the face records it reads are contiguous and the
-// neighbours' schedule positions (from the unit's inverse schedule) are
-// gathered from a few lines.  Every lane first loads one cell's task (schedule
-// slot, row pointers, face range); then, 16 cells per round, 16 lanes share
-// one task, one face per lane, 16 faces at a time.  Each face's neighbour code
-// and signed weight (from k_count) give its class; a ballot over the 16 lanes
-// gives every entry its place in the row (rows keep the cell's face order).
-// Cells of one level that are consecutive in id have consecutive slots, so
-// their rows are written next to each other.
+// Unit of a slice.
+__device__ __forceinline__ int unit_of_slice(const int64_t* slice_base, int n_units, int64_t i) {
+  int lo = 0, hi = n_units - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (slice_base[mid] <= i) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+
+// Slices of the sweep: every level's tasks in ceil(w / 64) runs of consecutive
+// schedule positions with (nearly) equal task counts.
+__device__ __forceinline__ int level_slices(int w) { return (w + 63) >> 6; }
+
+__global__ __launch_bounds__(256) void k_count_slices(DagBuildArgs a) {
+  __shared__ int s_n;
+  const Unit U = a.units[blockIdx.x];
+  const int depth = a.depth[blockIdx.x];
+  const int32_t* lp = a.lp + U.lp_base;
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
+  int n = 0;
+  for (int l = threadIdx.x; l < depth; l += blockDim.x) n += level_slices(lp[l + 1] - lp[l]);
+  for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
+  if ((threadIdx.x & 63) == 0) atomicAdd(&s_n, n);
+  __syncthreads();
+  if (threadIdx.x == 0) a.n_unit_slices[blockIdx.x] = s_n;
+}
+
+// The slice tables of both walks (SliceRec but for the entries' place, which
+// k_fill adds), one workgroup per unit: a scan over the levels gives each its
+// first slice.
+constexpr int kSlicesBlock = 256;
+__global__ __launch_bounds__(kSlicesBlock) void k_slices(DagBuildArgs a) {
+  __shared__ int s_scan[kSlicesBlock];
+  __shared__ int s_carry;
+  const Unit U = a.units[blockIdx.x];
+  const int depth = a.depth[blockIdx.x];
+  const int tid = threadIdx.x;
+  const int32_t* lp = a.lp + U.lp_base;
+  const int64_t base = a.slice_base[blockIdx.x];
+  const int ns = (int)(a.slice_base[blockIdx.x + 1] - base);
+  const int C = U.n_cells;
+  if (tid == 0) s_carry = 0;
+  __syncthreads();
+  for (int l0 = 0; l0 < depth; l0 += kSlicesBlock) {
+    const int l = l0 + tid;
+    const int k0 = l < depth ? lp[l] : 0;
+    const int w = l < depth ? lp[l + 1] - k0 : 0;
+    const int n = level_slices(w);
+    s_scan[tid] = n;
+    __syncthreads();
+    for (int o = 1; o < kSlicesBlock; o <<= 1) {  // inclusive scan over the block
+      const int x = tid >= o ? s_scan[tid - o] : 0;
+      __syncthreads();
+      s_scan[tid] += x;
+      __syncthreads();
+    }
+    const int off = s_carry + s_scan[tid] - n;
+    for (int c = 0; c < n; ++c) {
+      const int ka = k0 + (int)(((int64_t)c * w) / n), kb = k0 + (int)(((int64_t)(c + 1) * w) / n);
+      SliceRec f{ka, kb - ka, off, k0 + w, k0, 0u, 0u, 0};
+      SliceRec r{ka, kb - ka, ns - (off + n), C - k0, C - (k0 + w), 0u, 0u, 0};
+      a.sl_up[base + off + c] = f;
+      a.sl_dn[base + off + c] = r;
+    }
+    __syncthreads();
+    if (tid == kSlicesBlock - 1) s_carry += s_scan[tid];
+    __syncthreads();
+  }
+}
+
+// Per task in schedule order: row lengths, Aperp and the cell's volume; per
+// slice: its rows' entry pairs (the input of the scan that places them).  One
+// wavefront per slice.
+__global__ __launch_bounds__(kCountBlock) void k_gather_tasks(DagBuildArgs a) {
+  const int64_t i = (int64_t)xcd_block(blockIdx.x, gridDim.x) * (kCountBlock / 64) + (threadIdx.x >> 6);
+  if (i >= a.n_slices) return;
+  const int lane = threadIdx.x & 63;
+  const Unit U = a.units[unit_of_slice(a.slice_base, a.n_units, i)];
+  const int k0 = a.sl_up[i].k0, cnt = a.sl_up[i].cnt;
+  int pu = 0, pd = 0;
+  if (lane < cnt) {
+    const int64_t t = U.task_base + k0 + lane;
+    const int c = a.sched[t];
+    const int nu = a.indeg[U.task_base + c], nd = a.rowlen_dn[U.task_base + c];
+    a.len_up[t] = nu;
+    a.len_dn[t] = nd;
+    a.aperp_s[t] = a.aperp[U.task_base + c];
+    a.vol_s[t] = (float)a.meshes[U.mesh].cell_volume[c];
+    pu = (nu + 1) >> 1;
+    pd = (nd + 1) >> 1;
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    pu += __shfl_xor(pu, o);
+    pd += __shfl_xor(pd, o);
+  }
+  if (lane == 0) {
+    a.np_up[i] = pu;
+    a.np_dn[i] = pd;
+  }
+}
+
+// Row entries of the units for the check of the 32-bit buffer range (meshes
+// with very many faces only), one workgroup per unit.
+__global__ __launch_bounds__(256) void k_unit_entries(const Unit* units, const int32_t* len_up,
+                                                      const int32_t* len_dn, unsigned long long* out) {
+  const Unit U = units[blockIdx.x];
+  unsigned long long u = 0, d = 0;
+  for (int k = threadIdx.x; k < U.n_cells; k += blockDim.x) {
+    u += (unsigned long long)len_up[U.task_base + k];
+    d += (unsigned long long)len_dn[U.task_base + k];
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    u += __shfl_xor(u, o);
+    d += __shfl_xor(d, o);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    atomicAdd(out + 2 * blockIdx.x, u);
+    atomicAdd(out + 2 * blockIdx.x + 1, d);
+  }
+}
+
+// Rows of the upwind and downwind lists.  The rows of a slice (up to 64 tasks)
+// lie together as entry pairs, column by column: pair j of the rows longer than
+// 2 j, in task order, then pair j + 1 of those longer than 2 j + 2, and so on,
+// so that a wavefront with one task per lane reads each column with one
+// coalesced 128-bit load and no padding but the second half of an odd row's
+// last pair (factor 0).  An entry is (position code, w): 4 (p + 1), p the
+// neighbour's position in the walk that reads the row (upwind rows: its
+// schedule position; downwind rows, walked backwards: the unit's last position
+// minus it), so 0 means no entry and the code with the low bits masked is the
+// byte offset of a ring slot.  Rows keep the cell's face order.
+//
+// One wavefront per slice.  Every lane first loads one task (cell, row lengths,
+// face range); then, 16 tasks per round, 16 lanes share one task, one face per
+// lane, 16 faces at a time.  Each face's neighbour code and signed weight (from
+// k_count) give its class, a ballot over the 16 lanes its entry number in the
+// row, and the columns' lane masks (LDS) its place.  All the stores of a slice
+// fall into its few KB.
 constexpr int kFillBlock = 256;
+constexpr int kFillCols = 32;  // pair columns with a mask in LDS (longer rows: a second look at their faces)
 
 // Five wavefronts per SIMD: the register budget (at most 102 VGPRs) still
 // compiles without spills.
 template <bool ALIGNED>
 __global__ __launch_bounds__(kFillBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_fill(DagBuildArgs a) {
-  const int blk = xcd_block(blockIdx.x, gridDim.x);
-  const int u = unit_of_block(a.blk_base, a.n_units, blk);
-  const Unit U = a.units[u];
+  __shared__ unsigned long long s_mask[kFillBlock / 64][2][kFillCols];
+  __shared__ int s_col[kFillBlock / 64][2][kFillCols];
+  const int wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int64_t sl = (int64_t)xcd_block(blockIdx.x, gridDim.x) * (kFillBlock / 64) + wv;
+  if (sl >= a.n_slices) return;  // (wavefronts share nothing here: no barrier below)
+  const Unit U = a.units[unit_of_slice(a.slice_base, a.n_units, sl)];
   const MeshDev M = a.meshes[U.mesh];
   const int64_t tb = U.task_base;
-  const int lane = threadIdx.x & 63;
+  const int C = U.n_cells;
   const int li = lane & 15;
   const int g = lane >> 4;
   const int32_t* inv = a.inv + tb;
   const float* wf = a.wface + (int64_t)a.D * M.face_off + (int64_t)U.dir * M.n_faces;
-  const int kw = (blk - a.blk_base[u]) * kFillBlock + (threadIdx.x & ~63);
-  if (kw >= U.n_cells) return;
-  // lane L: the task of cell kw + L (cells left out of the schedule of a cyclic
-  // graph, reported after the build, have slot -1 and get no row)
-  const int cl = kw + lane;
-  const int k = cl < U.n_cells ? inv[cl] : -1;
-  const bool kv = k >= 0 && k < a.lp[U.lp_base + a.depth[u]];
-  const int kc = kv ? k : 0;
-  const int c = kv ? cl : 0;
-  const int64_t eu0 = a.up_ptr[tb + kc];
-  const int64_t ed0 = a.dn_ptr[tb + kc];
+  const int k0 = a.sl_up[sl].k0, cnt = a.sl_up[sl].cnt;
+  const int64_t bu = a.pb_up[sl], bd = a.pb_dn[sl];
+  const bool act = lane < cnt;
+  const int c = act ? a.sched[tb + k0 + lane] : 0;
+  const int nu = act ? a.len_up[tb + k0 + lane] : 0;
+  const int nd = act ? a.len_dn[tb + k0 + lane] : 0;
   const int64_t f0 = M.face_ptr[c];
-  const int nf = kv ? (int)(M.face_ptr[c + 1] - f0) : 0;
-  const int rounds = min(4, (U.n_cells - kw + 15) >> 4);
+  const int nf = act ? (int)(M.face_ptr[c + 1] - f0) : 0;
+  int tot[2] = {0, 0};  // pairs of the columns so far
+  auto columns = [&](int side, int n) {
+    for (int j = 0; j < kFillCols; ++j) {
+      const unsigned long long m = __ballot(n > 2 * j);
+      if (m == 0ull) break;
+      if (lane == 0) {
+        s_mask[wv][side][j] = m;
+        s_col[wv][side][j] = tot[side];
+      }
+      tot[side] += __popcll(m);
+    }
+  };
+  columns(0, nu);
+  columns(1, nd);
+  if (lane == 0) {
+    SliceRec& ru = a.sl_up[sl];
+    ru.base_lo = (uint32_t)bu;
+    ru.base_hi = (uint32_t)((uint64_t)bu >> 32);
+    ru.np = (int)(a.pb_up[sl + 1] - bu);
+    SliceRec& rd = a.sl_dn[sl];
+    rd.base_lo = (uint32_t)bd;
+    rd.base_hi = (uint32_t)((uint64_t)bd >> 32);
+    rd.np = (int)(a.pb_dn[sl + 1] - bd);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the masks, to the wavefront's other lanes
+  // entry e of a row of n entries whose pair is `pair`; the last entry of an odd
+  // row also writes the empty half
+  auto put = [&](int4* pair, int e, int n, int x, float w) {
+    if ((e & 1) == 0 && e == n - 1) {
+      *pair = make_int4(x, __float_as_int(w), x, 0);
+    } else {
+      reinterpret_cast<int2*>(pair)[e & 1] = make_int2(x, __float_as_int(w));
+    }
+  };
+  // class, weight and neighbour of one face: code >= 0 is an interior neighbour
+  auto face = [&](int64_t f, bool has, int& code, bool& up, bool& dn, float& wu, float& wd) {
+    code = M.fcode[f];
+    const float ws = wf[f];
+    if (ALIGNED) {
+      // radiation leaves through the faces the cell chose and enters through the
+      // faces whose twin the neighbour chose
+      const float wi = wf[code != -1 ? M.face_twin[f] : f];
+      up = has && code >= 0 && !isnan(wi);
+      dn = has && code >= 0 && !isnan(ws);
+      wd = ws;
+      wu = wi;
+    } else {
+      const bool carries = has && !isnan(ws);
+      const bool in = carries && signbit(ws);
+      up = in && code >= 0;               // interior inflow
+      dn = carries && !in && code >= 0;   // interior outflow
+      wd = wu = fabsf(ws);
+    }
+  };
   const uint32_t below = (1u << li) - 1u;
+  const int rounds = (cnt + 15) >> 4;
   for (int r = 0; r < rounds; ++r) {
-    // group g handles slots kw + 16 r + 4 g + j, j = 0..3
-    int64_t eu[4], ed[4], fb[4];
-    int nfj[4];
+    // group g handles tasks 16 r + 4 g + j of the slice, j = 0..3
+    int eu[4], ed[4], lu[4], ld[4], nfj[4];
+    int64_t fb[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int src = 16 * r + 4 * g + j;
-      eu[j] = __shfl(eu0, src);
-      ed[j] = __shfl(ed0, src);
+      eu[j] = ed[j] = 0;
+      lu[j] = __shfl(nu, src);
+      ld[j] = __shfl(nd, src);
       fb[j] = __shfl(f0, src);
       nfj[j] = __shfl(nf, src);
     }
@@ -962,41 +1120,57 @@ __global__ __launch_bounds__(kFillBlock) __attribute__((amdgpu_waves_per_eu(5)))
     for (int h = 0; h * 16 < mx; ++h) {
       const int fo = h * 16 + li;
       int code[4];
-      float ws[4], wi[4];  // the face's own signed weight; scheme (b): its twin's
+      bool up[4], dn[4];
+      float wu[4], wd[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int64_t f = fo < nfj[j] ? fb[j] + fo : 0;  // face 0 exists
-        code[j] = M.fcode[f];
-        ws[j] = wf[f];
-        if (ALIGNED) wi[j] = wf[code[j] != -1 ? M.face_twin[f] : f];
-      }
+      for (int j = 0; j < 4; ++j)
+        face(fo < nfj[j] ? fb[j] + fo : 0, fo < nfj[j], code[j], up[j], dn[j], wu[j], wd[j]);  // face 0 exists
       int pos[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) pos[j] = inv[code[j] >= 0 ? code[j] : 0];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        bool up, dn;
-        float w, wu;
-        if (ALIGNED) {
-          // radiation leaves through the faces the cell chose and enters through
-          // the faces whose twin the neighbour chose
-          up = fo < nfj[j] && code[j] >= 0 && !isnan(wi[j]);
-          dn = fo < nfj[j] && code[j] >= 0 && !isnan(ws[j]);
-          w = ws[j];
-          wu = wi[j];
-        } else {
-          const bool has = fo < nfj[j] && !isnan(ws[j]);
-          const bool in = has && signbit(ws[j]);
-          up = in && code[j] >= 0;           // interior inflow
-          dn = has && !in && code[j] >= 0;   // interior outflow
-          w = wu = fabsf(ws[j]);
+        const int src = 16 * r + 4 * g + j;
+        const uint32_t mu = (uint32_t)(__ballot(up[j]) >> (16 * g)) & 0xffffu;
+        const uint32_t md = (uint32_t)(__ballot(dn[j]) >> (16 * g)) & 0xffffu;
+        if (up[j] || dn[j]) {
+          const int side = up[j] ? 0 : 1;
+          const int e = up[j] ? eu[j] + __popc(mu & below) : ed[j] + __popc(md & below);
+          const int col = e >> 1;
+          if (col < kFillCols) {
+            const int at = s_col[wv][side][col] + __popcll(s_mask[wv][side][col] & ((1ull << src) - 1ull));
+            if (up[j]) put(a.up + bu + at, e, lu[j], 4 * (pos[j] + 1), wu[j]);
+            else put(a.dn + bd + at, e, ld[j], 4 * (C - pos[j]), wd[j]);
+          }
         }
-        const uint32_t mu = (uint32_t)(__ballot(up) >> (16 * g)) & 0xffffu;
-        const uint32_t md = (uint32_t)(__ballot(dn) >> (16 * g)) & 0xffffu;
-        if (up) a.up[eu[j] + __popc(mu & below)] = make_int2(pos[j], __float_as_int(wu));
-        if (dn) a.dn[ed[j] + __popc(md & below)] = make_int2(pos[j], __float_as_int(w));
         eu[j] += __popc(mu);
         ed[j] += __popc(md);
+      }
+    }
+  }
+  // rows longer than the columns held in LDS: column by column, each lane looks
+  // through its own task's faces for the two entries
+  for (int side = 0; side < 2; ++side) {
+    const int n = side == 0 ? nu : nd;
+    for (int j = kFillCols;; ++j) {
+      const unsigned long long m = __ballot(n > 2 * j);
+      if (m == 0ull) break;
+      const int64_t at = tot[side] + __popcll(m & ((1ull << lane) - 1ull));
+      tot[side] += __popcll(m);
+      if (n > 2 * j) {
+        int e = 0;
+        for (int q = 0; q < nf; ++q) {
+          int code;
+          bool up, dn;
+          float wu, wd;
+          face(f0 + q, true, code, up, dn, wu, wd);
+          if (!(side == 0 ? up : dn)) continue;
+          if ((e >> 1) == j) {
+            if (side == 0) put(a.up + bu + at, e, n, 4 * (inv[code] + 1), wu);
+            else put(a.dn + bd + at, e, n, 4 * (C - inv[code]), wd);
+          }
+          ++e;
+        }
       }
     }
   }
@@ -1068,26 +1242,6 @@ __global__ void k_pdir(DagBuildArgs a, MeshDev M, int mesh) {
   a.ptask[i] = (int32_t)(U.task_base + a.inv[U.task_base + c]);
 }
 
-// First row entry of every level (per unit), so a level's rows form one block.
-__global__ void k_level_entries(DagBuildArgs a) {
-  const Unit U = a.units[blockIdx.x];
-  const int depth = a.depth[blockIdx.x];
-  for (int l = threadIdx.x; l <= depth + 1; l += blockDim.x) {
-    const int64_t k = U.task_base + a.lp[U.lp_base + l];
-    a.lev_up[U.lp_base + l] = a.up_ptr[k];
-    a.lev_dn[U.lp_base + l] = a.dn_ptr[k];
-  }
-}
-
-__global__ void k_unit_entries(const Unit* units, int32_t n_units, const int64_t* up_ptr,
-                               const int64_t* dn_ptr, int64_t* out) {
-  const int u = blockIdx.x * blockDim.x + threadIdx.x;
-  if (u >= n_units) return;
-  const int64_t t0 = units[u].task_base, t1 = t0 + units[u].n_cells;
-  out[2 * u] = up_ptr[t1] - up_ptr[t0];
-  out[2 * u + 1] = dn_ptr[t1] - dn_ptr[t0];
-}
-
 // Tasks per level, one workgroup per unit.
 __global__ void k_level_widths(const Unit* units, const int32_t* lp, int32_t mesh,
                                unsigned long long* width, int32_t n_levels) {
@@ -1096,76 +1250,6 @@ __global__ void k_level_widths(const Unit* units, const int32_t* lp, int32_t mes
   const int32_t* l = lp + U.lp_base;
   for (int k = threadIdx.x; k < min(U.depth, n_levels); k += blockDim.x)
     atomicAdd(width + k, (unsigned long long)(l[k + 1] - l[k]));
-}
-
-// Steps of the level-synchronous sweep, one workgroup per unit: every level l
-// (w tasks, e the larger of its upwind and downwind row entries) is cut into
-// n = max(1, ceil(w / cap_t), ceil(1.15 e / cap_e)) runs of consecutive
-// schedule positions with equal task counts (floor(c w / n) from the level's
-// start).  The tasks of a run are independent, so each run is one step of the
-// sweep; the 15 % margin keeps the runs' entry counts within cap_e for rows of
-// ordinary spread (a run above it is still correct, on the sweep's slower
-// path).  Writes the steps' first positions and entries (plus one closing
-// step) from step_base[u], and their number.
-constexpr int kStepsBlock = 256;
-__global__ __launch_bounds__(kStepsBlock) void k_steps(const Unit* units, const int32_t* lp,
-                                                       const int64_t* lev_up, const int64_t* lev_dn,
-                                                       const int64_t* up_ptr, const int64_t* dn_ptr,
-                                                       const int64_t* step_base, int32_t cap_t,
-                                                       int32_t cap_e, int32_t* sk, int64_t* seu,
-                                                       int64_t* sed, int32_t* n_steps) {
-  __shared__ int s_scan[kStepsBlock];
-  __shared__ int s_carry;
-  const Unit U = units[blockIdx.x];
-  const int tid = threadIdx.x;
-  const int32_t* l = lp + U.lp_base;
-  const int64_t* lu = lev_up + U.lp_base;
-  const int64_t* ld = lev_dn + U.lp_base;
-  const int64_t base = step_base[blockIdx.x];
-  const int64_t cap = step_base[blockIdx.x + 1] - base;  // room for the steps and the closing one
-  if (tid == 0) s_carry = 0;
-  __syncthreads();
-  for (int l0 = 0; l0 < U.depth; l0 += kStepsBlock) {
-    const int lv = l0 + tid;
-    int n = 0, k0 = 0, w = 0;
-    if (lv < U.depth) {
-      k0 = l[lv];
-      w = l[lv + 1] - k0;
-      const int64_t e = max(lu[lv + 1] - lu[lv], ld[lv + 1] - ld[lv]);
-      const int64_t ne = (e * 115 + 100LL * cap_e - 1) / (100LL * cap_e);
-      n = max(1, max((w + cap_t - 1) / cap_t, (int)ne));
-    }
-    s_scan[tid] = n;
-    __syncthreads();
-    for (int o = 1; o < kStepsBlock; o <<= 1) {  // inclusive scan over the block
-      const int x = tid >= o ? s_scan[tid - o] : 0;
-      __syncthreads();
-      s_scan[tid] += x;
-      __syncthreads();
-    }
-    const int off = s_carry + s_scan[tid] - n;
-    // (the host sizes the table above every count; a count past it is reported)
-    for (int c = 0; c < n && off + c + 1 < cap; ++c) {
-      const int kk = k0 + (int)(((int64_t)c * w) / n);
-      sk[base + off + c] = kk;
-      seu[base + off + c] = up_ptr[U.task_base + kk];
-      sed[base + off + c] = dn_ptr[U.task_base + kk];
-    }
-    __syncthreads();
-    if (tid == kStepsBlock - 1) s_carry += s_scan[tid];
-    __syncthreads();
-  }
-  if (tid == 0) {
-    const int ns = s_carry;
-    if (ns + 1 > cap) {
-      n_steps[blockIdx.x] = -1;
-      return;
-    }
-    sk[base + ns] = U.n_cells;
-    seu[base + ns] = up_ptr[U.task_base + U.n_cells];
-    sed[base + ns] = dn_ptr[U.task_base + U.n_cells];
-    n_steps[blockIdx.x] = ns;
-  }
 }
 
 __global__ void k_d2f(const double* in, float* out, int64_t n) {
@@ -1262,18 +1346,27 @@ hipError_t launch_sort_levels(const DagBuildArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_gather_len(const DagBuildArgs& a, int32_t n_blocks, hipStream_t s) {
-  if (n_blocks <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gather_len, dim3(n_blocks), dim3(kCountBlock), 0, s, a);
+hipError_t launch_count_slices(const DagBuildArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(k_count_slices, dim3(a.n_units), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
-hipError_t launch_fill(const DagBuildArgs& a, int32_t n_blocks, hipStream_t s) {
-  if (n_blocks <= 0) return hipSuccess;
-  if (a.scheme == SWEEP_SCHEME_ALIGNED)
-    hipLaunchKernelGGL(k_fill<true>, dim3(n_blocks), dim3(kFillBlock), 0, s, a);
-  else
-    hipLaunchKernelGGL(k_fill<false>, dim3(n_blocks), dim3(kFillBlock), 0, s, a);
+hipError_t launch_slices(const DagBuildArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(k_slices, dim3(a.n_units), dim3(kSlicesBlock), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_gather_tasks(const DagBuildArgs& a, hipStream_t s) {
+  if (a.n_slices <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_gather_tasks, dim3(grid1d(a.n_slices, kCountBlock / 64)), dim3(kCountBlock), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_fill(const DagBuildArgs& a, hipStream_t s) {
+  if (a.n_slices <= 0) return hipSuccess;
+  const dim3 grid(grid1d(a.n_slices, kFillBlock / 64));
+  if (a.scheme == SWEEP_SCHEME_ALIGNED) hipLaunchKernelGGL(k_fill<true>, grid, dim3(kFillBlock), 0, s, a);
+  else hipLaunchKernelGGL(k_fill<false>, grid, dim3(kFillBlock), 0, s, a);
   return hipGetLastError();
 }
 
@@ -1310,11 +1403,6 @@ hipError_t launch_face_codes(const MeshDev& m, int32_t* fcode, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_level_entries(const DagBuildArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_level_entries, dim3(a.n_units), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
 struct WidenToI64 {
   __host__ __device__ int64_t operator()(int32_t v) const { return (int64_t)v; }
 };
@@ -1328,11 +1416,11 @@ hipError_t launch_scan_len(const int32_t* in, int64_t* out, int64_t n, void* tmp
   return hipcub::DeviceScan::ExclusiveSum(tmp, *tmp_bytes, it, out, (int)n, s);
 }
 
-hipError_t launch_unit_entries(const Unit* units, int32_t n_units, const int64_t* up_ptr,
-                               const int64_t* dn_ptr, int64_t* out, hipStream_t s) {
+hipError_t launch_unit_entries(const Unit* units, int32_t n_units, const int32_t* len_up,
+                               const int32_t* len_dn, int64_t* out, hipStream_t s) {
   if (n_units <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_unit_entries, dim3(grid1d(n_units, 256)), dim3(256), 0, s, units, n_units,
-                     up_ptr, dn_ptr, out);
+  hipLaunchKernelGGL(k_unit_entries, dim3(n_units), dim3(256), 0, s, units, len_up, len_dn,
+                     reinterpret_cast<unsigned long long*>(out));
   return hipGetLastError();
 }
 
@@ -1341,16 +1429,6 @@ hipError_t launch_level_widths(const Unit* units, int32_t n_units, const int32_t
   if (n_units <= 0 || n_levels <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_level_widths, dim3(n_units), dim3(256), 0, s, units, lp, mesh,
                      reinterpret_cast<unsigned long long*>(width), n_levels);
-  return hipGetLastError();
-}
-
-hipError_t launch_steps(const Unit* units, int32_t n_units, const int32_t* lp, const int64_t* lev_up,
-                        const int64_t* lev_dn, const int64_t* up_ptr, const int64_t* dn_ptr,
-                        const int64_t* step_base, int32_t cap_t, int32_t cap_e, int32_t* step_k,
-                        int64_t* step_eu, int64_t* step_ed, int32_t* n_steps, hipStream_t s) {
-  if (n_units <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_steps, dim3(n_units), dim3(kStepsBlock), 0, s, units, lp, lev_up, lev_dn,
-                     up_ptr, dn_ptr, step_base, cap_t, cap_e, step_k, step_eu, step_ed, n_steps);
   return hipGetLastError();
 }
 

@@ -11,6 +11,26 @@ constexpr int32_t kErrKappa = 1;     // kappa negative or not finite
 constexpr int32_t kErrEmission = 2;  // emission negative or not finite
 constexpr int32_t kErrCell = 4;      // a task's denominator (Aperp + kappa V) not positive and finite
 constexpr int32_t kErrGrad = 8;      // dL/dJ or dL/dabsorbed not finite
+constexpr int32_t kErrStall = 16;    // a sweep's wait for earlier slices did not end (never expected)
+
+// Reads of a sweep's LDS counter before a wait gives up (about 0.2 s; a wait lasts
+// microseconds).
+constexpr int kSpinLimit = 1 << 22;
+
+// One slice of the sweep: at most 64 consecutive schedule positions of one level.
+// One table per sweep direction; positions, dependencies and level bounds are
+// those of its walk (the reverse walk counts positions from the unit's end).
+struct SliceRec {
+  int32_t k0;       // first schedule position
+  int32_t cnt;      // tasks
+  int32_t dep;      // slices of the walk's earlier levels
+  int32_t lim;      // the walk's position after the level's last task
+  int32_t ks;       // the walk's position of the level's first task
+  uint32_t base_lo; // first entry pair of the slice's rows (64-bit)
+  uint32_t base_hi;
+  int32_t np;       // entry pairs of the slice's rows
+};
+static_assert(sizeof(SliceRec) == 32, "two 128-bit loads");
 
 // Largest byte size of any array the sweep kernels address through a buffer
 // resource (32-bit offsets; offsets from kOob up stay past the end).
@@ -87,8 +107,6 @@ struct DagBuildArgs {
   int32_t* lp;     // level pointers
   int32_t* depth;  // [n_units]
   int32_t* err;    // set to 1 if a unit could not be fully ordered
-  int64_t* lev_up;  // per unit level table: first upwind-row entry of each level
-  int64_t* lev_dn;
   // periodic half-faces (the lists that fold the coupling between periodic passes
   // into the sources, built after the rows; see PinArgs)
   int32_t* npf;      // [C_total + 1] periodic half-faces of every cell (scan input)
@@ -105,12 +123,21 @@ struct DagBuildArgs {
   float* pwa;        // [D][n_pf] outflow weight (0 where the half-face is no outflow)
   int32_t* ptask;    // [D][n_pc] task of (direction, periodic cell)
   int32_t* pc_map;   // [C_total] periodic cell index of every cell, -1 for the others
-  int32_t* len_up;  // [T+1] row lengths in schedule order (scan input)
-  int32_t* len_dn;  // [T+1]
-  int64_t* up_ptr;  // [T+1]
-  int64_t* dn_ptr;  // [T+1]
-  int2* up;         // (position of the upwind task | -(partner cell + 1) for periodic inflow, w)
-  int2* dn;         // (position of the downwind task, w)
+  int32_t* len_up;  // [T] row lengths in schedule order
+  int32_t* len_dn;  // [T]
+  // slices of the sweep (see SliceRec): unit u's are [slice_base[u], slice_base[u + 1])
+  const int64_t* slice_base;  // [n_units + 1]
+  int64_t n_slices;
+  int32_t* n_unit_slices;     // [n_units] out of k_count_slices
+  SliceRec* sl_up;            // [n_slices] forward walk, upwind rows
+  SliceRec* sl_dn;            // [n_slices] reverse walk, downwind rows
+  int32_t* np_up;             // [n_slices + 1] entry pairs of every slice (scan input)
+  int32_t* np_dn;
+  const int64_t* pb_up;       // [n_slices + 1] first entry pair of every slice
+  const int64_t* pb_dn;
+  // entry pairs (position code, w, position code, w), see k_fill
+  int4* up;
+  int4* dn;
 };
 
 // Arguments of the forward and adjoint sweep kernels.
@@ -123,28 +150,20 @@ struct SweepArgs {
   // g0 + (i % n_chunks) GN (the chunks of the longest units first)
   int32_t n_chunks;
   int32_t* work_counter;  // persistent form: next work item; nullptr: item = blockIdx.x
-  const int32_t* sched;
-  // steps of the level-synchronous sweep (see k_steps): unit u's steps start at
-  // step_base[u]; step i covers schedule positions [step_k[i], step_k[i + 1]) and
-  // row entries [step_e[i], step_e[i + 1]) (upwind rows forward, downwind adjoint)
-  const int32_t* step_k;
-  const int64_t* step_e;
-  const int64_t* step_base;
-  const int32_t* n_steps;
-  const int64_t* row_ptr;  // up_ptr (forward) or dn_ptr (adjoint)
-  const int2* ent;         // up (forward) or dn (adjoint)
-  int64_t n_ent;           // entries in `ent`
+  const SliceRec* slices;     // of this launch's walk; unit u's from slice_base[u]
+  const int64_t* slice_base;  // [n_units + 1]
+  const int32_t* len;         // row lengths, schedule order (upwind forward, downwind adjoint)
+  const int4* ent;            // entry pairs of the rows (see k_fill)
   const float* tden;       // [T][G] schedule order: Aperp + kappa V
   const float* tsrc;       // [T][G] schedule order: source of the task (periodic
                            // coupling included, see PinArgs)
-  float* out;              // phi (forward) or lambda (adjoint), [D][C][G]
-  float* out_s;            // the same values in schedule order, [T][G]
+  float* out_s;            // phi (forward) or lambda (adjoint) in schedule order, [T][G]
   int64_t C_total;
   int32_t G;       // group stride
   int32_t g0;      // first group handled by this launch (see n_chunks)
   int32_t D;
   int32_t ring_mask;
-  int32_t stage_off;      // byte offset of the staging buffers in the dynamic LDS
+  int32_t* flag;   // device error bits: kErrStall
 };
 
 // Per-call preparation of the per-task denominators and sources, written in
@@ -269,20 +288,23 @@ constexpr int kTileCellsHost = 32;  // cells per tile of the cell-order build ke
 hipError_t launch_count(const DagBuildArgs& a, int32_t n_cblocks, int32_t lds_limit, hipStream_t s);
 constexpr int kMaxAligned = 4;  // most faces scheme (b) may share the outflow over
 hipError_t launch_kahn(const DagBuildArgs& a, bool lds_counters, int32_t max_cells, hipStream_t s);
-hipError_t launch_fill(const DagBuildArgs& a, int32_t n_blocks, hipStream_t s);
+hipError_t launch_fill(const DagBuildArgs& a, hipStream_t s);
 // out[0] = max faces of a cell, out[1] += overflow ints for rows of row_cap entries
 hipError_t launch_face_stats(const int64_t* face_ptr, int32_t n_cells, int32_t row_cap, int32_t n_dirs,
                              unsigned long long* out, hipStream_t s);
 hipError_t launch_face_codes(const MeshDev& m, int32_t* fcode, hipStream_t s);
 // Sorts every level of the schedule by cell id and writes the inverse schedule.
 hipError_t launch_sort_levels(const DagBuildArgs& a, hipStream_t s);
-hipError_t launch_gather_len(const DagBuildArgs& a, int32_t n_blocks, hipStream_t s);
+// Slices per unit (n_unit_slices); then, with the slices' place known, the slice
+// tables, and per task in schedule order the row lengths, Aperp and volume.
+hipError_t launch_count_slices(const DagBuildArgs& a, hipStream_t s);
+hipError_t launch_slices(const DagBuildArgs& a, hipStream_t s);
+hipError_t launch_gather_tasks(const DagBuildArgs& a, hipStream_t s);
 hipError_t launch_mark(const DagBuildArgs& a, int32_t n_big, hipStream_t s);
 size_t count_lds_bytes(int max_faces, int dn_width);
-hipError_t launch_level_entries(const DagBuildArgs& a, hipStream_t s);
 // out[2u], out[2u + 1]: upwind and downwind row entries of unit u
-hipError_t launch_unit_entries(const Unit* units, int32_t n_units, const int64_t* up_ptr,
-                               const int64_t* dn_ptr, int64_t* out, hipStream_t s);
+hipError_t launch_unit_entries(const Unit* units, int32_t n_units, const int32_t* len_up,
+                               const int32_t* len_dn, int64_t* out, hipStream_t s);
 // width[l] += tasks at level l of every unit of `mesh` (all meshes if mesh < 0), l < n_levels
 hipError_t launch_level_widths(const Unit* units, int32_t n_units, const int32_t* lp, int32_t mesh,
                                int64_t* width, int32_t n_levels, hipStream_t s);
@@ -298,6 +320,10 @@ hipError_t launch_sweep_fwd(const SweepArgs& a, int32_t gn, int32_t grid, int32_
                             size_t lds_bytes, hipStream_t s);
 hipError_t launch_sweep_adj(const SweepArgs& a, int32_t gn, int32_t grid, int32_t block,
                             size_t lds_bytes, hipStream_t s);
+// out[dir][cell][G] = out_s[task of (dir, cell)][G] of every unit (inv: cell -> schedule position)
+hipError_t launch_to_cells(const Unit* units, int32_t n_units, const int32_t* blk_base, int32_t n_blocks,
+                           const int32_t* inv, const float* out_s, float* out, int64_t C_total,
+                           int32_t G, hipStream_t s);
 hipError_t launch_reduce(const ReduceArgs& a, int32_t n_blocks, hipStream_t s);
 hipError_t launch_pin(const PinArgs& a, hipStream_t s);
 hipError_t launch_pcount(const DagBuildArgs& a, const MeshDev& m, hipStream_t s);
@@ -312,28 +338,11 @@ hipError_t launch_adj_reduce(const AdjReduceArgs& a, double* dk, double* de, hip
 hipError_t launch_d2f_pair(const double* a, const double* b, float* oa, float* ob, int64_t n,
                            hipStream_t s);
 hipError_t set_sweep_lds_limit(int32_t bytes);
-// Row entries each sweep thread stages per step (a step holds at most
-// kStageCh x threads - 8 entries in LDS).  Twice as many (fewer, larger steps,
-// which the LDS holds with two packed groups) measured slower on the clustered
-// 2M-cell mesh: each step then keeps more loads in flight than the memory
-// system returns in time.
-constexpr int kStageCh = 4;
 // Largest sweep workgroup for gn packed groups: one group fits 1024 threads'
 // registers (128 VGPRs each), more groups need the 256 VGPRs of 512 threads.
 constexpr int kSweepMaxBlock(int gn) { return gn == 1 ? 1024 : 512; }
-// Dynamic LDS layout of a sweep workgroup of `block` threads: values (ring
-// slots, a zero slot, a sink, 2 x kStageCh x block prefetched slots) x gn FP32,
-// then two staging buffers of kStageCh x block + 8 entries.
-struct LdsLayout {
-  int32_t stage_off;
-  size_t bytes;
-};
-LdsLayout sweep_lds_layout(int32_t gn, int32_t ring, int32_t block);
-// Steps of the level-synchronous sweep with at most cap_t tasks and about
-// cap_e row entries each (see k_steps), written from step_base[u] per unit.
-hipError_t launch_steps(const Unit* units, int32_t n_units, const int32_t* lp, const int64_t* lev_up,
-                        const int64_t* lev_dn, const int64_t* up_ptr, const int64_t* dn_ptr,
-                        const int64_t* step_base, int32_t cap_t, int32_t cap_e, int32_t* step_k,
-                        int64_t* step_eu, int64_t* step_ed, int32_t* n_steps, hipStream_t s);
+// Dynamic LDS bytes of a sweep workgroup: the ring of `ring` results x gn FP32, a
+// slot of zeros and a sink, then the counters.
+constexpr size_t sweep_lds_bytes(int32_t gn, int32_t ring) { return (size_t)gn * (ring + 2) * sizeof(float) + 16; }
 
 }  // namespace sweep

@@ -1,19 +1,21 @@
 // Forward and adjoint sweep kernels and the per-cell reductions (gfx950).
 //
-// Schedule: one workgroup owns one (mesh, direction) sweep at a time and walks
-// its levels in order (reverse order for the adjoint), one barrier per level.
-// The tasks of a level are independent (their upwind tasks sit on earlier
-// levels), so the workgroup's threads solve them in parallel; every task pulls
-// its inflow from its upwind tasks' results in a fixed row order, so results do
-// not depend on which thread runs which task.  Persistent form: a grid sized to
-// the resident capacity takes (mesh, direction) units from an atomic counter,
-// longest first.
+// Schedule: one workgroup owns one (mesh, direction) sweep at a time and works
+// through its levels in order (reverse order for the adjoint).  The tasks of a
+// level are independent (their upwind tasks sit on earlier levels), so the
+// workgroup's wavefronts solve them in parallel, ordered by counters in LDS instead
+// of barriers; every task pulls its inflow from its upwind tasks' results in a fixed
+// row order, so results do not depend on which lane runs which task.  Persistent
+// form: a grid sized to the resident capacity takes (mesh, direction) units from an
+// atomic counter, longest first.
 //
-// LDS ring: the results of the last `ring` tasks of the schedule are kept in
-// LDS, indexed by schedule position modulo `ring`, so most upwind reads are LDS
-// reads; an older upwind result is prefetched from global memory a step ahead
-// (it was stored at least two barriers earlier by the same workgroup).
+// LDS ring: the results of the last `ring` tasks of the schedule are kept in LDS,
+// indexed by schedule position modulo `ring`, so most upwind reads are LDS reads; an
+// older upwind result is loaded from global memory before the task's turn.
 #include <float.h>
+#include <limits.h>
+
+#include <type_traits>
 
 #include "internal.h"
 #include "sweep.h"
@@ -108,535 +110,539 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// The unit's buffers (uniform over the workgroup).
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// A uniform pointer to global memory in scalar registers (its loads take a 32-bit
+// offset per lane).
+template <class T>
+using global_ptr = const T __attribute__((address_space(1)))*;
+
+template <class T>
+__device__ __forceinline__ global_ptr<T> uniform_ptr(const T* p) {
+  return (global_ptr<T>)(uint64_t)uniform64((int64_t)(uint64_t)p);
+}
+
+// Lanes of `m` below this one.
+__device__ __forceinline__ int rank_in(uint64_t m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+constexpr int kPairs = 8;  // entry pairs of a row held in registers (16 entries)
+
+// The unit's arrays (uniform over the workgroup).
 struct UnitBufs {
-  __amdgpu_buffer_rsrc_t ent;    // row entries of the unit (from its first entry)
-  __amdgpu_buffer_rsrc_t sched;  // schedule of the unit
-  __amdgpu_buffer_rsrc_t rp;     // row pointers of the unit (int64)
-  __amdgpu_buffer_rsrc_t den;    // [slot][G] at group g0 of the unit's first task
-  __amdgpu_buffer_rsrc_t src;
+  global_ptr<int32_t> len;       // row lengths of the unit, schedule order
+  global_ptr<float> den;         // [slot][G] at group g0 of the unit's first task
+  global_ptr<float> src;
   __amdgpu_buffer_rsrc_t outs;   // out_s at group g0 of the unit's first task: [slot][G]
-  __amdgpu_buffer_rsrc_t out;    // out of this direction at group g0: [cell][G]
-  int64_t ue0;                   // first row entry of the unit
+  int C;                         // tasks of the unit
+  int ns;                        // slices of the unit
 };
 
-// Record of one task: cell, row [r0, r1) relative to its step's first entry,
-// denominator and source per group.
+// GN consecutive values at 32-bit word offset `off` of a uniform pointer.
 template <int GN>
-struct TaskRec {
-  int c;
-  int r0, r1;
-  float den[GN];
-  float src[GN];
-};
-
-// Per-step values, uniform over the workgroup.
-struct LevelInfo {
-  int k0, k1;     // the step's task range (schedule positions)
-  int ne;         // row entries of the step
-  int nst;        // entries of the step held in LDS staging
-  int64_t e0;     // first row entry of the step
-};
-
-// Entries of a staged row hold the LDS byte address of their value instead of a
-// schedule position (the ring slot of a result inside the window, or the slot
-// the older value was prefetched into) and their factor.  An entry whose value
-// is not in LDS names the zero slot and marks its step for the global-memory
-// path.
-
-// Loads in flight for one step: the thread's share of the step's row block
-// (raw entries, two per load) and the record of the thread's task of the step,
-// with the step's bounds.  Lanes past the step read past the buffers' ends (no
-// memory traffic, value 0).
-template <int GN, int CH>
-struct Pref {
-  LevelInfo L;
-  int4 st[CH / 2];
-  int c;
-  // low words of the row pointers of the task and the next one (two loads: a
-  // register a load writes and nothing reads would be reused while the load is
-  // in flight, and the wait for it would stall the next solve)
-  int rp0, rp1;
-  float den[GN];
-  float src[GN];
-};
-
-template <int GN>
-__device__ __forceinline__ void load_rec(const SweepArgs& a, const UnitBufs& B, int k, int64_t e0,
-                                         TaskRec<GN>& t) {
-  t.c = ld_b32(B.sched, 4u * (uint32_t)k, 0);
-  t.r0 = (int)((uint32_t)ld_b32(B.rp, 8u * (uint32_t)k, 0) - (uint32_t)e0);
-  t.r1 = (int)((uint32_t)ld_b32(B.rp, 8u * (uint32_t)(k + 1), 0) - (uint32_t)e0);
-  ld_gn<GN>(B.den, 4u * (uint32_t)(k * a.G), 0, t.den);
-  ld_gn<GN>(B.src, 4u * (uint32_t)(k * a.G), 0, t.src);
-}
-
-// Every thread issues the same loads at every step (fixed count, so the waits
-// for the loads in flight stay exact); the offsets of lanes past the step are
-// moved past the buffers' ends.  Entry pair i of thread t is entries
-// 2 (t + i nthr) and 2 (t + i nthr) + 1 of the step's block.
-template <int GN, int CH>
-__device__ __forceinline__ void issue_pref(const SweepArgs& a, const UnitBufs& B, int tid, int nthr,
-                                           Pref<GN, CH>& P) {
-  const LevelInfo& L = P.L;
-  const uint32_t eoff = 8u * (uint32_t)(L.e0 - B.ue0);
+__device__ __forceinline__ void ld_stream(global_ptr<float> p, uint32_t off, float* v) {
 #pragma unroll
-  for (int i = 0; i < CH / 2; ++i) {
-    const int idx = 2 * (tid + i * nthr);
-    P.st[i] = ld_b128<kStream>(B.ent, idx < L.nst ? 8u * (uint32_t)idx : kOob, eoff);
-  }
-  const bool act = L.k0 + tid < L.k1;
-  const uint32_t k0 = (uint32_t)L.k0;
-  P.c = ld_b32<kStream>(B.sched, act ? 4u * (uint32_t)tid : kOob, 4u * k0);
-  P.rp0 = ld_b32<kStream>(B.rp, act ? 8u * (uint32_t)tid : kOob, 8u * k0);
-  P.rp1 = ld_b32<kStream>(B.rp, act ? 8u * (uint32_t)tid + 8u : kOob, 8u * k0);
-  const uint32_t vo = act ? 4u * (uint32_t)(tid * a.G) : kOob, so = 4u * k0 * (uint32_t)a.G;
-  ld_gn<GN, kStream>(B.den, vo, so, P.den);
-  ld_gn<GN, kStream>(B.src, vo, so, P.src);
+  for (int g = 0; g < GN; ++g) v[g] = __builtin_nontemporal_load(p + off + g);
 }
 
-// Inflow of one task per group.
+// One slice: its uniform part and one task per lane.
 template <int GN>
-struct Inflow {
-  float acc[GN];
+struct Slice {
+  int k0, cnt, dep, lim, ks;  // uniform: SliceRec
+  int64_t base;               // uniform: first entry pair
+  int np;                     // uniform: entry pairs
+  int n4, n6, nt;             // uniform: pairs in columns 4 and 6; pairs past the columns in registers
+  int len;                    // per lane: row length
+  float den[GN], src[GN];
 };
 
-// Schedule positions whose results are in the LDS ring while a step is solved,
-// [lo, lo + n) with lo >= 0: forward, the last R positions up to the step's end;
-// adjoint (steps in reverse order), the R positions from the step's start.
-// The step's own writes never evict an upwind result inside the window.
-struct Window {
-  int lo;
-  uint32_t n;
-  __device__ __forceinline__ bool has(int p) const { return (uint32_t)(p - lo) < n; }
+// Row entries of a slice in registers: kPairs pairs of this lane's row, and one
+// pair of the slice's entries past those columns.  Loaded as (position code,
+// factor) twice; resolving turns the codes into LDS byte offsets.
+struct Entries {
+  int4 e[kPairs];
+  int4 t;
 };
 
-template <bool REVERSE>
-__device__ __forceinline__ Window window(int k0, int k1, int R) {
-  Window w;
-  if (REVERSE) {
-    w.lo = k0;
-    w.n = (uint32_t)R;
+// LDS byte offset of the ring slot of position code x (see k_fill).
+template <int GN>
+__device__ __forceinline__ int slot_of(int x, int mask4) { return (x & mask4) * GN; }
+
+// The sweep's LDS is dynamic only, so it starts at LDS address 0 and slot offsets
+// are addresses: GN consecutive floats read or written there in one access.
+template <int GN>
+struct LdsVec {
+  using type = float __attribute__((ext_vector_type(GN)));
+};
+template <class T>
+__device__ __forceinline__ T __attribute__((address_space(3)))* lds_at(int addr) {
+  return (T __attribute__((address_space(3)))*)(uint32_t)addr;
+}
+
+template <int GN>
+__device__ __forceinline__ void lds_read(int addr, float* v) {
+  if constexpr (GN == 1) {
+    v[0] = *lds_at<float>(addr);
+  } else if constexpr (GN == 3) {
+#pragma unroll
+    for (int g = 0; g < 3; ++g) v[g] = *lds_at<float>(addr + 4 * g);
   } else {
-    w.lo = k1 - R > 0 ? k1 - R : 0;
-    w.n = (uint32_t)(k1 - w.lo);
-  }
-  return w;
-}
-
-template <int GN>
-__device__ __forceinline__ void finish_task(const SweepArgs& a, const UnitBufs& B,
-                                            const TaskRec<GN>& t, int k, const Inflow<GN>& in,
-                                            float* ring) {
-  float* rr = ring + (k & a.ring_mask) * GN;
-  const uint32_t oc = 4u * (uint32_t)(t.c * a.G), ok = 4u * (uint32_t)(k * a.G);
-  float v[GN];
+    const typename LdsVec<GN>::type x = *lds_at<typename LdsVec<GN>::type>(addr);
 #pragma unroll
-  for (int g = 0; g < GN; ++g) {
-    v[g] = __fdiv_rn(__fadd_rn(in.acc[g], t.src[g]), t.den[g]);
-    rr[g] = v[g];
+    for (int g = 0; g < GN; ++g) v[g] = x[g];
   }
-  st_gn<GN, kStream>(v, B.out, oc);
-  st_gn<GN>(v, B.outs, ok);
 }
 
-// The common step: at most one task per thread and every inflow in LDS.  Every
-// memory operation is issued unconditionally (a thread without a task writes
-// the sink slot and stores past the buffers' ends, which are dropped), so each
-// step issues a fixed number of vector-memory operations.
 template <int GN>
-__device__ __forceinline__ void finish_fast(const SweepArgs& a, const UnitBufs& B,
-                                            const TaskRec<GN>& t, int k, const Inflow<GN>& in,
-                                            float* ring, float* sink) {
-  const bool act = t.c >= 0;
-  float* rr = act ? ring + (k & a.ring_mask) * GN : sink;
-  const uint32_t oc = act ? 4u * (uint32_t)(t.c * a.G) : kOob;
-  const uint32_t ok = act ? 4u * (uint32_t)(k * a.G) : kOob;
-  float v[GN];
+__device__ __forceinline__ void lds_write(int addr, const float* v) {
+  if constexpr (GN == 1 || GN == 3) {
 #pragma unroll
-  for (int g = 0; g < GN; ++g) {
-    v[g] = __fdiv_rn(__fadd_rn(in.acc[g], t.src[g]), t.den[g]);
-    rr[g] = v[g];
-  }
-  st_gn<GN, kStream>(v, B.out, oc);
-  st_gn<GN>(v, B.outs, ok);
-}
-
-// GN consecutive groups of one task from a [slot][G] array (one load; offsets
-// past the buffer's end read zeros without memory traffic).
-template <int GN>
-__device__ __forceinline__ void ld_groups(__amdgpu_buffer_rsrc_t r, uint32_t off, float* v) {
-  if constexpr (GN == 4) {
-    const int4 x = ld_b128(r, off, 0);
-    v[0] = __int_as_float(x.x);
-    v[1] = __int_as_float(x.y);
-    v[2] = __int_as_float(x.z);
-    v[3] = __int_as_float(x.w);
-  } else if constexpr (GN == 2) {
-    const int2 x = ld_b64(r, off, 0);
-    v[0] = __int_as_float(x.x);
-    v[1] = __int_as_float(x.y);
+    for (int g = 0; g < GN; ++g) *lds_at<float>(addr + 4 * g) = v[g];
   } else {
+    typename LdsVec<GN>::type x;
 #pragma unroll
-    for (int g = 0; g < GN; ++g) v[g] = ld_f32(r, off + 4u * g, 0);
+    for (int g = 0; g < GN; ++g) x[g] = v[g];
+    *lds_at<typename LdsVec<GN>::type>(addr) = x;
   }
 }
 
-// Inflow of one task in row order, in batches of 8 entries (the row's entries
-// from the LDS staging buffer, or from global memory for levels that were not
-// staged).  An entry inside the window reads its ring slot; an older result is
-// loaded from out_s (stored at least one barrier earlier by this workgroup).
-// Every load of a batch is issued before the first is used, so a batch
-// costs one memory round trip whatever its mix.  The sum is the same sequence
-// of fused multiply-adds in row order on every path; entries past the row's end
-// (the rest of the batch) are skipped.
-template <int GN, bool STAGED>
-__device__ __forceinline__ Inflow<GN> gather(const SweepArgs& a, const UnitBufs& B,
-                                             const TaskRec<GN>& t, const int2* stg, uint32_t eoff,
-                                             const float* ring, Window w) {
-  Inflow<GN> in;
-#pragma unroll
-  for (int g = 0; g < GN; ++g) in.acc[g] = 0.0f;
-  for (int rb = t.r0; rb < t.r1; rb += 8) {
-    int2 en[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-      en[q] = STAGED ? stg[rb + q] : ld_b64(B.ent, 8u * (uint32_t)(rb + q), eoff);
-    const int nr = t.r1 - rb;  // entries of the row in this batch
-    float gv[8][GN], rv[8][GN];
-    bool inw[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int p = en[q].x;
-      const bool val = q < nr;
-      inw[q] = w.has(p);
-      const bool glob = val && !inw[q];
-      ld_groups<GN>(B.outs, glob ? 4u * (uint32_t)(p * a.G) : kOob, gv[q]);
-      const float* v = ring + (p & a.ring_mask) * GN;
-#pragma unroll
-      for (int g = 0; g < GN; ++g) rv[q][g] = v[g];
-    }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const bool val = q < nr;
-      const float y = __int_as_float(en[q].y);
-#pragma unroll
-      for (int g = 0; g < GN; ++g) {
-        const float x = inw[q] ? rv[q][g] : gv[q][g];
-        in.acc[g] = val ? __builtin_fmaf(y, x, in.acc[g]) : in.acc[g];
-      }
-    }
-  }
-  return in;
-}
+using lds_int = int __attribute__((address_space(3)));
 
-// Inflow of one task from its staged row, every value from LDS (`lds`: the base
-// the entries' addresses are relative to), in batches of 8 with the same
-// sequence of fused multiply-adds in row order as gather().  The entries of a
-// batch past the row's end (the next row's, or padding naming the zero slot)
-// take factor 0; adding +-0 x (x finite) leaves a sum that starts at +0 and only
-// grows unchanged, so the result is gather()'s bit for bit.
-template <int GN>
-__device__ __forceinline__ Inflow<GN> gather_lds(const TaskRec<GN>& t, const int2* stg,
-                                                 const unsigned char* lds) {
-  Inflow<GN> in;
-#pragma unroll
-  for (int g = 0; g < GN; ++g) in.acc[g] = 0.0f;
-  for (int rb = t.r0; rb < t.r1; rb += 8) {
-    int2 en[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) en[q] = stg[rb + q];
-    const int nr = t.r1 - rb;
-    float rv[8][GN], y[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      y[q] = q < nr ? __int_as_float(en[q].y) : 0.0f;
-      // value slots are GN floats at a multiple of GN floats: one LDS read
-      const unsigned char* v = lds + en[q].x;
-      if constexpr (GN == 4) {
-        const float4 x = *reinterpret_cast<const float4*>(v);
-        rv[q][0] = x.x;
-        rv[q][1] = x.y;
-        rv[q][2] = x.z;
-        rv[q][3] = x.w;
-      } else if constexpr (GN == 2) {
-        const float2 x = *reinterpret_cast<const float2*>(v);
-        rv[q][0] = x.x;
-        rv[q][1] = x.y;
-      } else {
-#pragma unroll
-        for (int g = 0; g < GN; ++g) rv[q][g] = reinterpret_cast<const float*>(v)[g];
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-#pragma unroll
-      for (int g = 0; g < GN; ++g) in.acc[g] = __builtin_fmaf(y[q], rv[q][g], in.acc[g]);
-    }
-  }
-  return in;
-}
-
-// One workgroup per (mesh, direction) unit at a time, steps in order (reverse
-// for the adjoint), one barrier per step.  A step is a run of consecutive
-// schedule positions inside one level (levels wider than the workgroup or
-// with more entries than the staging buffer are cut into several), so its
-// tasks are independent.  Each step's row block and each thread's task record
-// are loaded NS - 1 steps ahead into registers (NS rotating sets).  Two steps
-// ahead, the holder of each staged entry whose upwind result lies outside the
-// LDS ring window loads that value from global memory; the step before it is solved the holder copies the value into the
-// entry's own slot of the LDS value area and rewrites the entry to name its
-// slot (ring slot or prefetched slot).  The solve then reads only LDS, and no
-// load is waited for on the critical path of a common step.
-// A value is prefetched only when it is final: at the prefetch (after the
-// thread's solve of step t, for step t + 2) every step before t is complete,
-// which covers every result outside the window when the ring holds at least
-// three steps (R >= 3 x threads, as the host sizes it).
-//
-// LDS: [values: ring R slots | zero | sink | 2 x SE prefetched slots] x GN floats,
-// then two staging buffers of SE + 8 entries.
-// The rows hold graph edges only: the other pass's values through the periodic
-// faces are folded into the sources before the launch.
-template <int GN, bool REVERSE, int CH>
-__global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
-  constexpr int NS = 3;
-  extern __shared__ __align__(16) unsigned char smem[];
-  float* vals = reinterpret_cast<float*>(smem);
-  int2* stage = reinterpret_cast<int2*>(smem + a.stage_off);
-  __shared__ int s_unit;
-  // s_bad[b]: the running number of the last step staged in buffer b with an
-  // entry whose value is not in LDS (such a step is solved from global memory)
-  __shared__ int s_bad[2];
-  const int tid = threadIdx.x;
-  const int nthr = blockDim.x;
-  const int SE = CH * nthr;
-  const int SP = SE + 8;  // staging buffer stride
-  const int SMAX = SE - 8;  // entries staged per step; 8 padding entries follow them
-  const int R = a.ring_mask + 1;
-  const int zero = R;       // value slot that always holds zeros (padding entries)
-  const int sink = R + 1;   // value slot the threads without a task write
-  const int far0 = R + 2;   // prefetched slots of staging buffer b: far0 + b SE + entry index
-  const int wbase = __builtin_amdgcn_readfirstlane(tid & ~63);  // the wavefront's first thread
-  float* ring = vals;
-  float* sinkp = vals + sink * GN;
-  for (int i = tid; i < 2 * SP; i += nthr) stage[i] = make_int2(zero * GN * 4, 0);
-  for (int i = tid; i < (R + 2 + 2 * SE) * GN; i += nthr) vals[i] = 0.0f;
-  if (tid < 2) s_bad[tid] = -1;
-  int gbase = 0;  // running number of this workgroup's step 0 of the current unit
+// Waits until the workgroup's counter has reached `need` (it is only ever
+// raised by wavefronts that never wait for this one, see k_sweep; a counter that
+// stands still for millions of reads raises the error flag instead of hanging).
+__device__ __forceinline__ void wait_count(lds_int* counter, int need, int& seen, int32_t* flag) {
+  if (seen >= need) return;
   for (int it = 0;; ++it) {
-    int ui;
-    if (a.work_counter != nullptr) {
-      if (tid == 0) s_unit = atomicAdd(a.work_counter, 1);
-      __syncthreads();
-      ui = __builtin_amdgcn_readfirstlane(s_unit);  // uniform: the unit's buffers stay scalar
-      __syncthreads();
-    } else {
-      ui = it == 0 ? (int)blockIdx.x : a.n_units * a.n_chunks;
+    seen = uni(__hip_atomic_load(counter, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
+    if (seen >= need) return;
+    if (it >= kSpinLimit) {
+      atomicOr(flag, kErrStall);
+      seen = INT_MAX;
+      return;
     }
+  }
+}
+
+// One workgroup sweeps one (mesh, direction, group chunk) work item at a time.
+// The tasks of every level are cut into slices of at most 64 (k_slices), one
+// task per lane, and slice i belongs to wavefront i mod (wavefronts).  A slice
+// may run once every slice of the earlier levels has finished: each finishing
+// slice adds one to an LDS counter, and a wavefront waits until the counter has
+// reached the number of slices before its level (SliceRec.dep; slices of the
+// level itself or later ones cannot be among those counted, as they wait for
+// the same number).  There is no barrier: a wavefront has everything of its next
+// slice but the recent upwind results in registers before its turn comes, and
+// between two turns of a wavefront the others' levels pass.  The wavefront with
+// the lowest unfinished slice never waits for anything unfinished, so every wait
+// ends.
+//
+// Per slice and lane: the row's entries (position code, factor), loaded a turn
+// ahead from a layout in which pair j of the rows that have one is contiguous
+// over the lanes (k_fill), so each load is coalesced; upwind results older than
+// the LDS ring's window, loaded a turn ahead into registers; then, in turn, one
+// LDS read per entry, the fused multiply-adds in row order, the division, the
+// ring slot and the count.  The store to out_s (schedule order, coalesced) follows
+// the count; k_to_cells brings the results into cell order afterwards (a store in
+// cell order here would touch a line per lane, more than all the loads together).
+//
+// LDS ring: the results of the last R positions of the schedule.  Position p is
+// read from the ring by a slice of a level that ends at `lim` only if p >= lim - R:
+// while a slice runs, no later level writes, so the slot has not been reused (and
+// of a level wider than the ring, whose slices run in any order, only the last R
+// positions write at all).
+// An older result is read from out_s.  It is visible there to a slice's early
+// loads if it lies before the level of the wavefront's previous slice by more than
+// the positions whose slices may have been counted but not yet stored (one slice
+// per wavefront: 64 x wavefronts).  A slice with an older result that is neither
+// (very wide levels, tiny rings), or with more row entries than the registers
+// hold, is summed after its wait straight from memory, once a second counter
+// shows the stores of the earlier levels; same terms in the same order, so every
+// path gives the same bits.
+//
+// The adjoint walks the slices backwards; its rows name reversed positions, so
+// the same code serves both.
+//
+// What bounds it: narrow levels, the chain from one level's count to the next
+// (about 0.42 us: LDS reads, multiply-adds, division, ring write, count, poll);
+// wide ones, the line requests of one compute unit's L1 (a unit runs on one) and
+// its instruction issue.  Against steps of a level with one barrier each, whose
+// wavefronts loaded, staged through LDS and solved by turns (forward sweep per
+// launch): 64^3 cells x 84 directions 2.27 -> 0.72 ms; 4,096 cells x 8 directions
+// 0.288 -> 0.100 ms; 2M clustered cells x 84 directions x 4 groups 27.0 -> 12.6 ms
+// (+ 1.5 ms for k_to_cells; with the results stored in cell order from here, 26.4).
+template <int GN, bool REVERSE>
+__global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = uni(tid >> 6);
+  const int nw = blockDim.x >> 6;
+  const int R = a.ring_mask + 1;
+  const int mask4 = a.ring_mask * 4;
+  const int lag = 64 * nw;
+  const uint32_t lane4G = 4u * (uint32_t)(lane * a.G);
+  const int zero = R * GN * 4;  // the zero slot's address
+  if (tid < GN) *lds_at<float>(zero + 4 * tid) = 0.0f;
+  // behind the ring, the zero slot and the sink: the counts of finished and of stored
+  // slices, the next work item
+  lds_int* s_done = lds_at<int>(zero + 2 * GN * 4);
+  lds_int* s_unit = s_done + 2;
+  for (int it = 0;; ++it) {
+    __syncthreads();  // the previous item's counters and ring are no longer read
+    if (tid == 0) {
+      s_done[0] = 0;
+      s_done[1] = 0;
+      if (a.work_counter != nullptr) *s_unit = atomicAdd(a.work_counter, 1);
+    }
+    __syncthreads();
+    const int ui = a.work_counter != nullptr ? uni(*s_unit) : (it == 0 ? (int)blockIdx.x : INT_MAX);
     if (ui >= a.n_units * a.n_chunks) break;
     const int u = a.unit_order[ui / a.n_chunks];
     const int g0 = a.g0 + (ui % a.n_chunks) * GN;
     const Unit U = a.units[u];
     const int64_t tb = U.task_base;
-    const int ns = a.n_steps[u];
-    if (ns <= 0) continue;
-    // step tables are read through the scalar cache (constant address space:
-    // the sweep never writes them), so reading them never waits for the vector
-    // loads in flight
-    using cint = const __attribute__((address_space(4))) int32_t;
-    using clong = const __attribute__((address_space(4))) int64_t;
-    cint* SK = (cint*)(a.step_k + a.step_base[u]);
-    clong* SEn = (clong*)(a.step_e + a.step_base[u]);
-    const int64_t obase = ((int64_t)U.dir * a.C_total + U.cell_off) * a.G + g0;
-    const int C = U.n_cells;
     UnitBufs B;
-    {
-      const int64_t ea = SEn[0], eb = SEn[ns];
-      B.ue0 = ea < eb ? ea : eb;
-      const int64_t ue1 = ea < eb ? eb : ea;
-      B.ent = rsrc(a.ent + B.ue0, 8 * (ue1 - B.ue0));
-    }
-    B.sched = rsrc(a.sched + tb, 4 * (int64_t)C);
-    B.rp = rsrc(a.row_ptr + tb, 8 * ((int64_t)C + 1));
-    B.den = rsrc(a.tden + tb * a.G + g0, 4 * ((int64_t)C * a.G - g0));
-    B.src = rsrc(a.tsrc + tb * a.G + g0, 4 * ((int64_t)C * a.G - g0));
-    B.outs = rsrc(a.out_s + tb * a.G + g0, 4 * ((int64_t)C * a.G - g0));
-    B.out = rsrc(a.out + obase, 4 * ((int64_t)C * a.G - g0));
-    // step solved at iteration s (iterations past the last one repeat it: their
-    // loads are issued and never used)
-    auto info = [&](int s) -> LevelInfo {
-      s = s < ns - 1 ? s : ns - 1;
-      const int st = REVERSE ? ns - 1 - s : s;
-      LevelInfo L;
-      // the values are uniform: keep them in scalar registers
-      L.k0 = __builtin_amdgcn_readfirstlane(SK[st]);
-      L.k1 = __builtin_amdgcn_readfirstlane(SK[st + 1]);
-      L.e0 = uniform64(SEn[st]);
-      L.ne = (int)(uniform64(SEn[st + 1]) - L.e0);
-      L.nst = L.ne < SMAX ? L.ne : SMAX;
-      return L;
+    B.C = uni(U.n_cells);
+    const int64_t s0 = a.slice_base[u];
+    B.ns = uni((int)(a.slice_base[u + 1] - s0));
+    if (B.ns <= 0) continue;
+    const int64_t C = B.C;
+    B.len = uniform_ptr(a.len + tb);
+    B.den = uniform_ptr(a.tden + tb * a.G + g0);
+    B.src = uniform_ptr(a.tsrc + tb * a.G + g0);
+    B.outs = rsrc(a.out_s + tb * a.G + g0, 4 * (C * a.G - g0));
+
+    // a slice record, one word per lane (lanes 0 to 7); past the unit's last slice
+    // it is empty
+    const global_ptr<int32_t> recs = uniform_ptr(reinterpret_cast<const int32_t*>(a.slices + s0));
+    auto load_info = [&](int i) -> int {
+      const int at = min(i, B.ns - 1);
+      return recs[8u * (uint32_t)(REVERSE ? B.ns - 1 - at : at) + (uint32_t)(lane & 7)];
     };
-    Pref<GN, CH> P[NS];
-    float F[CH][GN];  // prefetched values of the thread's staged entries
-    TaskRec<GN> cur;
-    LevelInfo curL;
-    // results final at the last prefetch: forward, positions below vis; adjoint,
-    // positions from vis up
-    int vis = REVERSE ? 0x7fffffff : 0, visF = vis;
-    auto prefetchable = [&](int p, const Window& w, int v) -> bool {
-      return !w.has(p) && (REVERSE ? p >= v : p < v);
+    auto take_info = [&](int i, int info, Slice<GN>& S) {
+      const bool in = i < B.ns;
+      S.k0 = __builtin_amdgcn_readlane(info, 0);
+      S.cnt = in ? __builtin_amdgcn_readlane(info, 1) : 0;
+      S.dep = in ? __builtin_amdgcn_readlane(info, 2) : 0;
+      S.lim = __builtin_amdgcn_readlane(info, 3);
+      S.ks = __builtin_amdgcn_readlane(info, 4);
+      S.base = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(info, 6) << 32) |
+                         (uint32_t)__builtin_amdgcn_readlane(info, 5));
+      S.np = in ? __builtin_amdgcn_readlane(info, 7) : 0;
     };
-    auto issue = [&](int s, Pref<GN, CH>& Q) {
-      Q.L = info(s);
-      issue_pref<GN, CH>(a, B, tid, nthr, Q);
+    // (lanes without a task read the slice's first one)
+    auto load_tasks = [&](Slice<GN>& S) {
+      const uint32_t k = (uint32_t)(S.k0 + (lane < S.cnt ? lane : 0));
+      S.len = __builtin_nontemporal_load(B.len + k);
+      ld_stream<GN>(B.den, k * (uint32_t)a.G, S.den);
+      ld_stream<GN>(B.src, k * (uint32_t)a.G, S.src);
     };
-    // the older results of the thread's staged entries of step s (one load per
-    // entry; the others read past the buffer's end)
-    auto farload = [&](const Pref<GN, CH>& Q) {
-      const LevelInfo& L = Q.L;
-      const Window w = window<REVERSE>(L.k0, L.k1, R);
-      uint32_t po = 0;  // per entry: an older result to load
+    // Pair j of the rows that have one is stored for those lanes in lane order.
+    auto load_entries = [&](Slice<GN>& S, Entries& E) {
+      const __amdgpu_buffer_rsrc_t ent = rsrc(a.ent + S.base, 16 * (int64_t)S.np);
+      const int len = S.len = lane < S.cnt ? S.len : 0;
+      int off = 0;
 #pragma unroll
-      for (int i = 0; i < CH / 2; ++i) {
-        if (2 * (wbase + i * nthr) >= L.nst) continue;  // no entry of this wavefront
+      for (int j = 0; j < kPairs; ++j) {
+        const bool has = len > 2 * j;
+        const uint64_t m = __ballot(has);
+        uint32_t at = 16u * (uint32_t)rank_in(m);
+        asm volatile("" : "+v"(at));  // (a select, not a branch around its computation)
+        E.e[j] = ld_b128<kStream>(ent, has ? at : kOob, 16u * (uint32_t)off);
+        const int n = __popcll(m);
+        off += n;
+        if (j == 4) S.n4 = n;
+        if (j == 6) S.n6 = n;
+      }
+      S.nt = S.np - off;
+      E.t = ld_b128<kStream>(ent, lane < S.nt ? 16u * (uint32_t)lane : kOob, 16u * (uint32_t)off);
+    };
+
+    Slice<GN> S0, S1, S2;
+    int info;                  // record of the slice after S2
+    Entries EA, EB;
+    float f[2 * kPairs][GN], ft[2][GN];  // results from outside the window (else 0), of the slice resolved last
+    bool any = false, bad = false;       // some entry outside the window; one of them not visible yet
+    int seen = 0, seen_st = 0;           // the counters as last read
+    int vis = 0;                         // results before this position are in out_s
+
+    // Window test, early loads of the older results and LDS offsets of a slice
+    // (entries outside the window, and lanes without an entry, name the zero slot).
+    auto resolve = [&](const Slice<GN>& S, Entries& E, auto&& between) {
+      // codes below lo4 lie outside the window; real ones (not 0) are tested after
+      // subtracting 4, which sends 0 to the top
+      const uint32_t lo4 = 4u * (uint32_t)(max(S.lim - R, 0) + 1);
+      const uint32_t vis4 = 4u * (uint32_t)max(vis, 0);
+      uint32_t low = 0xffffffffu;  // the smallest real code
+#pragma unroll
+      for (int j = 0; j < kPairs; ++j) {
+        low = min(low, (uint32_t)E.e[j].x - 4u);
+        low = min(low, (uint32_t)E.e[j].z - 4u);
+      }
+      low = min(low, (uint32_t)E.t.x - 4u);
+      low = min(low, (uint32_t)E.t.z - 4u);
+      any = __ballot(low < lo4 - 4u) != 0ull;
+      bad = S.nt > 64;
+      between();
+      if (any) {
+        bool b = false;
+        // the early load of one entry: out of range (0) for lanes without one
+        auto old = [&](int x, float* v) {
+          const uint32_t y = (uint32_t)x - 4u;
+          const bool need = y < lo4 - 4u;
+          const uint32_t d = REVERSE ? 4u * (uint32_t)B.C - (uint32_t)x : y;
+          b |= need && y >= vis4;
+          ld_gn<GN>(B.outs, need ? d * (uint32_t)a.G : kOob, 0, v);
+        };
+#pragma unroll
+        for (int j = 0; j < kPairs; ++j) {
+          old(E.e[j].x, f[2 * j]);
+          old(E.e[j].z, f[2 * j + 1]);
+        }
+        old(E.t.x, ft[0]);
+        old(E.t.z, ft[1]);
+        bad |= __ballot(b) != 0ull;
+      }
+      auto slot = [&](int x) { return (uint32_t)x < lo4 ? zero : slot_of<GN>(x, mask4); };
+#pragma unroll
+      for (int j = 0; j < kPairs; ++j) {
+        E.e[j].x = slot(E.e[j].x);
+        E.e[j].z = slot(E.e[j].z);
+      }
+      E.t.x = slot(E.t.x);
+      E.t.z = slot(E.t.z);
+    };
+
+    // Inflow of a resolved slice: the terms of each row in order.  A value is the
+    // ring's or, OLD, the early-loaded one; the other of the two is +0, so their
+    // bits are joined.
+    auto gather = [&](const Slice<GN>& S, const Entries& E, auto old_c, float* acc) {
+      constexpr bool OLD = decltype(old_c)::value;
+      auto join = [&](float x, float y) {
+        return OLD ? __int_as_float(__float_as_int(x) | __float_as_int(y)) : x;
+      };
+      auto part = [&](auto j0_c, auto j1_c) {
+        constexpr int J0 = decltype(j0_c)::value, J1 = decltype(j1_c)::value;
+        float v[2 * (J1 - J0)][GN];
+#pragma unroll
+        for (int j = J0; j < J1; ++j) {
+          lds_read<GN>(E.e[j].x, v[2 * (j - J0)]);
+          lds_read<GN>(E.e[j].z, v[2 * (j - J0) + 1]);
+        }
+#pragma unroll
+        for (int q = 2 * J0; q < 2 * J1; ++q) {
+          const float w = __int_as_float(q & 1 ? E.e[q / 2].w : E.e[q / 2].y);
+#pragma unroll
+          for (int g = 0; g < GN; ++g) acc[g] = __builtin_fmaf(w, join(v[q - 2 * J0][g], f[q][g]), acc[g]);
+        }
+      };
+      part(std::integral_constant<int, 0>{}, std::integral_constant<int, 4>{});
+      if (S.n4 > 0) part(std::integral_constant<int, 4>{}, std::integral_constant<int, 6>{});
+      if (S.n6 > 0) part(std::integral_constant<int, 6>{}, std::integral_constant<int, 8>{});
+      if (S.nt > 0) {
+        // pairs past the registers: lane i holds pair i of them; each column's rows
+        // take theirs in turn
+        float x0[GN], x1[GN];
+        lds_read<GN>(E.t.x, x0);
+        lds_read<GN>(E.t.z, x1);
+#pragma unroll
+        for (int g = 0; g < GN; ++g) {
+          x0[g] = join(x0[g], ft[0][g]);
+          x1[g] = join(x1[g], ft[1][g]);
+        }
+        for (int j = kPairs, at = 0; at < S.nt; ++j) {
+          const bool has = S.len > 2 * j;
+          const uint64_t m = __ballot(has);
+          const int from = at + rank_in(m);
+          const float w0 = __shfl(__int_as_float(E.t.y), from), w1 = __shfl(__int_as_float(E.t.w), from);
+#pragma unroll
+          for (int g = 0; g < GN; ++g) {
+            const float y0 = __shfl(x0[g], from), y1 = __shfl(x1[g], from);
+            const float s = __builtin_fmaf(w1, y1, __builtin_fmaf(w0, y0, acc[g]));
+            acc[g] = has ? s : acc[g];
+          }
+          at += __popcll(m);
+        }
+      }
+    };
+
+    // The same sum straight from memory (after the wait for the stores of the
+    // earlier levels).
+    auto gather_slow = [&](const Slice<GN>& S, float* acc) {
+      wait_count(s_done + 1, S.dep, seen_st, a.flag);
+      const __amdgpu_buffer_rsrc_t ent = rsrc(a.ent + S.base, 16 * (int64_t)S.np);
+      const uint32_t lo4 = 4u * (uint32_t)(max(S.lim - R, 0) + 1);
+      int off = 0;
+      for (int j = 0;; ++j) {
+        const bool has = S.len > 2 * j;
+        const uint64_t m = __ballot(has);
+        if (m == 0ull) break;
+        const int4 e = ld_b128(ent, has ? 16u * (uint32_t)(off + rank_in(m)) : kOob, 0);
+        off += __popcll(m);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const int idx = 2 * (tid + i * nthr) + h;
-          const int p = h ? Q.st[i].z : Q.st[i].x;
-          po |= (uint32_t)(idx < L.nst && prefetchable(p, w, vis)) << (2 * i + h);
-        }
-      }
-      // the loads of a wavefront whose lanes need none are not issued
-      if (__ballot(po != 0u) != 0ull) {
+          const int x = h ? e.z : e.x;
+          const float w = __int_as_float(h ? e.w : e.y);
+          const bool old = has && (uint32_t)x < lo4;
+          const uint32_t d = REVERSE ? 4u * (uint32_t)B.C - (uint32_t)x : (uint32_t)x - 4u;
+          float v[GN], o[GN];
+          ld_gn<GN>(B.outs, old ? d * (uint32_t)a.G : kOob, 0, o);
+          lds_read<GN>(slot_of<GN>(x, mask4), v);
 #pragma unroll
-        for (int i = 0; i < CH / 2; ++i)
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const int p = h ? Q.st[i].z : Q.st[i].x;
-            ld_groups<GN>(B.outs, (po >> (2 * i + h)) & 1u ? 4u * (uint32_t)(p * a.G) : kOob,
-                          F[2 * i + h]);
-          }
-      }
-      visF = vis;
-    };
-    // staged entries of step s (value slots, followed by 8 padding entries that
-    // name the zero slot with factor 0) and the prefetched values into the staging
-    // buffer and value slots of s's parity; the thread's record into `cur`
-    auto publish = [&](int s, const Pref<GN, CH>& Q) {
-      const LevelInfo& L = Q.L;
-      const int b = s & 1;
-      int2* dst = stage + b * SP;
-      const Window w = window<REVERSE>(L.k0, L.k1, R);
-#pragma unroll
-      for (int i = 0; i < CH / 2; ++i) {
-        const int idx0 = 2 * (tid + i * nthr);
-        int4 v = Q.st[i];
-        if (2 * (wbase + i * nthr) >= L.nst + 8) {
-          // no entry of this wavefront in the step: the registers loaded for it
-          // (entries and prefetched values) are only consumed (a load nothing
-          // reads would leave its wait to a later reuse of the registers)
-          asm volatile("" ::"v"(v.x), "v"(v.y), "v"(v.z), "v"(v.w));
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int g = 0; g < GN; ++g) asm volatile("" ::"v"(F[2 * i + h][g]));
-          continue;
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int idx = idx0 + h;
-          const int p = h ? v.z : v.x;
-          const bool val = idx < L.nst;
-          const bool pf = val && prefetchable(p, w, visF);
-          const int fs = far0 + b * SE + idx;
-          const bool inw = w.has(p);
-          const int slot = !val ? zero : (inw ? (p & a.ring_mask) : (pf ? fs : zero));
-          if (val && !inw && !pf) s_bad[b] = gbase + s;
-          if (pf) {
-#pragma unroll
-            for (int g = 0; g < GN; ++g) vals[fs * GN + g] = F[2 * i + h][g];
-          }
-          const int addr = slot * (GN * 4);
-          if (h) {
-            v.z = addr;
-            v.w = !val ? 0 : v.w;
-          } else {
-            v.x = addr;
-            v.y = !val ? 0 : v.y;
+          for (int g = 0; g < GN; ++g) {
+            const float s = __builtin_fmaf(w, old ? o[g] : v[g], acc[g]);
+            acc[g] = has ? s : acc[g];
           }
         }
-        if (idx0 < L.nst + 8) *reinterpret_cast<int4*>(dst + idx0) = v;
       }
-      curL = L;
-      const bool act = L.k0 + tid < L.k1;
-      cur.c = act ? Q.c : -1;
-      cur.r0 = act ? (int)((uint32_t)Q.rp0 - (uint32_t)L.e0) : 0;
-      cur.r1 = act ? (int)((uint32_t)Q.rp1 - (uint32_t)L.e0) : 0;
-#pragma unroll
-      for (int g = 0; g < GN; ++g) {
-        cur.den[g] = Q.den[g];
-        cur.src[g] = Q.src[g];
-      }
-    };
-    auto solve = [&](int s) {
-      const int k0 = curL.k0, k1 = curL.k1;
-      const int64_t e0 = curL.e0;
-      const int2* stg = stage + (s & 1) * SP;
-      const Window w = window<REVERSE>(k0, k1, R);
-      const uint32_t eoff = 8u * (uint32_t)(e0 - B.ue0);
-      vis = REVERSE ? k1 : k0;
-      const bool bad = __builtin_amdgcn_readfirstlane(s_bad[s & 1]) == gbase + s;
-      if (curL.nst == curL.ne && k1 - k0 <= nthr && !bad) {
-        const Inflow<GN> in = gather_lds<GN>(cur, stg, smem);
-        finish_fast<GN>(a, B, cur, k0 + tid, in, ring, sinkp);
-        return;
-      }
-      for (int k = k0 + tid; k < k1; k += nthr) {
-        TaskRec<GN> t;
-        if (k == k0 + tid) t = cur; else load_rec<GN>(a, B, k, e0, t);
-        const Inflow<GN> in = gather<GN, false>(a, B, t, nullptr, eoff, ring, w);
-        finish_task<GN>(a, B, t, k, in, ring);
-      }
-      // the uncommon steps leave no memory operation of theirs in flight, so the
-      // waits of the common steps are counted exactly
+      // no memory operation of this path stays in flight, so the waits of the
+      // common path are counted exactly
       __builtin_amdgcn_s_waitcnt(0);
     };
-    // prologue: steps 0 .. NS - 1 in flight, the values of steps 0 and 1
-    // prefetched, step 0 staged.  Iteration s then solves step s, stages step
-    // s + 1 (its values were prefetched an iteration earlier), issues the loads
-    // of step s + NS into the set it freed and prefetches the values of step
-    // s + 2.
+
+    // The early-loaded results are consumed whether any were loaded or not (the loads
+    // issued after them are counted exactly, and nothing later waits for them).
+    auto consume_old = [&]() {
 #pragma unroll
-    for (int j = 0; j < NS; ++j) issue(j, P[j]);
-    farload(P[0]);
-    publish(0, P[0]);
-    farload(P[1]);
-    __syncthreads();
-    for (int s = 0; s < ns; s += NS) {
+      for (int q = 0; q < 2 * kPairs; ++q)
 #pragma unroll
-      for (int j = 0; j < NS; ++j) {
-        if (s + j >= ns) break;
-        solve(s + j);
-        // unconditional (past the last step it stages a copy of the last step
-        // into the staging buffer no solve reads), so every set of loads is
-        // consumed on every path and the waits stay exact
-        publish(s + j + 1, P[(j + 1) % NS]);
-        issue(s + j + NS, P[j]);
-        farload(P[(j + 2) % NS]);
-        __syncthreads();
-      }
+        for (int g = 0; g < GN; ++g) asm volatile("" : "+v"(f[q][g]));
+#pragma unroll
+      for (int g = 0; g < GN; ++g) asm volatile("" : "+v"(ft[0][g]), "+v"(ft[1][g]));
+    };
+
+    // One turn: slice S0 (entries E resolved) is solved, S1 (entries N in flight)
+    // is resolved, S2's entries are loaded into E, and the loads of the
+    // following slices are issued.
+    int i = wave;
+    auto turn = [&](Entries& E, Entries& N) {
+      consume_old();
+      // ring slot of the lane's result: the sink for lanes without a task and for
+      // positions of a level wider than the ring that a later one of the level reuses
+      const bool act = lane < S0.cnt;
+      const int code = 4 * (REVERSE ? B.C - (S0.k0 + lane) : S0.k0 + lane + 1);
+      const int at = act && code > 4 * (S0.lim - R) ? slot_of<GN>(code, mask4) : zero + 4 * GN;
+      wait_count(s_done, S0.dep, seen, a.flag);
+      __builtin_amdgcn_s_setprio(3);
+      float acc[GN], v[GN];
+#pragma unroll
+      for (int g = 0; g < GN; ++g) acc[g] = 0.0f;
+      if (bad) gather_slow(S0, acc);
+      else if (any) gather(S0, E, std::true_type{}, acc);
+      else gather(S0, E, std::false_type{}, acc);
+      const int n0 = S0.cnt > 0 ? 1 : 0;  // (past the wavefront's last slice a turn has no task)
+#pragma unroll
+      for (int g = 0; g < GN; ++g) v[g] = __fdiv_rn(__fadd_rn(acc[g], S0.src[g]), S0.den[g]);
+      lds_write<GN>(at, v);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      if (lane < n0) __hip_atomic_fetch_add(s_done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __builtin_amdgcn_s_setprio(0);
+      st_gn<GN>(v, B.outs, act ? 4u * (uint32_t)(S0.k0 * a.G) + lane4G : kOob);
+      int n1 = n0;
+      asm volatile("" : "+v"(n1));  // (its own condition, or the compiler splits the code between the two)
+      if (lane < n1) __hip_atomic_fetch_add(s_done + 1, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+      vis = S0.ks - lag;
+      Slice<GN> next = S2;
+      resolve(S1, N, [&]() {
+        // S2's tasks are consumed, by copies, before the early loads, whose number
+        // varies, are issued: their wait is counted exactly, and the registers they
+        // were loaded into take the next tasks' loads without a move behind those
+#pragma unroll
+        for (int g = 0; g < GN; ++g) {
+          asm volatile("v_mov_b32 %0, %1" : "=v"(next.den[g]) : "v"(S2.den[g]));
+          asm volatile("v_mov_b32 %0, %1" : "=v"(next.src[g]) : "v"(S2.src[g]));
+        }
+        asm volatile("v_mov_b32 %0, %1" : "=v"(next.len) : "v"(S2.len));
+        asm volatile("" : "+v"(info));
+      });
+      load_entries(next, E);
+      S0 = S1;
+      S1 = next;
+      take_info(i + 3 * nw, info, S2);
+      load_tasks(S2);
+      info = load_info(i + 4 * nw);
+      i += nw;
+    };
+    // prologue: slices i, i + nw, i + 2 nw of this wavefront
+    {
+      const int i0 = load_info(i), i1 = load_info(i + nw), i2 = load_info(i + 2 * nw);
+      info = load_info(i + 3 * nw);
+      take_info(i, i0, S0);
+      take_info(i + nw, i1, S1);
+      take_info(i + 2 * nw, i2, S2);
     }
-    gbase += ns + 1;  // past the last step's number and the one staged after it
+    load_tasks(S0);
+    load_tasks(S1);
+    load_tasks(S2);
+#pragma unroll
+    for (int q = 0; q < 2 * kPairs; ++q)
+#pragma unroll
+      for (int g = 0; g < GN; ++g) f[q][g] = 0.0f;
+#pragma unroll
+    for (int g = 0; g < GN; ++g) ft[0][g] = ft[1][g] = 0.0f;
+    load_entries(S0, EA);
+    load_entries(S1, EB);
+    resolve(S0, EA, []() {});
+    consume_old();
+    __builtin_amdgcn_s_waitcnt(0);
+    while (i < B.ns) {
+      turn(EA, EB);
+      turn(EB, EA);  // (a turn past the last slice has nothing to wait for and counts nothing)
+    }
   }
 }
 
 template <int GN, bool REVERSE>
 hipError_t launch_sweep_g(const SweepArgs& a, int32_t grid, int32_t block, size_t lds,
                           hipStream_t s) {
-  if ((block != 256 && block != 512 && block != 1024) || block > kSweepMaxBlock(GN))
-    return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_sweep<GN, REVERSE, kStageCh>), dim3(grid), dim3(block), lds, s, a);
+  if (block < 64 || block % 64 != 0 || block > kSweepMaxBlock(GN)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_sweep<GN, REVERSE>), dim3(grid), dim3(block), lds, s, a);
   return hipGetLastError();
+}
+
+__device__ __forceinline__ int unit_of_block(const int32_t* blk_base, int n_units, int b) {
+  int lo = 0, hi = n_units - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (blk_base[mid] <= b) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+
+// Workgroups are dispatched round-robin over the 8 XCDs, each with its own L2
+// cache: this renumbering gives each XCD one contiguous range of the grid.
+__device__ __forceinline__ int xcd_block(int b, int nb) {
+  constexpr int kXcd = 8;
+  const int per = nb / kXcd, rem = nb % kXcd;
+  const int x = b % kXcd;
+  return x * per + min(x, rem) + b / kXcd;
+}
+
+// Results in schedule order -> cell order, [D][C][G]: one thread per (cell, VEC
+// consecutive groups), the workgroups of a unit together on one XCD so that its
+// gathers find the unit's lines in that L2.  Memory-bound: 2M cells x 84 directions x 4
+// groups (5.6 GB of results in and out, 0.7 GB of positions) in 1.5 ms.
+template <int VEC>
+__global__ __launch_bounds__(256) void k_to_cells(const Unit* units, int n_units, const int32_t* blk_base,
+                                                  const int32_t* inv, const float* out_s, float* out,
+                                                  int64_t C_total, int G) {
+  const int blk = xcd_block(blockIdx.x, gridDim.x);
+  const int u = unit_of_block(blk_base, n_units, blk);
+  const Unit U = units[u];
+  const int c0 = (blk - blk_base[u]) * 256;
+  const int n = min(256, U.n_cells - c0);
+  const int64_t ob = (((int64_t)U.dir * C_total + U.cell_off) + c0) * G;
+  const int32_t* iv = inv + U.task_base + c0;
+  const float* os = out_s + U.task_base * G;
+  const int GV = G / VEC;
+  for (int i = threadIdx.x; i < n * GV; i += 256) {
+    const int c = i / GV, g = i - c * GV;
+    struct __attribute__((aligned(4 * VEC))) Vec {
+      float x[VEC];
+    };
+    reinterpret_cast<Vec*>(out + ob)[i] = reinterpret_cast<const Vec*>(os + (int64_t)iv[c] * G)[g];
+  }
 }
 
 template <bool REVERSE>
@@ -723,15 +729,6 @@ __global__ __launch_bounds__(256) void k_prep_cells(PrepArgs a) {
     bad |= kErrEmission;
   if (bad != 0) atomicOr(a.flag, bad);
   a.crec[i] = make_float2(a.kappa[i], (float)s);
-}
-
-__device__ __forceinline__ int unit_of_block(const int32_t* blk_base, int n_units, int b) {
-  int lo = 0, hi = n_units - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (blk_base[mid] <= b) lo = mid; else hi = mid - 1;
-  }
-  return lo;
 }
 
 // Tasks of a workgroup whose G values per task are staged in LDS, so that the
@@ -1030,17 +1027,6 @@ inline unsigned grid1d(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 }  // namespace
 
-LdsLayout sweep_lds_layout(int32_t gn, int32_t ring, int32_t block) {
-  LdsLayout L;
-  const size_t se = (size_t)kStageCh * block;
-  size_t off = (size_t)gn * (ring + 2 + 2 * se) * sizeof(float);  // ring, zero, sink, prefetched
-  off = (off + 15) & ~(size_t)15;
-  L.stage_off = (int32_t)off;
-  off += 2 * (se + 8) * sizeof(int2);  // two staging buffers, 8 entries of padding
-  L.bytes = off;
-  return L;
-}
-
 hipError_t launch_sweep_fwd(const SweepArgs& a, int32_t gn, int32_t grid, int32_t block,
                             size_t lds, hipStream_t s) {
   return launch_sweep_t<false>(a, gn, grid, block, lds, s);
@@ -1049,6 +1035,22 @@ hipError_t launch_sweep_fwd(const SweepArgs& a, int32_t gn, int32_t grid, int32_
 hipError_t launch_sweep_adj(const SweepArgs& a, int32_t gn, int32_t grid, int32_t block,
                             size_t lds, hipStream_t s) {
   return launch_sweep_t<true>(a, gn, grid, block, lds, s);
+}
+
+hipError_t launch_to_cells(const Unit* units, int32_t n_units, const int32_t* blk_base, int32_t n_blocks,
+                           const int32_t* inv, const float* out_s, float* out, int64_t C_total,
+                           int32_t G, hipStream_t s) {
+  if (n_blocks <= 0) return hipSuccess;
+  // several groups in one access where every address is a multiple of it
+  const uintptr_t al = reinterpret_cast<uintptr_t>(out) | reinterpret_cast<uintptr_t>(out_s);
+  auto launch = [&](auto fn) {
+    hipLaunchKernelGGL(fn, dim3(n_blocks), dim3(256), 0, s, units, n_units, blk_base, inv, out_s, out,
+                       C_total, G);
+  };
+  if (G % 4 == 0 && al % 16 == 0) launch(k_to_cells<4>);
+  else if (G % 2 == 0 && al % 8 == 0) launch(k_to_cells<2>);
+  else launch(k_to_cells<1>);
+  return hipGetLastError();
 }
 
 hipError_t launch_prep(const PrepArgs& a, int32_t n_blocks, hipStream_t s) {
@@ -1061,7 +1063,7 @@ hipError_t launch_prep(const PrepArgs& a, int32_t n_blocks, hipStream_t s) {
 
 template <int GN, bool REVERSE>
 hipError_t set_lds_g(int32_t bytes) {
-  return hipFuncSetAttribute((const void*)k_sweep<GN, REVERSE, kStageCh>,
+  return hipFuncSetAttribute((const void*)k_sweep<GN, REVERSE>,
                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
