@@ -883,9 +883,14 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
     max_cells = std::max(max_cells, meshes[m].n_cells);
   }
   const int n_cblocks = (int)cbm.size();
-  // scheme (b) rows hold at most n_aligned <= 4 entries: never any overflow
-  int dn_width = scheme == SWEEP_SCHEME_ALIGNED ? sweep::kMaxAligned
-                                                : std::min(kRowNarrow, (max_faces + 3) / 4 * 4);
+  // scheme (b) rows hold at most n_aligned <= 4 entries: never any overflow.  Widths are
+  // powers of two (Kahn's algorithm reads a row with width / 4 lanes)
+  auto row_width = [&](int cap) {
+    int w = 4;
+    while (w < std::min(cap, max_faces)) w *= 2;
+    return w;
+  };
+  int dn_width = scheme == SWEEP_SCHEME_ALIGNED ? sweep::kMaxAligned : row_width(kRowNarrow);
   const int64_t ovf_cap_narrow = std::max<int64_t>(1 << 20, T / 4);
   if (ovf_cap > INT32_MAX / 2)
     return fail(SWEEP_ERR_UNSUPPORTED, "too many cells with more than %d faces", kRowCap);
@@ -991,9 +996,7 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   int32_t n_big = 0;
   for (int attempt = 0;; ++attempt) {
     const int64_t cap = dn_width == kRowNarrow ? ovf_cap_narrow : ovf_cap;
-    const int sent_len = std::max(64, dn_width);  // sentinel row of -1 after the rows
-    HIP_TRY(dnw.alloc(4 * ((size_t)T * dn_width + sent_len)));
-    HIP_TRY(sweep::launch_fill_i32(dnw.as<int32_t>() + (size_t)T * dn_width, sent_len, -1, s));
+    HIP_TRY(dnw.alloc(4 * (size_t)T * dn_width));
     // the pool ends with room for one list that is written when it has run out
     HIP_TRY(dn_ovf.alloc(4 * (cap + max_faces + 2)));
     HIP_TRY(sweep::launch_fill_i32(dn_ovf_top.as<int32_t>(), 1, 0, s));
@@ -1002,7 +1005,6 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
     HIP_TRY(sweep::launch_fill_i32(ent_tot.as<int32_t>(), 4, 0, s));
     a.dn_width = dn_width;
     a.dnw = dnw.as<int32_t>();
-    a.dn_sentinel = (int64_t)T * dn_width;
     a.dn_ovf = dn_ovf.as<int32_t>();
     a.dn_ovf_cap = cap;
     {
@@ -1021,32 +1023,33 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
     if (top <= cap) break;
     if (dn_width >= kRowCap || attempt > 0)
       return fail(SWEEP_ERR_HIP, "downwind overflow pool exhausted (%d > %lld)", top, (long long)cap);
-    dn_width = std::min(kRowCap, (max_faces + 3) / 4 * 4);
+    dn_width = row_width(kRowCap);
   }
-  // the longest downwind list sets how much of every row Kahn's algorithm loads
-  a.dn_chunks = std::max(1, std::min(dn_width / 4, (stats[1] + 3) / 4));
   HIP_TRY(D->len_up.alloc(4 * T));
   HIP_TRY(D->len_dn.alloc(4 * T));
   a.len_up = D->len_up.as<int32_t>();
   a.len_dn = D->len_dn.as<int32_t>();
   HIP_TRY(nsl_d.alloc(4 * n_units));
   a.n_unit_slices = nsl_d.as<int32_t>();
-  // Kahn counters in LDS as 4-bit fields when the mesh fits the LDS
-  // (the kernel's static LDS holds two frontier copies of 2048 cells); the
+  // Kahn counters in LDS as bytes or 4-bit fields when the mesh fits the LDS
+  // (the kernel's static LDS holds two frontier copies of 2048 cells); with 4 bits the
   // rows' entries of cells with larger counts are flagged first
-  const bool lds_fits = (size_t)4 * ((max_cells + 7) / 8 + 64) + 17 * 1024 <= (size_t)lds_limit;
+  const bool lds_fits = sweep::kahn_lds_bytes(4, max_cells) + 17 * 1024 <= (size_t)lds_limit;
+  const bool bytes_fit = stats[0] <= 254 && sweep::kahn_lds_bytes(8, max_cells) + 17 * 1024 <= (size_t)lds_limit;
   if (kahn_counters == 1 && !lds_fits)
     return fail(SWEEP_ERR_UNSUPPORTED, "the counters of a %d-cell mesh do not fit in LDS", max_cells);
   const bool lds_cnt = kahn_counters == 2 ? false : lds_fits;
-  // counters in global memory are bytes
+  // otherwise in an LDS hash table of the cells being counted, or as bytes in global memory
+  a.hash_bits = lds_cnt ? 0 : sweep::kahn_hash_bits(max_cells, stats[0]);
   if (!lds_cnt && stats[0] > 254)
     return fail(SWEEP_ERR_UNSUPPORTED, "a cell with %d upwind dependencies in one direction "
                 "(at most 254 when the mesh's counters do not fit in LDS)", stats[0]);
   D->kahn_lds = lds_cnt ? 1 : 0;
-  if (lds_cnt) HIP_TRY(sweep::launch_mark(a, n_big, s));
+  const int lds_bits = !lds_cnt ? 0 : bytes_fit ? 8 : 4;
+  if (lds_bits == 4) HIP_TRY(sweep::launch_mark(a, n_big, s));
   {
     ProfScope ps("kahn", s);
-    HIP_TRY(sweep::launch_kahn(a, lds_cnt, max_cells, s));
+    HIP_TRY(sweep::launch_kahn(a, lds_bits, max_cells, s));
   }
   HIP_TRY(sweep::launch_count_slices(a, s));
   // the inverse schedule of cells that a cyclic graph leaves out stays -1

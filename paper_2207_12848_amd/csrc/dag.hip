@@ -6,7 +6,8 @@
 //
 //   k_count   per task (unit, cell): upwind/downwind counts, Aperp, boundary outflow
 //   k_kahn    per unit, one workgroup: levels by Kahn's algorithm (algorithm 2's
-//             counters), ready cells compacted with wavefront ballots
+//             counters, in LDS or a hash table there), ready cells compacted with
+//             wavefront ballots
 //   k_slices  the sweep's slices: every level in runs of at most 64 tasks
 //   k_gather_tasks, k_fill  row lengths and rows of the upwind/downwind lists,
 //             stored slice by slice in schedule order (and Aperp and the volumes in
@@ -27,13 +28,6 @@ constexpr int kCountBlock = 256;
 // workgroups with their face tiles and staged rows keep 16 wavefronts per CU
 constexpr int kCountThreads = 512;
 constexpr int kTileCells = 32;  // cells per tile of the cell-order kernels
-// Workgroup of Kahn's algorithm: 15 worker wavefronts and one that stores the
-// schedule (the largest workgroup).  A level's frontier is processed in rounds
-// of one task per worker thread, each round a chain of dependent memory round
-// trips (row loads, then counter decrements), so a typical level of a few
-// hundred tasks takes one round.
-constexpr int kKahnBlock(int) { return 1024; }
-
 __device__ __forceinline__ double orient(double ox, double oy, double oz, const double* n) {
   const double a = ox * n[0];
   const double b = oy * n[1];
@@ -410,11 +404,11 @@ __global__ __launch_bounds__(kCountThreads) void k_count_in(DagBuildArgs a) {
 // Tasks with 15 or more upwind dependencies keep their counter in global
 // memory; the entries that point at them in their upwind cells' downwind rows
 // get bit 30 set, so that Kahn's algorithm sends those decrements there without
-// first reading the LDS counter.  One thread per such task (rare).
+// first reading the LDS counter.  One wavefront per such task, one face per lane.
 constexpr int32_t kBigFlag = 0x40000000;
 
-__global__ void k_mark(DagBuildArgs a, int32_t n_big) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(256) void k_mark(DagBuildArgs a, int32_t n_big) {
+  const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (i >= n_big) return;
   const int64_t t = a.big[i];
   int lo = 0, hi = a.n_units - 1;  // unit of task t (task bases ascend)
@@ -428,7 +422,7 @@ __global__ void k_mark(DagBuildArgs a, int32_t n_big) {
   const double ox = a.dirs[3 * U.dir], oy = a.dirs[3 * U.dir + 1], oz = a.dirs[3 * U.dir + 2];
   const int W = a.dn_width;
   const float* wf = a.wface + (int64_t)a.D * M.face_off + (int64_t)U.dir * M.n_faces;
-  for (int64_t f = M.face_ptr[c]; f < M.face_ptr[c + 1]; ++f) {
+  for (int64_t f = M.face_ptr[c] + (threadIdx.x & 63); f < M.face_ptr[c + 1]; f += 64) {
     const int nb = M.face_nbr[f];
     if (nb < 0 || (M.face_shift != nullptr && M.face_shift[f] != 0)) continue;
     const bool upwind = a.scheme == SWEEP_SCHEME_ALIGNED ? !isnan(wf[M.face_twin[f]])
@@ -436,11 +430,14 @@ __global__ void k_mark(DagBuildArgs a, int32_t n_big) {
     if (!upwind) continue;
     // nb is upwind of c: flag c in nb's row (or in its overflow list)
     int32_t* row = a.dnw + (U.task_base + nb) * W;
-    for (int q = 0; q < W; ++q) {
-      const int e = row[q];
-      if (e == c) row[q] = c | kBigFlag;
-      if (q == W - 1 && e < -1) {
-        int32_t* ov = a.dn_ovf + (-(e + 2));
+    for (int q = 0; q < W; q += 4) {
+      const int4 e = *reinterpret_cast<const int4*>(row + q);
+      if (e.x == c) row[q] = c | kBigFlag;
+      if (e.y == c) row[q + 1] = c | kBigFlag;
+      if (e.z == c) row[q + 2] = c | kBigFlag;
+      if (e.w == c) row[q + 3] = c | kBigFlag;
+      if (q == W - 4 && e.w < -1) {
+        int32_t* ov = a.dn_ovf + (-(e.w + 2));
         for (int r = 1; r <= ov[0]; ++r)
           if (ov[r] == c) ov[r] = c | kBigFlag;
       }
@@ -450,40 +447,92 @@ __global__ void k_mark(DagBuildArgs a, int32_t n_big) {
 
 constexpr int kFrontierCap = 2048;  // frontier entries kept in LDS per level
 
-// Inclusive prefix sum over the 64 lanes of a wavefront (all lanes active):
-// shifts of 1, 2, 4, 8 inside each row of 16 lanes, then the row totals are
-// carried into the following rows with the row broadcasts of lanes 15 and 31.
-__device__ __forceinline__ int wave_inclusive_sum(int x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31
-  return x;
+// Where Kahn's counters live (k_kahn).
+enum KahnMode { kKahnLds4 = 0, kKahnLds8 = 1, kKahnGlobal = 2, kKahnHash = 3 };
+
+// The hash table of counters: a bucket is two words, four tag bytes and four
+// counts.  Cell c belongs to one bucket, and its tag c / buckets + 1 (0: free way)
+// tells it from the others there: consecutive cells (neighbours on the
+// space-filling curve) lie in different buckets.  A free way's count is kHashBias.
+constexpr int kHashBits = 14;  // at most 2^14 buckets (128 KB)
+constexpr uint32_t kHashBias = 128;
+constexpr int kMissCap = 2048;  // a level's decrements that did not find their cell, listed in LDS
+
+using lds_int = int __attribute__((address_space(3)));
+
+// Lanes of `m` below this one.
+__device__ __forceinline__ int rank_in(unsigned long long m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// First byte of w that is 0, as its bit offset (0, 8, 16, 24); -1 if there is none.
+// (The bytes above a zero byte may be marked wrongly, the lowest mark is exact.)
+__device__ __forceinline__ int zero_byte(uint32_t w) {
+  const uint32_t t = (w - 0x01010101u) & ~w & 0x80808080u;
+  return t != 0u ? (__ffs((int)t) - 1) & 24 : -1;
 }
 
 // Kahn's algorithm for one (mesh, direction) unit per workgroup: tasks without
 // upwind dependencies form level 0; solving a level decrements the counters of
 // its tasks' downwind cells and those reaching zero form the next level.  The
 // schedule lists every level's cells in the order they were appended (slots
-// [lp[l], lp[l+1]) hold level l), together with its inverse.
-// LDSCNT: the counters live in LDS as 4-bit fields; the value 15 marks a cell
-// whose count (>= 15) is kept in global memory instead (it is never changed, so
-// reading the field to pick the counter is race-free).
-// NCH: chunks of 4 entries of a downwind row that are loaded at once (rows are
-// -1 padded; NCH covers the longest list, or the whole row when some list
-// continues in the overflow area).
-template <bool LDSCNT, int NCH>
-__global__ __launch_bounds__(kKahnBlock(NCH)) void k_kahn(DagBuildArgs a) {
-  extern __shared__ uint32_t nib[];
-  __shared__ int fr[2][kFrontierCap];
+// [lp[l], lp[l+1]) hold level l); k_sort_levels brings it into canonical order.
+//
+// Each lane takes four entries of a downwind row (the lanes of a row read it with
+// one line request, and a level of a few hundred tasks keeps every wavefront
+// busy); ready cells are compacted with ballots and one LDS atomic per wavefront.
+// The last wavefront makes every global store of the level loop (the schedule and
+// the level pointers) and never waits for a load, so the others' waits for row
+// loads never include a store.
+//
+// Counters:
+//  kKahnLds8    bytes in LDS, when the largest mesh fits (and no task has more than
+//               254 dependencies).
+//  kKahnLds4    4-bit fields in LDS, when those fit; the value 15 marks a cell whose
+//               count (>= 15) is kept in global memory instead (it is never changed,
+//               so reading the field to pick the counter is race-free; the entries that
+//               point at such cells are flagged beforehand, k_mark).  A decrement in
+//               global memory costs its level a round trip, which on meshes of a few
+//               thousand cells was most of the level.
+//  kKahnHash    larger meshes: only cells between their first and last decrement need
+//               a counter on chip (about 20,000 of 2M clustered cells at a time).  They
+//               live in an LDS hash table.  A level's decrements that find their cell
+//               in the table are made at once; the others are listed and, after a
+//               barrier, made by full wavefronts: the first of a cell inserts it and
+//               loads its remaining count (a byte in global memory).  A ready cell is
+//               removed while the next level's rows are loaded, so that while cells
+//               are inserted full buckets stay full and every lane of a cell comes to
+//               the same decision.  A cell whose bucket is full is decremented in
+//               global memory, where a later insertion finds its remaining count.
+//  kKahnGlobal  bytes in global memory, four to a word: cells with more dependencies
+//               than the hash table's count holds, or meshes too large for its keys.
+//
+// What bounds it: narrow levels, the chain from a level's barrier to the next (the
+// rows come from HBM); wider ones, the instructions of 16 wavefronts (about 90 per
+// row's lane and batch).  Per launch, against one lane per row of 16 entries and
+// counters of larger meshes decremented in global memory (1.1 G atomics there at 2M
+// cells): 4,096 cells x 8 directions 0.63 -> 0.21 ms, 64^3 jittered cells x 84
+// directions 4.0 -> 2.3 ms, 2M clustered cells x 84 directions 69 -> 41 ms.  Loading
+// a word of each newly ready cell's row at once, so that the next level finds it in
+// L2, made it 7 to 9 % slower.
+template <int MODE>
+__global__ __launch_bounds__(1024) void k_kahn(DagBuildArgs a) {
+  extern __shared__ __align__(16) uint32_t tab[];  // counters or hash table
+  constexpr bool LDS = MODE == kKahnLds4 || MODE == kKahnLds8;
+  constexpr int B = MODE == kKahnLds4 ? 4 : 8;  // bits of a counter in LDS, 32 / B to a word
+  constexpr int PW = 32 / B;
+  constexpr int LPW = MODE == kKahnLds4 ? 3 : 2;
+  constexpr uint32_t M = (1u << B) - 1u;
+  __shared__ int fr[2][kFrontierCap + 64];  // and 64 dummy words
   __shared__ int s_cnt[3];
+  __shared__ int misses[MODE == kKahnHash ? kMissCap + 64 : 1];
+  __shared__ int s_nmiss[2];
   const Unit U = a.units[blockIdx.x];
   const int C = U.n_cells;
   const int64_t tb = U.task_base;
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int lane = tid & 63;
+  const int wfirst = __builtin_amdgcn_readfirstlane(tid & ~63);  // the wavefront's first thread
   int32_t* cnt = a.cnt + tb;
   // counters in global memory: one byte per cell, four to a word, so that the
   // counters of a whole unit (C bytes) stay in the last-level caches
@@ -492,35 +541,41 @@ __global__ __launch_bounds__(kKahnBlock(NCH)) void k_kahn(DagBuildArgs a) {
   int32_t* sched = a.sched + tb;
   int32_t* spill = sched;  // frontier entries beyond the LDS copy (rewritten in place)
   int32_t* lp = a.lp + U.lp_base;
-  const int W = a.dn_width;
-  const int Wr4 = W / 4;  // chunks per row
+  const int W = a.dn_width;          // 4, 8, 16 or 32
+  const int sh = 31 - __clz(W >> 2); // lanes per row: 1 << sh
   if (tid < 3) s_cnt[tid] = 0;
-  const int nwords = (C + 7) / 8;  // counter words; 64 dummy words follow
-  if (LDSCNT) {
-    if (tid < 64) nib[nwords + tid] = 0u;
+  if (tid < 2) s_nmiss[tid] = 0;
+  const int nwords = (C + PW - 1) / PW;  // counter words; 64 dummy words follow
+  const int hbits = a.hash_bits;
+  if (LDS) {
+    if (tid < 64) tab[nwords + tid] = 0u;
     for (int wi = tid; wi < nwords; wi += nthr) {
-      int n[8];
+      int n[PW];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) n[j] = a.indeg[tb + min(8 * wi + j, C - 1)];
+      for (int j = 0; j < PW; ++j) n[j] = a.indeg[tb + min(PW * wi + j, C - 1)];
       uint32_t v = 0;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int c = 8 * wi + j;
+      for (int j = 0; j < PW; ++j) {
+        const int c = PW * wi + j;
         if (c < C) {
-          if (n[j] >= 15) cnt[c] = n[j];
-          v |= (uint32_t)min(n[j], 15) << (4 * j);
+          if (MODE == kKahnLds4 && n[j] >= 15) cnt[c] = n[j];
+          v |= (uint32_t)min(n[j], (int)M) << (B * j);
         }
       }
-      nib[wi] = v;
+      tab[wi] = v;
     }
+  }
+  if (MODE == kKahnHash) {
+    for (uint32_t i = tid; i < 2u << hbits; i += nthr) tab[i] = (i & 1u) ? kHashBias * 0x01010101u : 0u;
+    if (tid < 64) tab[(2u << hbits) + tid] = 0u;  // dummy words
   }
   __syncthreads();
   // level 0: cells without upwind dependencies (global counters: the in-degrees
   // of kInitBatch cells per thread are loaded together, then stored as bytes)
-  constexpr int kInitBatch = LDSCNT ? 1 : 8;
+  constexpr int kInitBatch = LDS ? 1 : 8;
   for (int c0 = 0; c0 < C; c0 += kInitBatch * nthr) {
     int n[kInitBatch];
-    if (!LDSCNT) {
+    if (!LDS) {
 #pragma unroll
       for (int j = 0; j < kInitBatch; ++j) {
         const int c = c0 + j * nthr + tid;
@@ -532,8 +587,8 @@ __global__ __launch_bounds__(kKahnBlock(NCH)) void k_kahn(DagBuildArgs a) {
       const int c = c0 + j * nthr + tid;
       bool ready = false;
       if (c < C) {
-        if (LDSCNT) {
-          ready = ((nib[c >> 3] >> (4 * (c & 7))) & 15u) == 0u;
+        if (LDS) {
+          ready = ((tab[c >> LPW] >> (B * (c & (PW - 1)))) & M) == 0u;
         } else {
           cnt8[c] = (uint8_t)n[j];  // below 256 (the host checks the largest in-degree)
           ready = n[j] == 0;
@@ -564,210 +619,292 @@ __global__ __launch_bounds__(kKahnBlock(NCH)) void k_kahn(DagBuildArgs a) {
     lp[1] = tail;
   }
   __syncthreads();
-  const int4* sent4 = reinterpret_cast<const int4*>(a.dnw + a.dn_sentinel);
-  // The last wavefront makes every global store of the level loop (the
-  // schedule and the level pointers; the inverse schedule is written when the
-  // levels are sorted, k_sort_levels) and never waits for a load;
-  // the other wavefronts process the frontier and only load, so their waits for
-  // row loads never include a store (the vector-memory counter is in order).
   const int nwork = nthr - 64;
-  const bool writer = tid >= nwork;
+  const bool writer = wfirst >= nwork;
+  const int4* rows = reinterpret_cast<const int4*>(a.dnw + tb * W);  // (at most 2^31 chunks: T < 2^31)
+
+  // Decrement of a counter in global memory; true if the cell became ready.
+  auto dec_global = [&](int nb) -> bool {
+    if (MODE == kKahnLds4) {  // whole words (cells with 15 or more dependencies)
+      const int old = __hip_atomic_fetch_add(cnt + nb, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      return old == 1;
+    }
+    const uint32_t s8 = (uint32_t)(nb & 3) * 8u;
+    const uint32_t old = __hip_atomic_fetch_add(cntw + (nb >> 2), 0u - (1u << s8), __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_WORKGROUP);
+    return ((old >> s8) & 255u) == 1u;
+  };
+  // Hash table: a cell's bucket (index of its tag word) and tag.
+  auto bucket_of = [&](int c) -> uint32_t {
+    return 2u * (((uint32_t)c ^ __umul24((uint32_t)c >> hbits, 2897u)) & ((1u << hbits) - 1u));
+  };
+  auto tags_of = [&](int c) -> uint32_t {
+    return __builtin_amdgcn_perm(0u, ((uint32_t)c >> hbits) + 1u, 0u);  // in all four bytes
+  };
+  // the remaining count past any cached copy (it may have been lowered in memory)
+  auto remaining = [&](int c) -> uint32_t {
+    const uint32_t w = __hip_atomic_load(cntw + (c >> 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return (w >> ((c & 3) * 8)) & 255u;
+  };
+  // One decrement of a cell that was not in the table (or may be by now); true if
+  // the cell became ready.
+  auto dec_new = [&](int c) -> bool {
+    const uint32_t b = bucket_of(c), tg = tags_of(c);
+    int at;
+    bool fresh = false;
+    for (;;) {  // (a lost race means that another lane filled a way: at most 4 times)
+      const uint32_t w = __hip_atomic_load(&tab[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      at = zero_byte(w ^ tg);
+      if (at >= 0) break;
+      at = zero_byte(w);
+      if (at < 0) break;
+      if (atomicCAS(&tab[b], w, w | ((tg & 255u) << at)) == w) {
+        fresh = true;
+        break;
+      }
+    }
+    if (at < 0) return dec_global(c);
+    // a new cell counts down from the bias until its remaining count is known
+    uint32_t by = 1u;
+    if (fresh) by += kHashBias - remaining(c);
+    const uint32_t old = atomicSub(&tab[b + 1], by << at);
+    return ((old >> at) & 255u) == by;
+  };
+  auto remove = [&](int c) {
+    const uint32_t b = bucket_of(c);
+    const int at = zero_byte(tab[b] ^ tags_of(c));
+    if (at < 0) return;
+    atomicAnd(&tab[b], ~(255u << at));
+    atomicAdd(&tab[b + 1], kHashBias << at);  // (a ready cell's count is 0)
+  };
+  auto dec_one = [&](int e) -> bool {  // one entry, any mode (overflow lists)
+    const int nb = e & ~kBigFlag;
+    if (LDS) {
+      if ((e & kBigFlag) != 0) return dec_global(nb);
+      const uint32_t sb = (uint32_t)(nb & (PW - 1)) * B;
+      return ((atomicSub(&tab[nb >> LPW], 1u << sb) >> sb) & M) == 1u;
+    }
+    if (MODE == kKahnGlobal) return dec_global(nb);
+    return dec_new(nb);
+  };
+
   // Level l: the frontier is [head, tail); its pushes count in s_cnt[l % 3].
   // s_cnt[(l + 1) % 3] was last read right after the barrier that ended level
-  // l - 2, so it can be cleared now for level l + 1; one barrier per level.
+  // l - 2, so it can be cleared now for level l + 1.
   while (head < tail) {
-    if (tid == 0) s_cnt[(l + 1) % 3] = 0;
+    if (tid == 0) {
+      s_cnt[(l + 1) % 3] = 0;
+      s_nmiss[(l + 1) & 1] = 0;
+    }
     int* s_push = &s_cnt[l % 3];
-    const int* frc = fr[l & 1];
-    int* frn = fr[(l + 1) & 1];
-    const bool fr_lds = tail - head <= kFrontierCap;  // the whole frontier is in LDS
+    int* s_miss = &s_nmiss[l & 1];
+    // (LDS pointers by type: mixed with the spill's pointer they became flat accesses)
+    lds_int* const frc = (lds_int*)fr[l & 1];
+    lds_int* const frn = (lds_int*)fr[(l + 1) & 1];
+    const int dummy = kFrontierCap + lane;
+    const int n = tail - head;
+    const bool fr_lds = n <= kFrontierCap;  // the whole frontier is in LDS
     if (writer) {
       // the level's cells in slot order form the schedule (entries past the LDS
       // copy are in place already; each store is issued without waiting)
-      const int n = min(tail - head, kFrontierCap);
-      for (int i = lane; i < n; i += 64) sched[head + i] = frc[i];
+      const int ns = min(n, kFrontierCap);
+      for (int i = lane; i < ns; i += 64) sched[head + i] = frc[i];
       if (lane == 0) lp[l + 1] = tail;
     }
-    for (int kb = head; !writer && kb < tail; kb += nwork) {
-      const int k = kb + tid;
-      const bool active = k < tail;
-      if (__ballot(active) == 0ull) continue;  // wavefront without tasks this round
-      const int kk = k - head;
+    auto cell_at = [&](int kk) -> int {
+      if (fr_lds) return frc[kk];
       int c;
-      if (fr_lds) {
-        c = active ? frc[kk] : 0;
+      if (kk < kFrontierCap) {
+        c = frc[kk];
       } else {
-        c = !active ? 0 : (kk < kFrontierCap ? frc[kk] : spill[k]);
-        // no load of this path stays in flight: the common path's waits for the
-        // loads of earlier levels are then counted exactly
-        __builtin_amdgcn_s_waitcnt(0);
+        c = spill[head + kk];
       }
-      // all NCH chunk loads are unconditional: lanes without a task, and chunks
-      // past the row width, read a sentinel row of -1 instead (an address
-      // select), so they are in flight together
-      const int4* row4 = active ? reinterpret_cast<const int4*>(a.dnw + (tb + c) * W) : sent4;
-      int4 v[NCH];
+      // no load of this path stays in flight: the common path's waits for the
+      // loads of earlier levels are then counted exactly
+      __builtin_amdgcn_s_waitcnt(0);
+      return c;
+    };
+    // four entries of the row of frontier cell idx >> sh (none: -1)
+    auto load = [&](int idx) -> int4 {
+      if (idx >= n << sh) return make_int4(-1, -1, -1, -1);
+      const int c = cell_at(idx >> sh);
+      return rows[(uint32_t)((c << sh) | (idx & ((1 << sh) - 1)))];
+    };
+    // cells that became ready, appended to the next frontier: ballots and one LDS
+    // atomic per wavefront
+    auto push = [&](const bool (&ready)[4], const int (&xs)[4], auto n_c) {
+      constexpr int N = decltype(n_c)::value;
+      unsigned long long m[N];
+      int total = 0;
 #pragma unroll
-      for (int q = 0; q < NCH; ++q) v[q] = (q < Wr4 ? row4 : sent4)[q];
-      // a counter in global memory: 32-bit words of four byte counters (LDSCNT,
-      // the counters of cells with 15 or more dependencies: whole words)
-      auto dec_global = [&](int nb) -> bool {
-        if (LDSCNT) {
-          const int old = __hip_atomic_fetch_add(cnt + nb, -1, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_WORKGROUP);
-          return old == 1;
-        }
-        const uint32_t sh = (uint32_t)(nb & 3) * 8u;
-        const uint32_t old = __hip_atomic_fetch_add(cntw + (nb >> 2), 0u - (1u << sh), __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_WORKGROUP);
-        return ((old >> sh) & 255u) == 1u;
-      };
-      uint32_t wm = 0;  // bit 4q+i: cell i of chunk q became ready
-      if (LDSCNT) {
-        // rows are -1 padded at the end, so the wavefront's non-empty chunks are
-        // the first nq; inside them every entry issues one LDS decrement without
-        // a branch (padding and flagged entries use the lane's private dummy
-        // word and a zero operand); flagged entries (counters kept in global
-        // memory) are decremented there afterwards
-        int nq = 0;
+      for (int i = 0; i < N; ++i) {
+        m[i] = __ballot(ready[i]);
+        total += __popcll(m[i]);
+      }
+      if (total == 0) return;
+      int base = 0;
+      if (lane == 0) base = atomicAdd(s_push, total);
+      base = __builtin_amdgcn_readfirstlane(base);
+      if (base + total <= kFrontierCap) {
+        // (lanes without a ready cell write their dummy word: no branches)
 #pragma unroll
-        for (int q = 0; q < NCH; ++q) nq += __ballot(v[q].x >= 0) != 0ull ? 1 : 0;
-        const int dummy = nwords + lane;
-        uint32_t old[4 * NCH];
-        bool any_big = false;
-#pragma unroll
-        for (int q = 0; q < NCH; ++q) {
-          if (q >= nq) break;
-          const int xs[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int e = xs[i];
-            const bool big = e >= 0 && (e & kBigFlag) != 0;
-            const bool lds = e >= 0 && !big;
-            any_big |= big;
-            const uint32_t sh = (uint32_t)(e & 7) * 4u;
-            old[4 * q + i] = atomicSub(&nib[lds ? e >> 3 : dummy], lds ? (1u << sh) : 0u);
-          }
-        }
-#pragma unroll
-        for (int q = 0; q < NCH; ++q) {
-          if (q >= nq) break;
-          const int xs[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int e = xs[i];
-            const uint32_t sh = (uint32_t)(e & 7) * 4u;
-            const bool ready = e >= 0 && (e & kBigFlag) == 0 && ((old[4 * q + i] >> sh) & 15u) == 1u;
-            wm |= (uint32_t)ready << (4 * q + i);
-          }
-        }
-        if (__ballot(any_big) != 0ull) {
-#pragma unroll
-          for (int q = 0; q < NCH; ++q) {
-            if (q >= nq) break;
-            const int xs[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (xs[i] >= 0 && (xs[i] & kBigFlag) != 0)
-                wm |= (uint32_t)dec_global(xs[i] & ~kBigFlag) << (4 * q + i);
-          }
+        for (int i = 0; i < N; ++i) {
+          frn[ready[i] ? base + rank_in(m[i]) : dummy] = xs[i] & ~kBigFlag;
+          base += __popcll(m[i]);
         }
       } else {
-        // counters in global memory: every real entry of the wavefront's
-        // non-empty chunks issues its atomic before the first result is used;
-        // padding lanes issue none (the memory system is the bottleneck here:
-        // an atomic on a shared dummy word costs as much as a real one)
-        int nq = 0;
 #pragma unroll
-        for (int q = 0; q < NCH; ++q) nq += __ballot(v[q].x >= 0) != 0ull ? 1 : 0;
-        uint32_t old[4 * NCH];
+        for (int i = 0; i < N; ++i) {
+          const int q = base + rank_in(m[i]);
+          if (ready[i] && q < kFrontierCap) frn[q] = xs[i] & ~kBigFlag;
+          if (ready[i] && q >= kFrontierCap) spill[tail + q] = xs[i] & ~kBigFlag;
+          base += __popcll(m[i]);
+        }
+      }
+    };
+    auto process = [&](const int4& v, bool last_chunk) {
+      const int xs[4] = {v.x, v.y, v.z, v.w};
+      bool ready[4];
+      if (LDS) {
+        // every entry issues one LDS decrement without a branch (padding: a zero from
+        // the lane's private dummy word); flagged entries are decremented in global
+        // memory instead
+        uint32_t old[4];
+        const bool big = max(max(v.x, v.y), max(v.z, v.w)) >= kBigFlag;
+        const bool any_big = MODE == kKahnLds4 && __ballot(big) != 0ull;
 #pragma unroll
-        for (int q = 0; q < NCH; ++q) {
-          if (q >= nq) break;
-          const int xs[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int nb = xs[i] & ~kBigFlag;
-            const uint32_t sh = (uint32_t)(nb & 3) * 8u;
-            old[4 * q + i] = xs[i] >= 0 ? __hip_atomic_fetch_add(cntw + (nb >> 2), 0u - (1u << sh),
-                                                                 __ATOMIC_RELAXED,
-                                                                 __HIP_MEMORY_SCOPE_WORKGROUP)
-                                        : 0u;
-          }
+        for (int i = 0; i < 4; ++i) {
+          const int e = xs[i];
+          const bool lds = e >= 0 && !(any_big && e >= kBigFlag);
+          old[i] = atomicSub(&tab[lds ? e >> LPW : nwords + lane], lds ? 1u << ((e * B) & 31) : 0u);
         }
 #pragma unroll
-        for (int q = 0; q < NCH; ++q) {
-          if (q >= nq) break;
-          const int xs[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+        for (int i = 0; i < 4; ++i) ready[i] = ((old[i] >> ((xs[i] * B) & 31)) & M) == 1u;  // (padding: 0)
+        if (any_big) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (xs[i] >= kBigFlag) ready[i] = dec_global(xs[i] & ~kBigFlag);
+        }
+      } else if (MODE == kKahnGlobal) {
+        uint32_t old[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t s8 = (uint32_t)(xs[i] & 3) * 8u;
+          old[i] = xs[i] >= 0 ? __hip_atomic_fetch_add(cntw + (xs[i] >> 2), 0u - (1u << s8), __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_WORKGROUP)
+                              : 0u;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          ready[i] = xs[i] >= 0 && ((old[i] >> ((uint32_t)(xs[i] & 3) * 8u)) & 255u) == 1u;
+      } else {
+        // entries in the table are decremented, the others listed
+        uint32_t bk[4];
+        uint2 w[4];
+        int at[4];
+        bool miss[4];
+        uint32_t old[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          bk[i] = bucket_of(max(xs[i], 0));
+          w[i] = *reinterpret_cast<const uint2*>(tab + bk[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          at[i] = zero_byte(w[i].x ^ tags_of(max(xs[i], 0)));
+          const bool hit = xs[i] >= 0 && at[i] >= 0;
+          miss[i] = xs[i] >= 0 && at[i] < 0;
+          // (lanes without a hit: their own dummy word; one address would serialise them)
+          old[i] = atomicSub(&tab[hit ? bk[i] + 1 : (2u << hbits) + lane], hit ? 1u << (at[i] & 31) : 0u);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ready[i] = ((old[i] >> (at[i] & 31)) & 255u) == 1u;  // (no hit: 0)
+        unsigned long long m[4];
+        int total = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          m[i] = __ballot(miss[i]);
+          total += __popcll(m[i]);
+        }
+        if (total > 0) {
+          int base = 0;
+          if (lane == 0) base = atomicAdd(s_miss, total);
+          base = __builtin_amdgcn_readfirstlane(base);
+          const bool fits = base + total <= kMissCap;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const uint32_t sh = (uint32_t)(xs[i] & 3) * 8u;
-            wm |= (uint32_t)(xs[i] >= 0 && ((old[4 * q + i] >> sh) & 255u) == 1u) << (4 * q + i);
+            const int q = base + rank_in(m[i]);
+            misses[miss[i] && q < kMissCap ? q : kMissCap + lane] = xs[i];
+            base += __popcll(m[i]);
+          }
+          if (!fits) {  // past the list: at once
+            base -= total;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              if (miss[i] && base + rank_in(m[i]) >= kMissCap) ready[i] = dec_new(xs[i]);
+              base += __popcll(m[i]);
+            }
           }
         }
       }
       // a full row may end in a pointer to its overflow list (rare): one
       // wavefront push per extra entry
-      int ptr = -1;
-#pragma unroll
-      for (int q = 0; q < NCH; ++q) ptr = q == Wr4 - 1 ? v[q].w : ptr;
+      const int ptr = last_chunk ? v.w : -1;
       if (__ballot(ptr < -1) != 0ull) {
         const int o = ptr < -1 ? -(ptr + 2) : 0;
         const int no = ptr < -1 ? a.dn_ovf[o] : 0;
         int mx = no;
 #pragma unroll
-        for (int sh = 1; sh < 64; sh <<= 1) mx = max(mx, __shfl_xor(mx, sh));
+        for (int s = 1; s < 64; s <<= 1) mx = max(mx, __shfl_xor(mx, s));
         for (int i = 0; i < mx; ++i) {
           const int e = i < no ? a.dn_ovf[o + 1 + i] : -1;
-          const int nb = e >= 0 ? e & ~kBigFlag : -1;
-          bool ready = false;
-          if (nb >= 0) {
-            const uint32_t sh = (uint32_t)(nb & 7) * 4u;
-            if (LDSCNT && (e & kBigFlag) == 0) {
-              const uint32_t old = atomicSub(&nib[nb >> 3], 1u << sh);
-              ready = ((old >> sh) & 15u) == 1u;
-            } else {
-              ready = dec_global(nb);
-            }
-          }
-          const unsigned long long m = __ballot(ready);
-          if (m != 0ull) {
-            const int leader = __ffsll((long long)m) - 1;
-            int base = 0;
-            if (lane == leader) base = atomicAdd(s_push, __popcll(m));
-            base = __shfl(base, leader);
-            if (ready) {
-              const int r = base + __popcll(m & ((1ull << lane) - 1ull));
-              if (r < kFrontierCap) frn[r] = nb;
-              else spill[tail + r] = nb;
-            }
-          }
+          const int one[4] = {e, -1, -1, -1};
+          const bool rdy[4] = {e >= 0 && dec_one(e), false, false, false};
+          push(rdy, one, std::integral_constant<int, 1>{});
         }
       }
-      // ready cells: one wavefront prefix sum and one LDS atomic per wavefront
-      const int n = __popc(wm);
-      const int incl = wave_inclusive_sum(n);
-      const int total = __builtin_amdgcn_readlane(incl, 63);
-      if (total > 0) {
-        int base = 0;
-        if (lane == 63) base = atomicAdd(s_push, total);
-        int r = __builtin_amdgcn_readlane(base, 63) + incl - n;
+      push(ready, xs, std::integral_constant<int, 4>{});
+    };
+    // two rows' worth of lanes in flight at a time
+    constexpr int kBatch = 2;
+    const int lanes = n << sh;
+    int4 v[kBatch];
+    if (!writer) {
 #pragma unroll
-        for (int q = 0; q < NCH; ++q) {
-          const int xs[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+      for (int b = 0; b < kBatch; ++b) v[b] = load(tid + b * nwork);
+    }
+    if (MODE == kKahnHash) {
+      // the frontier's cells leave the table (while the rows arrive)
+      if (!writer)
+        for (int i = tid; i < n; i += nwork) remove(cell_at(i));
+      __syncthreads();
+    }
+    if (!writer) {
+      const bool lc = (tid & ((1 << sh) - 1)) == (1 << sh) - 1;  // (nwork is a multiple of the lanes per row)
+      for (int i0 = 0; i0 < lanes; i0 += kBatch * nwork) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            if (wm & (1u << (4 * q + i))) {
-              const int cell = xs[i] & ~kBigFlag;
-              if (r < kFrontierCap) frn[r] = cell;
-              else spill[tail + r] = cell;
-              ++r;
-            }
-          }
+        for (int b = 0; b < kBatch; ++b) {
+          // a wavefront without a row in this batch has nothing to do
+          if (i0 + b * nwork + wfirst < lanes) process(v[b], lc);
+        }
+        if (i0 + kBatch * nwork < lanes) {
+#pragma unroll
+          for (int b = 0; b < kBatch; ++b) v[b] = load(i0 + (kBatch + b) * nwork + tid);
         }
       }
     }
     __syncthreads();
+    if (MODE == kKahnHash) {
+      const int nm = min(*s_miss, kMissCap);
+      if (!writer)
+        for (int i = tid, iw = wfirst; iw < nm; i += nwork, iw += nwork) {  // (whole wavefronts)
+          const int e = i < nm ? misses[i] : -1;
+          const int one[4] = {e, -1, -1, -1};
+          const bool rdy[4] = {e >= 0 && dec_new(e), false, false, false};
+          push(rdy, one, std::integral_constant<int, 1>{});
+        }
+      __syncthreads();
+    }
     head = tail;
     tail += s_cnt[l % 3];
     ++l;
@@ -1302,41 +1439,35 @@ hipError_t launch_count(const DagBuildArgs& a, int32_t n_cblocks, int32_t lds_li
   return hipGetLastError();
 }
 
-template <int NCH>
-hipError_t launch_kahn_n(const DagBuildArgs& a, size_t lds, hipStream_t s) {
-  hipError_t e = hipFuncSetAttribute((const void*)k_kahn<true, NCH>,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_kahn<true, NCH>), dim3(a.n_units), dim3(kKahnBlock(NCH)), lds, s, a);
-  return hipGetLastError();
-}
-
-template <int NCH>
-hipError_t launch_kahn_g(const DagBuildArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((k_kahn<false, NCH>), dim3(a.n_units), dim3(kKahnBlock(NCH)), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_kahn(const DagBuildArgs& a, bool lds_counters, int32_t max_cells, hipStream_t s) {
-  if (lds_counters) {
-    const size_t lds = sizeof(uint32_t) * (size_t)((max_cells + 7) / 8 + 64);
-    switch (a.dn_chunks) {
-      case 0: case 1: case 2: case 3: case 4: return launch_kahn_n<4>(a, lds, s);
-      case 5: return launch_kahn_n<5>(a, lds, s);
-      case 6: return launch_kahn_n<6>(a, lds, s);
-      case 7: return launch_kahn_n<7>(a, lds, s);
-      default: return launch_kahn_n<8>(a, lds, s);
+hipError_t launch_kahn(const DagBuildArgs& a, int32_t lds_bits, int32_t max_cells, hipStream_t s) {
+  auto launch = [&](auto kernel, size_t lds) {
+    if (lds > 0) {
+      const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               (int)lds);
+      if (e != hipSuccess) return e;
     }
-  }
-  switch (a.dn_chunks) {
-    case 0: case 1: case 2: case 3: case 4: return launch_kahn_g<4>(a, s);
-    default: return launch_kahn_g<8>(a, s);
-  }
+    hipLaunchKernelGGL(kernel, dim3(a.n_units), dim3(1024), lds, s, a);
+    return hipGetLastError();
+  };
+  if (lds_bits == 8) return launch(k_kahn<kKahnLds8>, kahn_lds_bytes(8, max_cells));
+  if (lds_bits == 4) return launch(k_kahn<kKahnLds4>, kahn_lds_bytes(4, max_cells));
+  if (a.hash_bits > 0) return launch(k_kahn<kKahnHash>, sizeof(uint32_t) * (((size_t)2 << a.hash_bits) + 64));
+  return launch(k_kahn<kKahnGlobal>, 0);
+}
+
+// log2 of k_kahn's hash buckets for meshes of up to max_cells cells whose tasks have
+// at most max_indeg dependencies: at least a bucket (four ways) per 128 cells, at
+// most 2^kHashBits.  0: the table cannot hold them (tags of one byte, and counts that
+// stay above 0 while they count down from the bias).
+int kahn_hash_bits(int32_t max_cells, int32_t max_indeg) {
+  int bits = 3;
+  while (bits < kHashBits && (max_cells >> bits) >= 128) ++bits;
+  return (max_cells >> bits) < 254 && max_indeg < (int)kHashBias - 4 ? bits : 0;
 }
 
 hipError_t launch_mark(const DagBuildArgs& a, int32_t n_big, hipStream_t s) {
   if (n_big <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_mark, dim3((n_big + 63) / 64), dim3(64), 0, s, a, n_big);
+  hipLaunchKernelGGL(k_mark, dim3((n_big + 3) / 4), dim3(256), 0, s, a, n_big);
   return hipGetLastError();
 }
 

@@ -77,8 +77,8 @@ struct DagBuildArgs {
   const int32_t* blk_base;  // [n_units+1] first block of each unit (cell-range kernels)
   const int32_t* cblk_mesh;  // cell-order kernels: mesh and first cell of every block
   const int32_t* cblk_c0;
-  int32_t dn_width;          // width of the fixed-width downwind rows (16 or 32)
-  int32_t dn_chunks;         // chunks of 4 row entries that may hold a downwind cell
+  int32_t dn_width;          // width of the fixed-width downwind rows (4, 8, 16 or 32)
+  int32_t hash_bits;         // Kahn's counters in an LDS hash table of 2^hash_bits buckets (0: not)
   int32_t* dn_ovf;           // overflow lists of full rows: [count, cells...]
   int32_t* dn_ovf_top;       // next free int of dn_ovf (atomic)
   int64_t dn_ovf_cap;        // ints of dn_ovf for lists (more: the pool has run out)
@@ -86,7 +86,6 @@ struct DagBuildArgs {
   int32_t* big_top;          // their number (atomic)
   int32_t max_faces;         // most half-faces of any cell
   int32_t* dnw;              // [T][dn_width] downwind cells of every task (-1 padded)
-  int64_t dn_sentinel;       // offset in dnw of a row of -1 (4 * kRowChunks entries)
   int32_t* stats;            // [0] max in-degree, [1] max out-degree (atomic max)
   unsigned long long* ent_tot;  // [0] upwind-row entries, [1] downwind-row entries (all tasks)
   // per task, cell order within the unit (the upwind row's length is indeg)
@@ -287,7 +286,11 @@ hipError_t launch_ion_update(const IonArgs& a, double dt, hipStream_t s);
 constexpr int kTileCellsHost = 32;  // cells per tile of the cell-order build kernels
 hipError_t launch_count(const DagBuildArgs& a, int32_t n_cblocks, int32_t lds_limit, hipStream_t s);
 constexpr int kMaxAligned = 4;  // most faces scheme (b) may share the outflow over
-hipError_t launch_kahn(const DagBuildArgs& a, bool lds_counters, int32_t max_cells, hipStream_t s);
+int kahn_hash_bits(int32_t max_cells, int32_t max_indeg);
+// Dynamic LDS of k_kahn with a counter of `bits` bits per cell (and 64 dummy words).
+constexpr size_t kahn_lds_bytes(int bits, int64_t cells) { return 4 * (size_t)((cells * bits + 31) / 32 + 64); }
+// lds_bits: bits of the counters in LDS (8 or 4), 0: in a hash table or in global memory
+hipError_t launch_kahn(const DagBuildArgs& a, int32_t lds_bits, int32_t max_cells, hipStream_t s);
 hipError_t launch_fill(const DagBuildArgs& a, hipStream_t s);
 // out[0] = max faces of a cell, out[1] += overflow ints for rows of row_cap entries
 hipError_t launch_face_stats(const int64_t* face_ptr, int32_t n_cells, int32_t row_cap, int32_t n_dirs,
