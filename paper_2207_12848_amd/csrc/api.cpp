@@ -281,6 +281,7 @@ namespace {
 
 bool dag_ok(sweep_dag_t d) { return d != nullptr && d->T > 0; }
 
+// The check of one mesh in host memory, which words what is wrong.
 sweep_status_t validate_mesh_host(const sweep_mesh_t& m, int idx) {
   const int32_t C = m.n_cells;
   const int64_t F = m.n_half_faces;
@@ -339,6 +340,36 @@ sweep_status_t validate_mesh_host(const sweep_mesh_t& m, int idx) {
                     idx, (long long)f, (long long)t);
     }
   }
+  return SWEEP_OK;
+}
+
+sweep::MeshDev mesh_dev(const sweep_mesh_t& m) {
+  sweep::MeshDev d{};
+  d.face_ptr = m.face_ptr;
+  d.face_twin = m.face_twin;
+  d.face_nbr = m.face_nbr;
+  d.face_shift = m.face_shift;
+  d.face_area = m.face_area;
+  d.face_normal = m.face_normal;
+  d.cell_volume = m.cell_volume;
+  d.n_faces = m.n_half_faces;
+  d.n_cells = m.n_cells;
+  return d;
+}
+
+// Checks meshes [0, n) on the device; a mesh that may be wrong is checked again on the
+// host, which finds and words the error.
+sweep_status_t validate_meshes(const sweep_mesh_t* meshes, int n, hipStream_t s) {
+  if (n <= 0) return SWEEP_OK;
+  Buf bad;
+  HIP_TRY(bad.alloc(4 * (size_t)n));
+  HIP_TRY(sweep::launch_fill_i32(bad.as<int32_t>(), n, 0, s));
+  for (int m = 0; m < n; ++m) HIP_TRY(sweep::launch_check_mesh(mesh_dev(meshes[m]), bad.as<int32_t>() + m, s));
+  std::vector<int32_t> b(n);
+  HIP_TRY(hipMemcpyAsync(b.data(), bad.p, 4 * (size_t)n, hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipStreamSynchronize(s));
+  for (int m = 0; m < n; ++m)
+    if (b[m] != 0) ST_TRY(validate_mesh_host(meshes[m], m));
   return SWEEP_OK;
 }
 
@@ -812,18 +843,26 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   int64_t off = 0;
   for (int m = 0; m < n_meshes; ++m) {
     const sweep_mesh_t& M = meshes[m];
+    // (an invalid mesh before this one is reported first)
     if (M.n_cells < 1 || M.n_half_faces < 1 || !M.face_ptr || !M.cell_volume || !M.face_nbr ||
-        !M.face_area || !M.face_normal)
+        !M.face_area || !M.face_normal) {
+      if (validate) ST_TRY(validate_meshes(meshes, m, s));
       return fail(SWEEP_ERR_INVALID_ARG, "mesh %d: missing arrays, no cells or no faces", m);
-    if (scheme == SWEEP_SCHEME_ALIGNED && !M.face_twin)
+    }
+    if (scheme == SWEEP_SCHEME_ALIGNED && !M.face_twin) {
+      if (validate) ST_TRY(validate_meshes(meshes, m, s));
       return fail(SWEEP_ERR_INVALID_ARG, "mesh %d: the aligned transport scheme needs face_twin", m);
-    if (validate) ST_TRY(validate_mesh_host(M, m));
+    }
     D->mesh_off.push_back((int32_t)off);
     D->mesh_cells.push_back(M.n_cells);
     if (M.face_shift) D->has_shift = true;
     off += M.n_cells;
-    if (off > INT32_MAX / 2) return fail(SWEEP_ERR_INVALID_ARG, "too many cells");
+    if (off > INT32_MAX / 2) {
+      if (validate) ST_TRY(validate_meshes(meshes, m + 1, s));
+      return fail(SWEEP_ERR_INVALID_ARG, "too many cells");
+    }
   }
+  if (validate) ST_TRY(validate_meshes(meshes, n_meshes, s));
   D->mesh_off.push_back((int32_t)off);
   D->C_total = off;
   D->T = off * n_dirs;
@@ -896,15 +935,7 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
     return fail(SWEEP_ERR_UNSUPPORTED, "too many cells with more than %d faces", kRowCap);
   std::vector<sweep::MeshDev> md(n_meshes);
   for (int m = 0; m < n_meshes; ++m) {
-    md[m].face_ptr = meshes[m].face_ptr;
-    md[m].face_twin = meshes[m].face_twin;
-    md[m].face_nbr = meshes[m].face_nbr;
-    md[m].face_shift = meshes[m].face_shift;
-    md[m].face_area = meshes[m].face_area;
-    md[m].face_normal = meshes[m].face_normal;
-    md[m].cell_volume = meshes[m].cell_volume;
-    md[m].n_faces = meshes[m].n_half_faces;
-    md[m].n_cells = meshes[m].n_cells;
+    md[m] = mesh_dev(meshes[m]);
     md[m].cell_off = D->mesh_off[m];
   }
   // per-face neighbour codes and per-(direction, face) signed weights for the row fill

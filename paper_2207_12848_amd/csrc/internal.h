@@ -295,6 +295,8 @@ hipError_t launch_fill(const DagBuildArgs& a, hipStream_t s);
 // out[0] = max faces of a cell, out[1] += overflow ints for rows of row_cap entries
 hipError_t launch_face_stats(const int64_t* face_ptr, int32_t n_cells, int32_t row_cap, int32_t n_dirs,
                              unsigned long long* out, hipStream_t s);
+// *bad is set if the mesh may violate a condition of the host's check
+hipError_t launch_check_mesh(const MeshDev& m, int32_t* bad, hipStream_t s);
 hipError_t launch_face_codes(const MeshDev& m, int32_t* fcode, hipStream_t s);
 // Sorts every level of the schedule by cell id and writes the inverse schedule.
 hipError_t launch_sort_levels(const DagBuildArgs& a, hipStream_t s);
