@@ -942,8 +942,9 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   int64_t n_faces_total = 0;
   for (int m = 0; m < n_meshes; ++m) n_faces_total += meshes[m].n_half_faces;
   Buf fcode, wface;
-  HIP_TRY(fcode.alloc(4 * n_faces_total));
-  HIP_TRY(wface.alloc(4 * (size_t)n_faces_total * n_dirs));
+  // (k_fill reads both four faces at a time, from any face on)
+  HIP_TRY(fcode.alloc(4 * n_faces_total + 16));
+  HIP_TRY(wface.alloc(4 * (size_t)n_faces_total * n_dirs + 16));
   {
     int64_t fo = 0;
     for (int m = 0; m < n_meshes; ++m) {
@@ -1110,6 +1111,9 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   a.sl_up = D->sl_up.as<sweep::SliceRec>();
   a.sl_dn = D->sl_dn.as<sweep::SliceRec>();
   a.np_up = np_up.as<int32_t>();
+  double mean_faces = 1.0;
+  for (const auto& m : md) mean_faces = std::max(mean_faces, (double)m.n_faces / m.n_cells);
+  a.fill_faces = sweep::fill_faces(mean_faces, max_faces);
   a.np_dn = np_dn.as<int32_t>();
   a.pb_up = pb_up.as<int64_t>();
   a.pb_dn = pb_dn.as<int64_t>();

@@ -1187,30 +1187,42 @@ __global__ __launch_bounds__(256) void k_unit_entries(const Unit* units, const i
 // byte offset of a ring slot.  Rows keep the cell's face order.
 //
 // One wavefront per slice.  Every lane first loads one task (cell, row lengths,
-// face range); then, 16 tasks per round, 16 lanes share one task, one face per
-// lane, 16 faces at a time.  Each face's neighbour code and signed weight (from
-// k_count) give its class, a ballot over the 16 lanes its entry number in the
-// row, and the columns' lane masks (LDS) its place.  All the stores of a slice
-// fall into its few KB.
+// face range); then four lanes share one task, four faces per lane and 16 tasks
+// at a time, and the wavefront assembles the rows of 32 tasks in LDS: entry e of
+// the upwind row of task t at [e][t], entry e of its downwind row at [K - 1 - e][t]
+// (slices with a cell of more faces than that holds: 16 tasks at a time).  Each
+// face's neighbour code and signed weight (from k_count) give its class, a sum over
+// the four lanes its entry number.  The columns are then read from LDS with one task
+// and side per lane and stored in whole cache lines; entries stored one by one from
+// where their face was looked at cost a line request each.
+//
+// Bound by the requests that the L1 keeps in flight: about 28 per task, of which 15
+// find the neighbours' positions (2.2 TB/s).  64^3 cells, 84 directions: 2.18 ms, and
+// 3.25 with 16 lanes per task and stores of single entries; 2 M cells: 19.8 ms, and
+// 29.1.
 constexpr int kFillBlock = 256;
-constexpr int kFillCols = 32;  // pair columns with a mask in LDS (longer rows: a second look at their faces)
+constexpr int kFillTasks = 32;  // tasks assembled in LDS at a time
+constexpr int kFillFaces = 96;  // entries per task in LDS at most
 
-// Five wavefronts per SIMD: the register budget (at most 102 VGPRs) still
-// compiles without spills.
+// Value of lane L of the lane's group of four.
+template <int L>
+__device__ __forceinline__ int quad_lane(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, L * 0x55, 0xf, 0xf, true);  // quad_perm [L, L, L, L]
+}
+
 template <bool ALIGNED>
 __global__ __launch_bounds__(kFillBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_fill(DagBuildArgs a) {
-  __shared__ unsigned long long s_mask[kFillBlock / 64][2][kFillCols];
-  __shared__ int s_col[kFillBlock / 64][2][kFillCols];
+  extern __shared__ __align__(16) unsigned char smem[];
   const int wv = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
+  const int room = a.fill_faces * (kFillTasks + 1);  // entries of a wavefront's LDS
+  int2* const s_ent = reinterpret_cast<int2*>(smem) + wv * room;
   const int64_t sl = (int64_t)xcd_block(blockIdx.x, gridDim.x) * (kFillBlock / 64) + wv;
   if (sl >= a.n_slices) return;  // (wavefronts share nothing here: no barrier below)
   const Unit U = a.units[unit_of_slice(a.slice_base, a.n_units, sl)];
   const MeshDev M = a.meshes[U.mesh];
   const int64_t tb = U.task_base;
   const int C = U.n_cells;
-  const int li = lane & 15;
-  const int g = lane >> 4;
   const int32_t* inv = a.inv + tb;
   const float* wf = a.wface + (int64_t)a.D * M.face_off + (int64_t)U.dir * M.n_faces;
   const int k0 = a.sl_up[sl].k0, cnt = a.sl_up[sl].cnt;
@@ -1221,20 +1233,6 @@ __global__ __launch_bounds__(kFillBlock) __attribute__((amdgpu_waves_per_eu(5)))
   const int nd = act ? a.len_dn[tb + k0 + lane] : 0;
   const int64_t f0 = M.face_ptr[c];
   const int nf = act ? (int)(M.face_ptr[c + 1] - f0) : 0;
-  int tot[2] = {0, 0};  // pairs of the columns so far
-  auto columns = [&](int side, int n) {
-    for (int j = 0; j < kFillCols; ++j) {
-      const unsigned long long m = __ballot(n > 2 * j);
-      if (m == 0ull) break;
-      if (lane == 0) {
-        s_mask[wv][side][j] = m;
-        s_col[wv][side][j] = tot[side];
-      }
-      tot[side] += __popcll(m);
-    }
-  };
-  columns(0, nu);
-  columns(1, nd);
   if (lane == 0) {
     SliceRec& ru = a.sl_up[sl];
     ru.base_lo = (uint32_t)bu;
@@ -1245,110 +1243,143 @@ __global__ __launch_bounds__(kFillBlock) __attribute__((amdgpu_waves_per_eu(5)))
     rd.base_hi = (uint32_t)((uint64_t)bd >> 32);
     rd.np = (int)(a.pb_dn[sl + 1] - bd);
   }
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the masks, to the wavefront's other lanes
-  // entry e of a row of n entries whose pair is `pair`; the last entry of an odd
-  // row also writes the empty half
-  auto put = [&](int4* pair, int e, int n, int x, float w) {
-    if ((e & 1) == 0 && e == n - 1) {
-      *pair = make_int4(x, __float_as_int(w), x, 0);
-    } else {
-      reinterpret_cast<int2*>(pair)[e & 1] = make_int2(x, __float_as_int(w));
-    }
-  };
-  // class, weight and neighbour of one face: code >= 0 is an interior neighbour
-  auto face = [&](int64_t f, bool has, int& code, bool& up, bool& dn, float& wu, float& wd) {
-    code = M.fcode[f];
-    const float ws = wf[f];
+  // class and weight of a face with neighbour code `code` (>= 0: an interior neighbour)
+  // and signed weight ws
+  auto classify = [&](int64_t f, bool has, int code, float ws, bool& up, bool& dn, float& w) {
+    has = has && code >= 0;
     if (ALIGNED) {
       // radiation leaves through the faces the cell chose and enters through the
       // faces whose twin the neighbour chose
-      const float wi = wf[code != -1 ? M.face_twin[f] : f];
-      up = has && code >= 0 && !isnan(wi);
-      dn = has && code >= 0 && !isnan(ws);
-      wd = ws;
-      wu = wi;
+      const float wi = wf[has ? M.face_twin[f] : 0];
+      up = has && !isnan(wi);
+      dn = has && !isnan(ws);
+      w = up ? wi : ws;
     } else {
-      const bool carries = has && !isnan(ws);
-      const bool in = carries && signbit(ws);
-      up = in && code >= 0;               // interior inflow
-      dn = carries && !in && code >= 0;   // interior outflow
-      wd = wu = fabsf(ws);
+      has = has && !isnan(ws);
+      up = has && signbit(ws);   // interior inflow
+      dn = has && !signbit(ws);  // interior outflow
+      w = fabsf(ws);
     }
   };
-  const uint32_t below = (1u << li) - 1u;
-  const int rounds = (cnt + 15) >> 4;
-  for (int r = 0; r < rounds; ++r) {
-    // group g handles tasks 16 r + 4 g + j of the slice, j = 0..3
-    int eu[4], ed[4], lu[4], ld[4], nfj[4];
-    int64_t fb[4];
+  // faces f..f + 3, of which the first m are the cell's (what lies behind them is readable)
+  auto faces = [&](int64_t f, int m, int (&code)[4], bool (&up)[4], bool (&dn)[4], float (&w)[4]) {
+    struct __attribute__((packed, aligned(4))) Four {
+      int x[4];
+    };
+    const Four c4 = *reinterpret_cast<const Four*>(M.fcode + f);
+    const Four w4 = *reinterpret_cast<const Four*>(wf + f);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int src = 16 * r + 4 * g + j;
-      eu[j] = ed[j] = 0;
-      lu[j] = __shfl(nu, src);
-      ld[j] = __shfl(nd, src);
-      fb[j] = __shfl(f0, src);
-      nfj[j] = __shfl(nf, src);
+    for (int k = 0; k < 4; ++k) {
+      code[k] = c4.x[k];
+      classify(f + k, k < m, code[k], __int_as_float(w4.x[k]), up[k], dn[k], w[k]);
     }
-    int mx = max(max(nfj[0], nfj[1]), max(nfj[2], nfj[3]));
-    mx = max(mx, __shfl_xor(mx, 16));
-    mx = max(mx, __shfl_xor(mx, 32));
-    for (int h = 0; h * 16 < mx; ++h) {
-      const int fo = h * 16 + li;
-      int code[4];
-      bool up[4], dn[4];
-      float wu[4], wd[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        face(fo < nfj[j] ? fb[j] + fo : 0, fo < nfj[j], code[j], up[j], dn[j], wu[j], wd[j]);  // face 0 exists
-      int pos[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) pos[j] = inv[code[j] >= 0 ? code[j] : 0];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int src = 16 * r + 4 * g + j;
-        const uint32_t mu = (uint32_t)(__ballot(up[j]) >> (16 * g)) & 0xffffu;
-        const uint32_t md = (uint32_t)(__ballot(dn[j]) >> (16 * g)) & 0xffffu;
-        if (up[j] || dn[j]) {
-          const int side = up[j] ? 0 : 1;
-          const int e = up[j] ? eu[j] + __popc(mu & below) : ed[j] + __popc(md & below);
-          const int col = e >> 1;
-          if (col < kFillCols) {
-            const int at = s_col[wv][side][col] + __popcll(s_mask[wv][side][col] & ((1ull << src) - 1ull));
-            if (up[j]) put(a.up + bu + at, e, lu[j], 4 * (pos[j] + 1), wu[j]);
-            else put(a.dn + bd + at, e, ld[j], 4 * (C - pos[j]), wd[j]);
+  };
+  // entry of a neighbour at schedule position p, upwind or downwind
+  auto code_of = [&](bool up, int p) { return up ? 4 * p + 4 : 4 * C - 4 * p; };
+  // tasks at a time, the stride of the entry numbers (odd: 16 lanes of one task fall on
+  // 16 banks) and the entries per task
+  const int tasks = __any(nf > a.fill_faces) ? kFillTasks / 2 : kFillTasks;
+  const int stride = tasks + 1;
+  const int K = tasks == kFillTasks ? a.fill_faces : room / stride;
+  if (__any(nf > K)) {
+    // each lane looks through its own task's faces, two entries per column
+    for (int side = 0; side < 2; ++side) {
+      const int n = side == 0 ? nu : nd;
+      int4* out = side == 0 ? a.up + bu : a.dn + bd;
+      int q = 0;
+      for (int j = 0;; ++j) {
+        const unsigned long long m = __ballot(n > 2 * j);
+        if (m == 0ull) break;
+        if (n > 2 * j) {
+          int4 pair = make_int4(0, 0, 0, 0);
+          for (int k = 0; q < nf && k < 2; ++q) {
+            const int code = M.fcode[f0 + q];
+            bool up, dn;
+            float w;
+            classify(f0 + q, true, code, wf[f0 + q], up, dn, w);
+            if (!(side == 0 ? up : dn)) continue;
+            pair.z = code_of(up, inv[code]);
+            pair.w = k == 0 ? 0 : __float_as_int(w);
+            if (k++ == 0) {
+              pair.x = pair.z;
+              pair.y = __float_as_int(w);
+            }
           }
+          out[__popcll(m & ((1ull << lane) - 1ull))] = pair;
         }
-        eu[j] += __popc(mu);
-        ed[j] += __popc(md);
+        out += __popcll(m);
       }
     }
+    return;
   }
-  // rows longer than the columns held in LDS: column by column, each lane looks
-  // through its own task's faces for the two entries
-  for (int side = 0; side < 2; ++side) {
-    const int n = side == 0 ? nu : nd;
-    for (int j = kFillCols;; ++j) {
-      const unsigned long long m = __ballot(n > 2 * j);
-      if (m == 0ull) break;
-      const int64_t at = tot[side] + __popcll(m & ((1ull << lane) - 1ull));
-      tot[side] += __popcll(m);
-      if (n > 2 * j) {
-        int e = 0;
-        for (int q = 0; q < nf; ++q) {
-          int code;
-          bool up, dn;
-          float wu, wd;
-          face(f0 + q, true, code, up, dn, wu, wd);
-          if (!(side == 0 ? up : dn)) continue;
-          if ((e >> 1) == j) {
-            if (side == 0) put(a.up + bu + at, e, n, 4 * (inv[code] + 1), wu);
-            else put(a.dn + bd + at, e, n, 4 * (C - inv[code]), wd);
+  const int q = lane & 3;
+  const int before[3] = {q > 0 ? -1 : 0, q > 1 ? -1 : 0, q > 2 ? -1 : 0};  // masks of the task's lanes below this one
+  for (int t0 = 0; t0 < cnt; t0 += tasks) {
+#pragma unroll 1
+    for (int tl = lane >> 2; tl < tasks; tl += 16) {
+      const int64_t fb = __shfl(f0, t0 + tl);
+      const int nft = __shfl(nf, t0 + tl);
+      int mx = nft;
+      for (int o = 4; o < 64; o <<= 1) mx = max(mx, __shfl_xor(mx, o));
+      mx = __builtin_amdgcn_readfirstlane(mx);
+      int eu = tl, ed = (K - 1) * stride + tl;  // places of the rows' next entries
+      for (int h = 0; h < mx; h += 16) {
+        const int64_t f = fb + h + 4 * q;
+        const int m = nft - h - 4 * q;  // faces of this lane
+        int code[4], pos[4];
+        bool up[4], dn[4];
+        float w[4];
+        int n = 0;  // upwind entries, downwind entries << 16
+        if (m > 0) {
+          faces(f, m, code, up, dn, w);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            pos[k] = inv[up[k] || dn[k] ? code[k] : 0];
+            n += (up[k] ? 1 : 0) + (dn[k] ? 1 << 16 : 0);
           }
-          ++e;
         }
+        const int n0 = quad_lane<0>(n), n1 = quad_lane<1>(n), n2 = quad_lane<2>(n), n3 = quad_lane<3>(n);
+        const int p = (n0 & before[0]) + (n1 & before[1]) + (n2 & before[2]);
+        if (m > 0) {
+          int xu = eu + stride * (p & 0xffff), xd = ed - stride * (p >> 16);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            if (up[k] || dn[k])
+              s_ent[up[k] ? xu : xd] = make_int2(code_of(up[k], pos[k]), __float_as_int(w[k]));
+            xu += up[k] ? stride : 0;
+            xd -= dn[k] ? stride : 0;
+          }
+        }
+        const int all = n0 + n1 + n2 + n3;
+        eu += stride * (all & 0xffff);
+        ed -= stride * (all >> 16);
       }
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the entries, to the wavefront's other lanes
+    // lanes 0..31: the upwind rows' columns, lanes 32..63: the downwind rows'
+    const bool mine = (lane & 31) < tasks;
+    const int t = mine ? t0 + (lane & 31) : 0;
+    const bool dside = lane >= 32;
+    const int xu = __shfl(nu, t), xd = __shfl(nd, t);
+    const int n = mine ? (dside ? xd : xu) : 0;
+    const unsigned long long low = (1ull << t) - 1ull;
+    int4* out = dside ? a.dn + bd : a.up + bu;
+    const int2* row = s_ent + (dside ? (K - 1) * stride : 0) + (lane & 31);
+    const int step = dside ? -stride : stride;
+    for (int j = 0;; ++j) {
+      const unsigned long long mu = __ballot(nu > 2 * j), md = __ballot(nd > 2 * j);
+      if ((mu | md) == 0ull) break;
+      if (n > 2 * j) {
+        const int2 x = row[2 * j * step];
+        const bool odd = n == 2 * j + 1;
+        const int2 y = row[(odd ? 2 * j : 2 * j + 1) * step];
+        typedef int v4 __attribute__((ext_vector_type(4)));
+        const v4 pair = {x.x, x.y, y.x, odd ? 0 : y.y};
+        __builtin_nontemporal_store(pair, reinterpret_cast<v4*>(out) + __popcll((dside ? md : mu) & low));
+      }
+      out += dside ? __popcll(md) : __popcll(mu);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // read before the next tasks' entries
   }
 }
 
@@ -1535,9 +1566,19 @@ hipError_t launch_gather_tasks(const DagBuildArgs& a, hipStream_t s) {
 hipError_t launch_fill(const DagBuildArgs& a, hipStream_t s) {
   if (a.n_slices <= 0) return hipSuccess;
   const dim3 grid(grid1d(a.n_slices, kFillBlock / 64));
-  if (a.scheme == SWEEP_SCHEME_ALIGNED) hipLaunchKernelGGL(k_fill<true>, grid, dim3(kFillBlock), 0, s, a);
-  else hipLaunchKernelGGL(k_fill<false>, grid, dim3(kFillBlock), 0, s, a);
+  size_t lds = kFillBlock / 64 * sizeof(int2) * (size_t)a.fill_faces * (kFillTasks + 1);
+  
+  auto kernel = a.scheme == SWEEP_SCHEME_ALIGNED ? k_fill<true> : k_fill<false>;
+  const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kernel, grid, dim3(kFillBlock), lds, s, a);
   return hipGetLastError();
+}
+
+// Entries per task that k_fill holds in LDS (one per face) for meshes of mean_faces faces
+// per cell on average and max_faces at most.
+int fill_faces(double mean_faces, int64_t max_faces) {
+  return (int)std::max(1.0, std::min({std::ceil(1.9 * mean_faces), (double)max_faces, (double)kFillFaces}));
 }
 
 hipError_t launch_pcount(const DagBuildArgs& a, const MeshDev& m, hipStream_t s) {

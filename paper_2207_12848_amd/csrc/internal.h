@@ -134,6 +134,7 @@ struct DagBuildArgs {
   int32_t* np_dn;
   const int64_t* pb_up;       // [n_slices + 1] first entry pair of every slice
   const int64_t* pb_dn;
+  int32_t fill_faces;         // entries per task that k_fill holds in LDS
   // entry pairs (position code, w, position code, w), see k_fill
   int4* up;
   int4* dn;
@@ -292,6 +293,7 @@ constexpr size_t kahn_lds_bytes(int bits, int64_t cells) { return 4 * (size_t)((
 // lds_bits: bits of the counters in LDS (8 or 4), 0: in a hash table or in global memory
 hipError_t launch_kahn(const DagBuildArgs& a, int32_t lds_bits, int32_t max_cells, hipStream_t s);
 hipError_t launch_fill(const DagBuildArgs& a, hipStream_t s);
+int fill_faces(double mean_faces, int64_t max_faces);
 // out[0] = max faces of a cell, out[1] += overflow ints for rows of row_cap entries
 hipError_t launch_face_stats(const int64_t* face_ptr, int32_t n_cells, int32_t row_cap, int32_t n_dirs,
                              unsigned long long* out, hipStream_t s);
