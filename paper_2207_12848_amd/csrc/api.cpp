@@ -222,7 +222,7 @@ struct ProfScope {
   }
 };
 
-constexpr int kRedBlock = 256;
+constexpr int kRedBlock = 256;  // items of a reduction's workgroup (k_reduce)
 constexpr int kNPart = 9;
 constexpr int kMaxG = 64;
 constexpr int kMaxLds = 160 * 1024;
@@ -243,7 +243,7 @@ struct sweep_dag_s {
   std::vector<int32_t> order;  // units, deepest first
   std::vector<int32_t> identity;
   Buf units_d, order_d, identity_d, sched, inv, indeg, lp, len_up, len_dn, up, dn, slice_base, sl_up, sl_dn,
-      aperp, aperp_s, vol_s, bnd, vol, counter, blk_base;
+      aperp, aperp_s, vol_s, bnd, edge, vol, counter, blk_base;
   int64_t n_slices = 0;  // slices of the sweep over all units (sweep::SliceRec)
   int32_t n_blocks = 0;  // 256-task blocks over all units (prep kernel)
   int32_t max_depth = 0;
@@ -537,12 +537,19 @@ sweep_status_t run_prep(sweep_dag_t d, int32_t G, const float* kappa, const floa
   return SWEEP_OK;
 }
 
+// Whether the reductions take a sweep's results straight from schedule order.  They go
+// through the directions side by side, so the L2 holds the lines that neighbouring cells
+// share only while a direction's results are small against it (4 MB per XCD); the copy to
+// cell order works direction by direction.  Copy and sums of 64^3 cells x 84 directions
+// (1 MB per direction): 122 us straight, 134 with the copy; 128^3 (8 MB), exponential
+// law: 2.5 and 1.9 ms.
+bool reduce_direct(sweep_dag_t d, int32_t G) { return (int64_t)d->max_cells * G * 4 <= (4 << 20); }
+
 // The direction reduction's arguments that do not change between the passes of
 // a call (the reduction tables must be in place: ensure_reduce_tables).
 sweep::ReduceArgs reduce_args(sweep_dag_t d, int32_t G, const FwdPlan& p, const float* kappa,
                               const float* emission, float* J, float* absorbed) {
   sweep::ReduceArgs r{};
-  r.units = d->units_d.as<Unit>();
   r.D = d->D;
   r.G = G;
   r.C_total = d->C_total;
@@ -550,7 +557,10 @@ sweep::ReduceArgs reduce_args(sweep_dag_t d, int32_t G, const FwdPlan& p, const 
   r.blk_cell0 = d->blk_cell0.as<int32_t>();
   r.mesh_off = d->mesh_off_d.as<int32_t>();
   r.mesh_cells = d->mesh_cells_d.as<int32_t>();
+  r.inv = d->inv.as<int32_t>();
+  r.out_s = reduce_direct(d, G) ? d->out_s.as<float>() : nullptr;
   r.bnd = d->bnd.as<float2>();
+  r.edge = d->edge.as<uint8_t>();
   r.aperp = d->aperp.as<float>();
   r.law = p.law;
   r.kappa = kappa;
@@ -561,6 +571,7 @@ sweep::ReduceArgs reduce_args(sweep_dag_t d, int32_t G, const FwdPlan& p, const 
   r.absorbed = absorbed;
   r.partial = d->partial.as<double>();
   r.cells_per_block = d->red_cpb;
+  r.n_blocks = d->red_blocks;
   return r;
 }
 
@@ -604,7 +615,8 @@ sweep_status_t run_pin(sweep_dag_t d, bool adjoint, int32_t G, const float* othe
 }
 
 // One sweep of every unit (after run_prep, and run_pin for a periodic pass with
-// another pass before it, forward, or after it, adjoint).
+// another pass before it, forward, or after it, adjoint), its results left in
+// d->out_s in schedule order and copied to `out` (if any) in cell order.
 sweep_status_t run_sweep(sweep_dag_t d, bool reverse, const FwdPlan& p, int32_t G, float* out,
                          hipStream_t s) {
   sweep::SweepArgs a{};
@@ -667,6 +679,7 @@ sweep_status_t run_sweep(sweep_dag_t d, bool reverse, const FwdPlan& p, int32_t 
       if (e != hipSuccess) return hip_fail(e, "sweep launch");
     }
   }
+  if (out == nullptr) return SWEEP_OK;
   HIP_TRY(sweep::launch_to_cells(d->units_d.as<Unit>(), n_units, d->blk_base.as<int32_t>(), d->n_blocks,
                                  d->inv.as<int32_t>(), d->out_s.as<float>(), out, d->C_total, G, s));
   return SWEEP_OK;
@@ -945,12 +958,13 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   // (k_fill reads both four faces at a time, from any face on)
   HIP_TRY(fcode.alloc(4 * n_faces_total + 16));
   HIP_TRY(wface.alloc(4 * (size_t)n_faces_total * n_dirs + 16));
+  HIP_TRY(D->edge.alloc(D->C_total));
   {
     int64_t fo = 0;
     for (int m = 0; m < n_meshes; ++m) {
       md[m].fcode = fcode.as<int32_t>() + fo;
       md[m].face_off = fo;
-      HIP_TRY(sweep::launch_face_codes(md[m], fcode.as<int32_t>() + fo, s));
+      HIP_TRY(sweep::launch_face_codes(md[m], fcode.as<int32_t>() + fo, D->edge.as<uint8_t>(), s));
       fo += meshes[m].n_half_faces;
     }
   }
@@ -1284,7 +1298,7 @@ sweep_status_t sweep_dag_info(sweep_dag_t d, sweep_dag_info_t* info) {
   info->min_depth = mn;
   info->mean_depth = sum / d->units.size();
   const Buf* bufs[] = {&d->sched, &d->inv, &d->indeg, &d->lp, &d->len_up, &d->len_dn,
-                       &d->slice_base, &d->sl_up, &d->sl_dn, &d->up, &d->dn, &d->aperp, &d->aperp_s, &d->vol_s, &d->bnd, &d->vol,
+                       &d->slice_base, &d->sl_up, &d->sl_dn, &d->up, &d->dn, &d->aperp, &d->aperp_s, &d->vol_s, &d->bnd, &d->edge, &d->vol,
                        &d->pcell, &d->pf_ptr, &d->pnb, &d->pwf, &d->pwa, &d->ptask, &d->pc_map};
   int64_t b = 0;
   for (const Buf* x : bufs) b += (int64_t)x->bytes;
@@ -1402,7 +1416,8 @@ sweep_status_t sweep_forward(sweep_dag_t d, int32_t G, const float* kappa, const
   const int64_t CG = d->C_total * G;
   const int64_t DCG = CG * d->D;
   ST_TRY(ensure_reduce_tables(d, G));
-  if (!saved) HIP_TRY(d->phi_a.alloc(4 * DCG));
+  const bool direct = reduce_direct(d, G);
+  if (!saved && (n_inner > 1 || !direct)) HIP_TRY(d->phi_a.alloc(4 * DCG));
   if (periodic && n_inner > 1) HIP_TRY(d->phi_b.alloc(4 * DCG));
   if (warm) HIP_TRY(d->phi_w.alloc(4 * DCG));
   if (periodic) ST_TRY(alloc_periodic(d, G));
@@ -1467,7 +1482,10 @@ sweep_status_t sweep_forward(sweep_dag_t d, int32_t G, const float* kappa, const
         }
         psum_before = psum_last;
         psum_last = psum_ps;
-        ST_TRY(run_sweep(d, false, p, G, dst, st));
+        // (a reduction straight from schedule order copies to cell order on its way what a
+        // later pass or the adjoint will read)
+        const bool reduced = tol || final_pass || merge;
+        ST_TRY(run_sweep(d, false, p, G, reduced && direct ? nullptr : dst, st));
         if (tol) {
           // the full reduction after every pass: E against the previous pass's
           // inflow, then the totals read back
@@ -1481,7 +1499,7 @@ sweep_status_t sweep_forward(sweep_dag_t d, int32_t G, const float* kappa, const
           q.jsum = ckpt(it);
           {
             ProfScope pr("reduce", st);
-            HIP_TRY(sweep::launch_reduce(q, d->red_blocks, st));
+            HIP_TRY(sweep::launch_reduce(q, st));
           }
           bool stop = final_pass;
           if (ps > 0 && !final_pass) {
@@ -1509,13 +1527,13 @@ sweep_status_t sweep_forward(sweep_dag_t d, int32_t G, const float* kappa, const
           q.phi = dst;
           q.jsum_prev = jprev;
           q.jsum = jm(ps);
-          HIP_TRY(sweep::launch_reduce(q, d->red_blocks, st));
+          HIP_TRY(sweep::launch_reduce(q, st));
         }
         prev = dst;
       }
       if (tol) continue;  // the last pass's reduction is done
       sweep::ReduceArgs q = r;
-      q.phi = phi_final;
+      q.phi = !direct || (saved && it == n_outer - 1) ? phi_final : nullptr;
       q.pc_map = periodic ? d->pc_map.as<int32_t>() : nullptr;
       q.psum = psum_last;
       q.psum_prev = psum_before;
@@ -1524,7 +1542,7 @@ sweep_status_t sweep_forward(sweep_dag_t d, int32_t G, const float* kappa, const
       q.jsum = merge ? jm(n_inner - 1) : ckpt(it);
       {
         ProfScope ps("reduce", st);
-        HIP_TRY(sweep::launch_reduce(q, d->red_blocks, st));
+        HIP_TRY(sweep::launch_reduce(q, st));
       }
       // merged: the final pass's sums are the last iteration's checkpoint
       if (merge && saved)
@@ -1583,7 +1601,8 @@ sweep_status_t sweep_adjoint(sweep_dag_t d, int32_t G, const float* kappa,
   // are recomputed into phi_a (x^{P-1}) and xpass (the others)
   const int P = merge ? std::max(p.n_pbc, p.n_scat) : periodic ? p.n_pbc : 1;
   ST_TRY(ensure_mesh_tables(d));
-  HIP_TRY(d->lam.alloc(4 * DCG));
+  const bool direct = reduce_direct(d, G);
+  if (P > 1 || !direct) HIP_TRY(d->lam.alloc(4 * DCG));
   HIP_TRY(d->gsrc.alloc(4 * CG));
   HIP_TRY(d->dk64.alloc(8 * CG));
   HIP_TRY(d->de64.alloc(8 * CG));
@@ -1596,7 +1615,7 @@ sweep_status_t sweep_adjoint(sweep_dag_t d, int32_t G, const float* kappa,
     if (p.n_scat > 1) HIP_TRY(d->phi_a.alloc(4 * DCG));
     if (p.n_scat > 1 && P > 1) HIP_TRY(d->xpass.alloc(4 * DCG * (P - 1)));
   }
-  if (P > 1) HIP_TRY(d->lam_b.alloc(4 * DCG));
+  if (P > (direct ? 2 : 1)) HIP_TRY(d->lam_b.alloc(4 * DCG));
   if (periodic) ST_TRY(alloc_periodic(d, G));
   HIP_TRY(d->tden.alloc(4 * (size_t)d->T * G));
   HIP_TRY(d->tsrc.alloc(4 * (size_t)d->T * G));
@@ -1672,7 +1691,7 @@ sweep_status_t sweep_adjoint(sweep_dag_t d, int32_t G, const float* kappa,
           }
           ST_TRY(run_pin(d, true, G, lam_next, nullptr, fresh, st));
         }
-        ST_TRY(run_sweep(d, true, p, G, lam_ps, st));
+        ST_TRY(run_sweep(d, true, p, G, direct ? nullptr : lam_ps, st));
         sweep::AdjReduceArgs q{};
         q.D = d->D;
         q.G = G;
@@ -1684,7 +1703,9 @@ sweep_status_t sweep_adjoint(sweep_dag_t d, int32_t G, const float* kappa,
         q.gsrc = d->gsrc.as<float>();
         q.use_g = loss_pass ? 1 : 0;
         q.accumulate = loss_pass ? 0 : 1;
-        q.lam = lam_ps;
+        q.inv = d->inv.as<int32_t>();
+        q.out_s = direct ? d->out_s.as<float>() : nullptr;
+        q.lam = !direct || ps > 0 ? lam_ps : nullptr;  // (the pass before takes it through the periodic faces)
         q.phi = xp(it, ps);
         q.kappa = kappa;
         q.vol = d->vol.as<float>();
@@ -1716,12 +1737,12 @@ sweep_status_t sweep_adjoint(sweep_dag_t d, int32_t G, const float* kappa,
       fresh = true;
       if (ps > 0) ST_TRY(run_pin(d, false, G, xm(ps - 1), nullptr, fresh, st));
       else if (warm_saved != nullptr) ST_TRY(run_pin(d, false, G, warm_saved, nullptr, fresh, st));
-      ST_TRY(run_sweep(d, false, p, G, xm(ps), st));
+      ST_TRY(run_sweep(d, false, p, G, direct ? nullptr : xm(ps), st));
       sweep::ReduceArgs q = r;
       q.phi = xm(ps);
       q.jsum_prev = jprev;
       q.jsum = jmp(ps);
-      HIP_TRY(sweep::launch_reduce(q, d->red_blocks, st));
+      HIP_TRY(sweep::launch_reduce(q, st));
     }
     HIP_TRY(sweep::launch_adj_init(dL_dJ, dL_dabsorbed, kappa, d->vol.as<float>(), jmp(P - 1),
                                    p.albedo, G, d->C_total, d->gsrc.as<float>(),
@@ -1734,7 +1755,7 @@ sweep_status_t sweep_adjoint(sweep_dag_t d, int32_t G, const float* kappa,
       ST_TRY(run_prep(d, G, kappa, nullptr, d->gsrc.as<float>(), nullptr, p.albedo, p.law, st));
       fresh = true;
       if (lam_next != nullptr) ST_TRY(run_pin(d, true, G, lam_next, nullptr, fresh, st));
-      ST_TRY(run_sweep(d, true, p, G, lam_ps, st));
+      ST_TRY(run_sweep(d, true, p, G, direct ? nullptr : lam_ps, st));
       sweep::AdjReduceArgs q{};
       q.D = d->D;
       q.G = G;
@@ -1746,7 +1767,9 @@ sweep_status_t sweep_adjoint(sweep_dag_t d, int32_t G, const float* kappa,
       q.gsrc = d->gsrc.as<float>();
       q.use_g = 1;
       q.accumulate = 0;
-      q.lam = lam_ps;
+      q.inv = d->inv.as<int32_t>();
+      q.out_s = direct ? d->out_s.as<float>() : nullptr;
+      q.lam = !direct || ps > 0 ? lam_ps : nullptr;
       q.phi = xm(ps);
       q.kappa = kappa;
       q.vol = d->vol.as<float>();

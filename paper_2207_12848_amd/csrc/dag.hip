@@ -1043,13 +1043,22 @@ __global__ __launch_bounds__(256) void k_check_mesh(MeshDev M, int32_t* bad) {
 
 // Per face: the neighbour code (>= 0: interior neighbour, -1: vacuum wall,
 // -(nb + 2): periodic image of cell nb), which the row fill reads next to the
-// face's signed weight instead of the FP64 geometry.
-__global__ void k_face_codes(MeshDev M, int32_t* fcode) {
-  const int64_t f = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (f >= M.n_faces) return;
-  const int nb = M.face_nbr[f];
-  const bool periodic = M.face_shift != nullptr && M.face_shift[f] != 0;
-  fcode[f] = nb < 0 ? -1 : (periodic ? -(nb + 2) : nb);
+// face's signed weight instead of the FP64 geometry; per cell: whether one is
+// negative.  16 lanes per cell.
+__global__ __launch_bounds__(256) void k_face_codes(MeshDev M, int32_t* fcode, uint8_t* edge) {
+  const int c = blockIdx.x * 16 + (threadIdx.x >> 4);
+  bool e = false;
+  if (c < M.n_cells) {
+    for (int64_t f = M.face_ptr[c] + (threadIdx.x & 15); f < M.face_ptr[c + 1]; f += 16) {
+      const int nb = M.face_nbr[f];
+      const bool periodic = M.face_shift != nullptr && M.face_shift[f] != 0;
+      fcode[f] = nb < 0 ? -1 : (periodic ? -(nb + 2) : nb);
+      e |= nb < 0 || periodic;
+    }
+  }
+  const unsigned long long any = __ballot(e);
+  if (c < M.n_cells && (threadIdx.x & 15) == 0)
+    edge[M.cell_off + c] = ((any >> (threadIdx.x & 48)) & 0xffffull) != 0ull ? 1 : 0;
 }
 
 // Unit of a slice.
@@ -1613,9 +1622,9 @@ hipError_t launch_check_mesh(const MeshDev& m, int32_t* bad, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_face_codes(const MeshDev& m, int32_t* fcode, hipStream_t s) {
-  if (m.n_faces <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_face_codes, dim3(grid1d(m.n_faces, 256)), dim3(256), 0, s, m, fcode);
+hipError_t launch_face_codes(const MeshDev& m, int32_t* fcode, uint8_t* edge, hipStream_t s) {
+  if (m.n_cells <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_face_codes, dim3(grid1d(m.n_cells, 16)), dim3(256), 0, s, m, fcode, edge);
   return hipGetLastError();
 }
 

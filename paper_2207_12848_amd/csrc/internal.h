@@ -193,7 +193,6 @@ struct PrepArgs {
 
 // Reduction over directions (per cell and group).
 struct ReduceArgs {
-  const Unit* units;
   int32_t D;
   int32_t G;
   int64_t C_total;
@@ -201,12 +200,15 @@ struct ReduceArgs {
   const int32_t* blk_cell0;  // [n_blocks] global first cell of the block
   const int32_t* mesh_off;   // [n_meshes+1]
   const int32_t* mesh_cells;  // [n_meshes]
-  const float* phi;          // [D][C][G]
+  const int32_t* inv;        // per task, cell order: schedule position in its unit
+  const float* out_s;        // [T][G] results in schedule order (nullptr: phi holds them)
+  float* phi;                // [D][C][G] results in cell order; with out_s: out, or nullptr
   const int32_t* pc_map;     // [C_total] periodic cell index or -1 (nullptr: no periodic inflow)
   const double* psum;        // [n_pc][G] periodic inflow of the pass summed over directions
   const double* psum_prev;   // [n_pc][G] the same of the pass before, or nullptr (zero inflow)
   int32_t with_e;            // 1: E of the pass against the pass before (sec. 2.7)
   const float2* bnd;         // per task, cell order
+  const uint8_t* edge;       // [C_total] 1: cells with wall or periodic faces (elsewhere bnd is zero)
   const float* aperp;        // per task, cell order
   int32_t law;
   const float* kappa;
@@ -219,6 +221,7 @@ struct ReduceArgs {
   float* absorbed;           // out
   double* partial;           // [n_blocks][G][9]
   int32_t cells_per_block;
+  int32_t n_blocks;
 };
 
 // Periodic coupling of a pass, folded into its sources: a task of a periodic
@@ -257,7 +260,9 @@ struct AdjReduceArgs {
   const float* gsrc;       // [C][G] adjoint source of this iteration (dL/d cell average)
   int32_t use_g;           // this pass carries the loss (its g enters the kappa derivative)
   int32_t accumulate;      // add to gsrc_next (earlier periodic passes) instead of writing it
-  const float* lam;        // [D][C][G]
+  const int32_t* inv;      // per task, cell order: schedule position in its unit
+  const float* out_s;      // [T][G] lambda in schedule order (nullptr: lam holds it)
+  float* lam;              // [D][C][G] lambda in cell order; with out_s: out, or nullptr
   const float* phi;        // [D][C][G]
   const float* kappa;
   const float* vol;
@@ -299,7 +304,7 @@ hipError_t launch_face_stats(const int64_t* face_ptr, int32_t n_cells, int32_t r
                              unsigned long long* out, hipStream_t s);
 // *bad is set if the mesh may violate a condition of the host's check
 hipError_t launch_check_mesh(const MeshDev& m, int32_t* bad, hipStream_t s);
-hipError_t launch_face_codes(const MeshDev& m, int32_t* fcode, hipStream_t s);
+hipError_t launch_face_codes(const MeshDev& m, int32_t* fcode, uint8_t* edge, hipStream_t s);
 // Sorts every level of the schedule by cell id and writes the inverse schedule.
 hipError_t launch_sort_levels(const DagBuildArgs& a, hipStream_t s);
 // Slices per unit (n_unit_slices); then, with the slices' place known, the slice
@@ -331,7 +336,7 @@ hipError_t launch_sweep_adj(const SweepArgs& a, int32_t gn, int32_t grid, int32_
 hipError_t launch_to_cells(const Unit* units, int32_t n_units, const int32_t* blk_base, int32_t n_blocks,
                            const int32_t* inv, const float* out_s, float* out, int64_t C_total,
                            int32_t G, hipStream_t s);
-hipError_t launch_reduce(const ReduceArgs& a, int32_t n_blocks, hipStream_t s);
+hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s);
 hipError_t launch_pin(const PinArgs& a, hipStream_t s);
 hipError_t launch_pcount(const DagBuildArgs& a, const MeshDev& m, hipStream_t s);
 hipError_t launch_plist(const DagBuildArgs& a, const MeshDev& m, hipStream_t s);

@@ -831,44 +831,100 @@ __global__ __launch_bounds__(256) void k_psum(PinArgs a) {
 }
 
 // ----------------------------------------------------------------------- reductions
-constexpr int kRedBlock = 256;
+constexpr int kRedItems = 256;  // (cell, group) items of a workgroup
+constexpr int kRedBatch = 4;    // directions whose loads a thread has in flight
 constexpr int kNPart = 9;
 
-__global__ __launch_bounds__(kRedBlock) void k_reduce(ReduceArgs a) {
-  __shared__ double part[kRedBlock][kNPart];
-  const int m = a.blk_mesh[blockIdx.x];
-  const int c0 = a.blk_cell0[blockIdx.x];
+// Threads per item, among which its directions go round.
+constexpr int red_teams(bool sched) { return sched ? 4 : 1; }
+
+// The direction sums of a pass.  SCHED: straight from the sweep's results in schedule
+// order (STORE: with their copy in cell order on the way), else from that copy.  Bound
+// by the gathers (SCHED, a line request per task; the workgroups of consecutive cells
+// run on one XCD, whose L2 then serves the other cells of a line) or by memory.  Four
+// threads share an item (SCHED), since one per item leaves small meshes waiting for a
+// chain of loads, and the boundary weights are read for cells that have boundary faces
+// only (8 bytes per task, all zero elsewhere).  Copy and sums of 4096 cells x 8
+// directions: 6.4 us, before 32; 32^3 x 84, exponential law: 32 us, before 96; 64^3 x 84:
+// 122 us, before 197; 12 meshes of 512 to 8192 cells x 24 directions: 41 us, before 97.
+// From the copy: 128^3 x 84, exponential law: 0.67 ms, before 0.80; 2 M cells x 84 x 4
+// groups: 0.79 ms (3.6 TB/s), before 1.31.
+template <bool EXP_LAW, bool SCHED, bool STORE>
+__global__ __launch_bounds__(kRedItems* red_teams(SCHED)) void k_reduce(ReduceArgs a) {
+  constexpr int kTeams = red_teams(SCHED);
+  __shared__ double part[kNPart][kRedItems];
+  __shared__ double sums[kTeams][3][kRedItems];
+  const int i = threadIdx.x % kRedItems;
+  const int team = __builtin_amdgcn_readfirstlane(threadIdx.x / kRedItems);
+  const int blk = xcd_block(blockIdx.x, gridDim.x);
+  const int m = a.blk_mesh[blk];
   const int G = a.G;
-  const int i = threadIdx.x;
-  const int c = c0 + i / G;
+  const int c = a.blk_cell0[blk] + i / G;
   const int g = i % G;
-  const int mend = a.mesh_off[m] + a.mesh_cells[m];
-  const bool active = (i < a.cells_per_block * G) && (c < mend);
-  double v[kNPart];
-#pragma unroll
-  for (int k = 0; k < kNPart; ++k) v[k] = 0.0;
+  const int C = a.mesh_cells[m];
+  const int lc = c - a.mesh_off[m];
+  const bool active = i < a.cells_per_block * G && lc < C;
+  const int64_t cg = (int64_t)c * G + g;
+  double V = 0.0, kap = 0.0, js = 0.0, esc = 0.0, pout = 0.0;
   if (active) {
-    const int64_t cg = (int64_t)c * G + g;
     const int64_t stride = a.C_total * G;
-    const int lc = c - a.mesh_off[m];
-    const double V = (double)a.vol[c];
-    const double kap = (double)a.kappa[cg];
-    const bool exp_law = a.law == SWEEP_LAW_EXP;
-    double js = 0.0, esc = 0.0, pout = 0.0;
-    for (int d = 0; d < a.D; ++d) {
-      // phi holds the exit flux density x (phi itself under the upwind law)
-      const double ph = (double)a.phi[d * stride + cg];
-      const int64_t t = a.units[m * a.D + d].task_base + lc;
-      const float2 b = a.bnd[t];
-      esc += (double)b.x * ph;
-      pout += (double)b.y * ph;
-      js += exp_law ? ph * exp_r((double)a.aperp[t], kap * V) : ph;
+    const int64_t t0 = (int64_t)a.D * a.mesh_off[m];  // tasks of the mesh: [direction][cell]
+    V = (double)a.vol[c];
+    kap = (double)a.kappa[cg];
+    const bool edge = a.edge[c] != 0;
+    float zero = 0.0f;  // 0 x every value, as the sums of zero weights would be
+    for (int d0 = team; d0 < a.D; d0 += kTeams * kRedBatch) {
+      int64_t t[kRedBatch];
+      int p[kRedBatch];
+      float ph[kRedBatch];
+#pragma unroll
+      for (int k = 0; k < kRedBatch; ++k) {  // (past the last direction: read again)
+        const int d = min(d0 + kTeams * k, a.D - 1);
+        t[k] = t0 + (int64_t)d * C;
+        if (SCHED) p[k] = a.inv[t[k] + lc];
+        else ph[k] = a.phi[d * stride + cg];
+      }
+      if (SCHED) {
+#pragma unroll
+        for (int k = 0; k < kRedBatch; ++k) ph[k] = a.out_s[(t[k] + p[k]) * G + g];
+      }
+#pragma unroll
+      for (int k = 0; k < kRedBatch; ++k) {
+        const int d = d0 + kTeams * k;
+        if (d >= a.D) break;
+        // (the exit flux density x: phi itself under the upwind law)
+        const double x = (double)ph[k];
+        if (STORE) a.phi[d * stride + cg] = ph[k];
+        js += EXP_LAW ? x * exp_r((double)a.aperp[t[k] + lc], kap * V) : x;
+        zero = __builtin_fmaf(0.0f, ph[k], zero);
+        if (edge) {
+          const float2 b = a.bnd[t[k] + lc];
+          esc += (double)b.x * x;
+          pout += (double)b.y * x;
+        }
+      }
     }
-    // the periodic inflow of the pass (and of the pass before), summed over
-    // directions when the pass's sources were folded
-    const int pc = a.pc_map != nullptr ? a.pc_map[c] : -1;
-    const double pn = pc >= 0 && a.psum != nullptr ? a.psum[(int64_t)pc * G + g] : 0.0;
-    {
+    if (!edge) esc = pout = (double)zero;
+  }
+  if (team > 0) {
+    sums[team][0][i] = js;
+    sums[team][1][i] = esc;
+    sums[team][2][i] = pout;
+  }
+  __syncthreads();
+  if (team == 0) {
+    double v[kNPart] = {};
+    if (active) {
+#pragma unroll
+      for (int k = 1; k < kTeams; ++k) {
+        js += sums[k][0][i];
+        esc += sums[k][1][i];
+        pout += sums[k][2][i];
+      }
+      // the periodic inflow of the pass (and of the pass before), summed over
+      // directions when the pass's sources were folded
+      const int pc = a.pc_map != nullptr ? a.pc_map[c] : -1;
+      const double pn = pc >= 0 && a.psum != nullptr ? a.psum[(int64_t)pc * G + g] : 0.0;
       const double ka = (1.0 - (double)a.albedo) * kap;
       const double ks = (double)a.albedo * kap;
       const double ab = ka * V * js;
@@ -890,23 +946,21 @@ __global__ __launch_bounds__(kRedBlock) void k_reduce(ReduceArgs a) {
         v[8] = den;
       }
     }
+#pragma unroll
+    for (int k = 0; k < kNPart; ++k) part[k][i] = v[k];
   }
-#pragma unroll
-  for (int k = 0; k < kNPart; ++k) part[i][k] = v[k];
   __syncthreads();
-  if (i < G) {
-    double s[kNPart];
-#pragma unroll
-    for (int k = 0; k < kNPart; ++k) s[k] = 0.0;
-    for (int j = i; j < kRedBlock; j += G) {
-#pragma unroll
-      for (int k = 0; k < kNPart; ++k) {
-        if (k == 6) s[k] = fmax(s[k], part[j][k]);
-        else s[k] += part[j][k];
-      }
+  // the workgroup's sums, a wavefront per (quantity, group), in a fixed order
+  const int lane = threadIdx.x & 63;
+  for (int q = threadIdx.x >> 6; q < kNPart * G; q += kRedItems * kTeams / 64) {
+    const int k = q / G, gq = q % G;
+    double r = 0.0;
+    for (int j = lane * G + gq; j < a.cells_per_block * G; j += 64 * G) r = k == 6 ? fmax(r, part[k][j]) : r + part[k][j];
+    for (int o = 32; o > 0; o >>= 1) {
+      const double x = __shfl_xor(r, o);
+      r = k == 6 ? fmax(r, x) : r + x;
     }
-#pragma unroll
-    for (int k = 0; k < kNPart; ++k) a.partial[((int64_t)blockIdx.x * G + i) * kNPart + k] = s[k];
+    if (lane == 0) a.partial[((int64_t)blk * G + gq) * kNPart + k] = r;
   }
 }
 
@@ -955,57 +1009,75 @@ __global__ void k_adj_init(const float* dJ, const float* dA, const float* kappa,
   de[i] = 0.0;
 }
 
-__global__ void k_adj_reduce(AdjReduceArgs a, double* dk, double* de) {
+// The adjoint's direction sums.  SCHED: lambda straight from the sweep's results in schedule
+// order (STORE: with its copy in cell order on the way), else from that copy.
+constexpr int kAdjBatch = 8;  // directions whose loads a thread has in flight
+
+template <bool EXP_LAW, bool SCHED, bool STORE>
+__global__ __launch_bounds__(256) void k_adj_reduce(AdjReduceArgs a, double* dk, double* de) {
   const int64_t n = a.C_total * a.G;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t i = (int64_t)(SCHED ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const double V = (double)a.vol[i / a.G];
-  double ls = 0.0, dks;
-  if (a.law == SWEEP_LAW_EXP) {
-    // per direction: -lambda x d(den)/dkappa + g x dr/dkappa, with
-    // tau < 40: d(den)/dkappa = V e^tau, dr/dkappa = h'(tau) V / Aperp;
-    // tau >= 40: d(den)/dkappa = 0, dr/dkappa = -r / kappa
-    const int c = (int)(i / a.G);
-    int lo = 0, hi = a.n_meshes - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (a.mesh_off[mid] <= c) lo = mid; else hi = mid - 1;
-    }
-    // tasks of mesh m: [direction][local cell] from D * (first cell of m)
-    const int64_t Cm = a.mesh_off[lo + 1] - a.mesh_off[lo];
-    const float* apc = a.aperp + (int64_t)a.D * a.mesh_off[lo] + (c - a.mesh_off[lo]);
-    const double kap = (double)a.kappa[i];
-    const double kV = kap * V;
-    const double g = a.use_g ? (double)a.gsrc[i] : 0.0;
-    dks = 0.0;
-#pragma unroll 4
-    for (int d = 0; d < a.D; ++d) {
-      const double l = (double)a.lam[d * n + i];
-      const double x = (double)a.phi[d * n + i];
-      const double ap = (double)apc[d * Cm];
-      const double tau = kV / ap;
-      double dden, dr;
-      if (tau < kTauCap) {
-        dden = V * exp(tau);
-        dr = dh_dt(tau) * V / ap;
-      } else {
-        dden = 0.0;
-        dr = -(ap * expm1(kTauCap) / kV) / kap;
-      }
-      ls += l;
-      dks += -l * x * dden + g * x * dr;
-    }
-  } else {
-    double lph = 0.0;
-    // (unrolled: the loads of eight directions in flight before the first is used)
-#pragma unroll 8
-    for (int d = 0; d < a.D; ++d) {
-      const double l = (double)a.lam[d * n + i];
-      ls += l;
-      lph += l * (double)a.phi[d * n + i];
-    }
-    dks = -V * lph;
+  const int c = (int)(i / a.G);
+  const int g = (int)(i - (int64_t)c * a.G);
+  const double V = (double)a.vol[c];
+  int lo = 0, hi = a.n_meshes - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (a.mesh_off[mid] <= c) lo = mid; else hi = mid - 1;
   }
+  // tasks of mesh m: [direction][local cell] from D * (first cell of m)
+  const int64_t Cm = a.mesh_off[lo + 1] - a.mesh_off[lo];
+  const int64_t t0 = (int64_t)a.D * a.mesh_off[lo];
+  const int lc = c - a.mesh_off[lo];
+  const double kap = (double)a.kappa[i];
+  const double kV = kap * V;
+  const double gs = EXP_LAW && a.use_g ? (double)a.gsrc[i] : 0.0;
+  double ls = 0.0, dks = 0.0;
+  for (int d0 = 0; d0 < a.D; d0 += kAdjBatch) {
+    int p[kAdjBatch];
+    float lam[kAdjBatch], phi[kAdjBatch];
+#pragma unroll
+    for (int k = 0; k < kAdjBatch; ++k) {  // (past the last direction: read again)
+      const int d = min(d0 + k, a.D - 1);
+      if (SCHED) p[k] = a.inv[t0 + d * Cm + lc];
+      else lam[k] = a.lam[d * n + i];
+      phi[k] = a.phi[d * n + i];
+    }
+    if (SCHED) {
+#pragma unroll
+      for (int k = 0; k < kAdjBatch; ++k)
+        lam[k] = a.out_s[(t0 + min(d0 + k, a.D - 1) * Cm + p[k]) * a.G + g];
+    }
+#pragma unroll
+    for (int k = 0; k < kAdjBatch; ++k) {
+      const int d = d0 + k;
+      if (d >= a.D) break;
+      const double l = (double)lam[k];
+      const double x = (double)phi[k];
+      if (STORE) a.lam[d * n + i] = lam[k];
+      ls += l;
+      if (EXP_LAW) {
+        // per direction: -lambda x d(den)/dkappa + g x dr/dkappa, with
+        // tau < 40: d(den)/dkappa = V e^tau, dr/dkappa = h'(tau) V / Aperp;
+        // tau >= 40: d(den)/dkappa = 0, dr/dkappa = -r / kappa
+        const double ap = (double)a.aperp[t0 + d * Cm + lc];
+        const double tau = kV / ap;
+        double dden, dr;
+        if (tau < kTauCap) {
+          dden = V * exp(tau);
+          dr = dh_dt(tau) * V / ap;
+        } else {
+          dden = 0.0;
+          dr = -(ap * expm1(kTauCap) / kV) / kap;
+        }
+        dks += -l * x * dden + gs * x * dr;
+      } else {
+        dks += l * x;
+      }
+    }
+  }
+  if (!EXP_LAW) dks = -V * dks;
   const double prev = a.jsum_prev != nullptr ? (double)a.jsum_prev[i] : 0.0;
   const double alb = (double)a.albedo;
   const double invD = (double)a.inv_D;
@@ -1093,9 +1165,14 @@ hipError_t launch_pin(const PinArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_reduce(const ReduceArgs& a, int32_t n_blocks, hipStream_t s) {
-  if (n_blocks <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_reduce, dim3(n_blocks), dim3(kRedBlock), 0, s, a);
+hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s) {
+  if (a.n_blocks <= 0) return hipSuccess;
+  auto pick = [&](auto e) {
+    constexpr bool E = decltype(e)::value;
+    return a.out_s == nullptr ? k_reduce<E, false, false> : a.phi != nullptr ? k_reduce<E, true, true> : k_reduce<E, true, false>;
+  };
+  auto kernel = a.law == SWEEP_LAW_EXP ? pick(std::true_type()) : pick(std::false_type());
+  hipLaunchKernelGGL(kernel, dim3(a.n_blocks), dim3(kRedItems * red_teams(a.out_s != nullptr)), 0, s, a);
   return hipGetLastError();
 }
 
@@ -1119,7 +1196,13 @@ hipError_t launch_adj_init(const float* dJ, const float* dA, const float* kappa,
 hipError_t launch_adj_reduce(const AdjReduceArgs& a, double* dk, double* de, hipStream_t s) {
   const int64_t n = a.C_total * a.G;
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_adj_reduce, dim3(grid1d(n, 256)), dim3(256), 0, s, a, dk, de);
+  auto pick = [&](auto e) {
+    constexpr bool E = decltype(e)::value;
+    return a.out_s == nullptr ? k_adj_reduce<E, false, false>
+           : a.lam != nullptr ? k_adj_reduce<E, true, true> : k_adj_reduce<E, true, false>;
+  };
+  auto kernel = a.law == SWEEP_LAW_EXP ? pick(std::true_type()) : pick(std::false_type());
+  hipLaunchKernelGGL(kernel, dim3(grid1d(n, 256)), dim3(256), 0, s, a, dk, de);
   return hipGetLastError();
 }
 
