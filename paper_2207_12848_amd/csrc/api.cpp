@@ -248,6 +248,7 @@ struct sweep_dag_s {
   int32_t n_blocks = 0;  // 256-task blocks over all units (prep kernel)
   int32_t max_depth = 0;
   int32_t max_cells = 0;  // cells of the largest mesh
+  int32_t max_up = 0, max_dn = 0;  // entries of the longest row of either walk
   int32_t kahn_lds = 0;   // the levels were computed with counters in LDS
   int32_t scheme = SWEEP_SCHEME_AREA;
   Buf flag;               // device error bits (see internal.h) raised by asynchronous calls
@@ -633,6 +634,7 @@ sweep_status_t run_sweep(sweep_dag_t d, bool reverse, const FwdPlan& p, int32_t 
   a.G = G;
   a.D = d->D;
   a.flag = d->flag.as<int32_t>();
+  a.max_row = reverse ? d->max_dn : d->max_up;
   const int n_units = (int)d->units.size();
   for (const GroupLaunch& c : group_plan(d, G, p.form == SWEEP_FORM_PLAIN, p.pack)) {
     const int gn = c.gn;
@@ -1087,6 +1089,8 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   const bool lds_cnt = kahn_counters == 2 ? false : lds_fits;
   // otherwise in an LDS hash table of the cells being counted, or as bytes in global memory
   a.hash_bits = lds_cnt ? 0 : sweep::kahn_hash_bits(max_cells, stats[0]);
+  D->max_up = stats[0];
+  D->max_dn = stats[1];
   if (!lds_cnt && stats[0] > 254)
     return fail(SWEEP_ERR_UNSUPPORTED, "a cell with %d upwind dependencies in one direction "
                 "(at most 254 when the mesh's counters do not fit in LDS)", stats[0]);

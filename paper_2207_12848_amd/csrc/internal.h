@@ -164,6 +164,7 @@ struct SweepArgs {
   int32_t D;
   int32_t ring_mask;
   int32_t* flag;   // device error bits: kErrStall
+  int32_t max_row;  // entries of this walk's longest row
 };
 
 // Per-call preparation of the per-task denominators and sources, written in

@@ -127,7 +127,11 @@ __device__ __forceinline__ int rank_in(uint64_t m) {
   return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-constexpr int kPairs = 8;  // entry pairs of a row held in registers (16 entries)
+// Entry pairs of a row held in registers, the kernel's P: kPairs (16 entries), or 2 where no
+// row of the walk is longer (regular grids, tetrahedra), which leaves out the loads and the
+// work for columns that nobody has.  128^3 lattice cells x 84 directions: 2.70 ms with 2
+// pairs, 4.14 with 8; 32^3: 56 and 86 us.
+constexpr int kPairs = 8;
 
 // The unit's arrays (uniform over the workgroup).
 struct UnitBufs {
@@ -152,16 +156,17 @@ struct Slice {
   int k0, cnt, dep, lim, ks;  // uniform: SliceRec
   int64_t base;               // uniform: first entry pair
   int np;                     // uniform: entry pairs
-  int n4, n6, nt;             // uniform: pairs in columns 4 and 6; pairs past the columns in registers
+  int n4 = 0, n6 = 0, nt;     // uniform: pairs in columns 4 and 6; pairs past the columns in registers
   int len;                    // per lane: row length
   float den[GN], src[GN];
 };
 
-// Row entries of a slice in registers: kPairs pairs of this lane's row, and one
+// Row entries of a slice in registers: P pairs of this lane's row, and one
 // pair of the slice's entries past those columns.  Loaded as (position code,
 // factor) twice; resolving turns the codes into LDS byte offsets.
+template <int P>
 struct Entries {
-  int4 e[kPairs];
+  int4 e[P];
   int4 t;
 };
 
@@ -264,16 +269,20 @@ __device__ __forceinline__ void wait_count(lds_int* counter, int need, int& seen
 // The adjoint walks the slices backwards; its rows name reversed positions, so
 // the same code serves both.
 //
-// What bounds it: narrow levels, the chain from one level's count to the next
-// (about 0.42 us: LDS reads, multiply-adds, division, ring write, count, poll);
-// wide ones, the line requests of one compute unit's L1 (a unit runs on one) and
-// its instruction issue.  Against steps of a level with one barrier each, whose
-// wavefronts loaded, staged through LDS and solved by turns (forward sweep per
-// launch): 64^3 cells x 84 directions 2.27 -> 0.72 ms; 4,096 cells x 8 directions
-// 0.288 -> 0.100 ms; 2M clustered cells x 84 directions x 4 groups 27.0 -> 12.6 ms
-// (+ 1.5 ms for k_to_cells; with the results stored in cell order from here, 26.4).
-template <int GN, bool REVERSE>
+// What bounds it: narrow levels, the chain from one level's count to the next (about
+// 0.31 us: LDS reads, multiply-adds, division, ring write, count, poll); all that does not
+// wait for the level before is kept out of it, against the compiler where need be (the
+// slots' addresses, the reads of the row's tail).  Wide levels, the line requests of one
+// compute unit's L1 (a unit runs on one) and its instruction issue.  Against steps of a
+// level with one barrier each, whose wavefronts loaded, staged through LDS and solved by
+// turns (forward sweep per launch): 64^3 cells x 84 directions 2.27 -> 0.72 ms; 4,096 cells
+// x 8 directions 0.288 -> 0.075 ms; 2M clustered cells x 84 directions x 4 groups 27.0 ->
+// 11.9 ms (+ 1.5 ms for k_to_cells; with the results stored in cell order from here, 26.4).
+// A division with the reciprocal taken before the wait, and a test whether that is exact,
+// was slower: the test's branch costs more than the divide's dependent steps.
+template <int GN, bool REVERSE, int P>
 __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
+  constexpr int P4 = P < 4 ? P : 4, P6 = P < 6 ? P : 6;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = uni(tid >> 6);
@@ -339,12 +348,12 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
       ld_stream<GN>(B.src, k * (uint32_t)a.G, S.src);
     };
     // Pair j of the rows that have one is stored for those lanes in lane order.
-    auto load_entries = [&](Slice<GN>& S, Entries& E) {
+    auto load_entries = [&](Slice<GN>& S, Entries<P>& E) {
       const __amdgpu_buffer_rsrc_t ent = rsrc(a.ent + S.base, 16 * (int64_t)S.np);
       const int len = S.len = lane < S.cnt ? S.len : 0;
       int off = 0;
 #pragma unroll
-      for (int j = 0; j < kPairs; ++j) {
+      for (int j = 0; j < P; ++j) {
         const bool has = len > 2 * j;
         const uint64_t m = __ballot(has);
         uint32_t at = 16u * (uint32_t)rank_in(m);
@@ -359,31 +368,45 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
       E.t = ld_b128<kStream>(ent, lane < S.nt ? 16u * (uint32_t)lane : kOob, 16u * (uint32_t)off);
     };
 
+    int i = wave;  // slice S0
     Slice<GN> S0, S1, S2;
     int info;                  // record of the slice after S2
-    Entries EA, EB;
-    float f[2 * kPairs][GN], ft[2][GN];  // results from outside the window (else 0), of the slice resolved last
-    bool any = false, bad = false;       // some entry outside the window; one of them not visible yet
+    Entries<P> EA, EB;
+    float f[2 * P][GN], ft[2][GN];  // results from outside the window (else 0), of the slice resolved last
+    // how the slice resolved last is summed: its rows have up to P4, P6 or P pairs, all in
+    // the window; kOlder: some entry lies outside it, or rows go past the registers; kSlow:
+    // one of those is not visible yet, or rows go on still longer
+    enum { kUpTo4, kUpTo6, kUpTo8, kOlder, kSlow };
+    int mode = kUpTo4;
     int seen = 0, seen_st = 0;           // the counters as last read
     int vis = 0;                         // results before this position are in out_s
 
     // Window test, early loads of the older results and LDS offsets of a slice
     // (entries outside the window, and lanes without an entry, name the zero slot).
-    auto resolve = [&](const Slice<GN>& S, Entries& E, auto&& between) {
+    auto resolve = [&](const Slice<GN>& S, Entries<P>& E, auto&& between) {
       // codes below lo4 lie outside the window; real ones (not 0) are tested after
       // subtracting 4, which sends 0 to the top
       const uint32_t lo4 = 4u * (uint32_t)(max(S.lim - R, 0) + 1);
       const uint32_t vis4 = 4u * (uint32_t)max(vis, 0);
       uint32_t low = 0xffffffffu;  // the smallest real code
+      auto lowest = [&](int j0, int j1) {
 #pragma unroll
-      for (int j = 0; j < kPairs; ++j) {
-        low = min(low, (uint32_t)E.e[j].x - 4u);
-        low = min(low, (uint32_t)E.e[j].z - 4u);
-      }
-      low = min(low, (uint32_t)E.t.x - 4u);
-      low = min(low, (uint32_t)E.t.z - 4u);
-      any = __ballot(low < lo4 - 4u) != 0ull;
-      bad = S.nt > 64;
+        for (int j = j0; j < j1; ++j) low = min(min(low, (uint32_t)E.e[j].x - 4u), (uint32_t)E.e[j].z - 4u);
+      };
+      const bool past4 = P > 4 && S.n4 > 0, past6 = P > 6 && S.n6 > 0;
+      lowest(0, P4);
+      if (past4) lowest(P4, P6);
+      if (past6) lowest(P6, P);
+      if (S.nt > 0) low = min(min(low, (uint32_t)E.t.x - 4u), (uint32_t)E.t.z - 4u);
+      const bool any = __ballot(low < lo4 - 4u) != 0ull;
+      bool bad = S.nt > 64;
+      // the older results of the slice before are dead (their registers are free until here)
+#pragma unroll
+      for (int q = 0; q < 2 * P; ++q)
+#pragma unroll
+        for (int g = 0; g < GN; ++g) asm volatile("" : "=v"(f[q][g]));
+#pragma unroll
+      for (int g = 0; g < GN; ++g) asm volatile("" : "=v"(ft[0][g]), "=v"(ft[1][g]));
       between();
       if (any) {
         bool b = false;
@@ -396,50 +419,74 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
           ld_gn<GN>(B.outs, need ? d * (uint32_t)a.G : kOob, 0, v);
         };
 #pragma unroll
-        for (int j = 0; j < kPairs; ++j) {
+        for (int j = 0; j < P; ++j) {
           old(E.e[j].x, f[2 * j]);
           old(E.e[j].z, f[2 * j + 1]);
         }
         old(E.t.x, ft[0]);
         old(E.t.z, ft[1]);
         bad |= __ballot(b) != 0ull;
-      }
-      auto slot = [&](int x) { return (uint32_t)x < lo4 ? zero : slot_of<GN>(x, mask4); };
+      } else if (S.nt > 0) {  // (summed as kOlder)
 #pragma unroll
-      for (int j = 0; j < kPairs; ++j) {
-        E.e[j].x = slot(E.e[j].x);
-        E.e[j].z = slot(E.e[j].z);
+        for (int q = 0; q < 2 * P; ++q)
+#pragma unroll
+          for (int g = 0; g < GN; ++g) f[q][g] = 0.0f;
+#pragma unroll
+        for (int g = 0; g < GN; ++g) ft[0][g] = ft[1][g] = 0.0f;
       }
-      E.t.x = slot(E.t.x);
-      E.t.z = slot(E.t.z);
+      // (computed now, not after the wait for the slice's turn, where they are used)
+      auto slot = [&](int& x) {
+        x = (uint32_t)x < lo4 ? zero : slot_of<GN>(x, mask4);
+        asm volatile("" : "+v"(x));
+      };
+      auto slots = [&](int j0, int j1) {
+#pragma unroll
+        for (int j = j0; j < j1; ++j) {
+          slot(E.e[j].x);
+          slot(E.e[j].z);
+        }
+      };
+      slots(0, P4);
+      if (past4 || any) slots(P4, P6);
+      if (past6 || any) slots(P6, P);
+      if (any || S.nt > 0) {
+        slot(E.t.x);
+        slot(E.t.z);
+      }
+      mode = bad ? kSlow : any || S.nt > 0 ? kOlder : past6 ? kUpTo8 : past4 ? kUpTo6 : kUpTo4;
     };
 
-    // Inflow of a resolved slice: the terms of each row in order.  A value is the
-    // ring's or, OLD, the early-loaded one; the other of the two is +0, so their
-    // bits are joined.
-    auto gather = [&](const Slice<GN>& S, const Entries& E, auto old_c, float* acc) {
-      constexpr bool OLD = decltype(old_c)::value;
-      auto join = [&](float x, float y) {
-        return OLD ? __int_as_float(__float_as_int(x) | __float_as_int(y)) : x;
-      };
-      auto part = [&](auto j0_c, auto j1_c) {
-        constexpr int J0 = decltype(j0_c)::value, J1 = decltype(j1_c)::value;
-        float v[2 * (J1 - J0)][GN];
+    // Inflow of a resolved slice, the terms of each row in order: its first J1 pairs, every
+    // read issued before the first is used.  OLD: a value is the ring's or the early-loaded
+    // one; the other of the two is +0, so their bits are joined.
+    auto join = [&](auto old_c, float x, float y) {
+      return decltype(old_c)::value ? __int_as_float(__float_as_int(x) | __float_as_int(y)) : x;
+    };
+    auto gather = [&](const Entries<P>& E, auto old_c, auto j0_c, auto j1_c, float* acc) {
+      constexpr int J0 = decltype(j0_c)::value, J1 = decltype(j1_c)::value;
+      float v[2 * (J1 - J0)][GN];
 #pragma unroll
-        for (int j = J0; j < J1; ++j) {
-          lds_read<GN>(E.e[j].x, v[2 * (j - J0)]);
-          lds_read<GN>(E.e[j].z, v[2 * (j - J0) + 1]);
-        }
+      for (int j = J0; j < J1; ++j) {
+        lds_read<GN>(E.e[j].x, v[2 * (j - J0)]);
+        lds_read<GN>(E.e[j].z, v[2 * (j - J0) + 1]);
+      }
 #pragma unroll
-        for (int q = 2 * J0; q < 2 * J1; ++q) {
-          const float w = __int_as_float(q & 1 ? E.e[q / 2].w : E.e[q / 2].y);
+      for (int q = 2 * J0; q < 2 * J1; ++q) {
+        const float w = __int_as_float(q & 1 ? E.e[q / 2].w : E.e[q / 2].y);
 #pragma unroll
-          for (int g = 0; g < GN; ++g) acc[g] = __builtin_fmaf(w, join(v[q - 2 * J0][g], f[q][g]), acc[g]);
-        }
-      };
-      part(std::integral_constant<int, 0>{}, std::integral_constant<int, 4>{});
-      if (S.n4 > 0) part(std::integral_constant<int, 4>{}, std::integral_constant<int, 6>{});
-      if (S.n6 > 0) part(std::integral_constant<int, 6>{}, std::integral_constant<int, 8>{});
+        for (int g = 0; g < GN; ++g) acc[g] = __builtin_fmaf(w, join(old_c, v[q - 2 * J0][g], f[q][g]), acc[g]);
+      }
+    };
+    constexpr std::integral_constant<int, 0> c0{};
+    constexpr std::integral_constant<int, P4> c4{};
+    constexpr std::integral_constant<int, P6> c6{};
+    constexpr std::integral_constant<int, P> c8{};
+    constexpr std::false_type ring{};
+    constexpr std::true_type older{};
+    // kOlder: in two halves (the registers do not hold all values at once)
+    auto gather_older = [&](const Slice<GN>& S, const Entries<P>& E, float* acc) {
+      gather(E, older, c0, c4, acc);
+      if constexpr (P > 4) gather(E, older, c4, c8, acc);
       if (S.nt > 0) {
         // pairs past the registers: lane i holds pair i of them; each column's rows
         // take theirs in turn
@@ -448,10 +495,10 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
         lds_read<GN>(E.t.z, x1);
 #pragma unroll
         for (int g = 0; g < GN; ++g) {
-          x0[g] = join(x0[g], ft[0][g]);
-          x1[g] = join(x1[g], ft[1][g]);
+          x0[g] = join(older, x0[g], ft[0][g]);
+          x1[g] = join(older, x1[g], ft[1][g]);
         }
-        for (int j = kPairs, at = 0; at < S.nt; ++j) {
+        for (int j = P, at = 0; at < S.nt; ++j) {
           const bool has = S.len > 2 * j;
           const uint64_t m = __ballot(has);
           const int from = at + rank_in(m);
@@ -468,10 +515,12 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
     };
 
     // The same sum straight from memory (after the wait for the stores of the
-    // earlier levels).
-    auto gather_slow = [&](const Slice<GN>& S, float* acc) {
+    // earlier levels), of slice `at`.
+    auto gather_slow = [&](int at, const Slice<GN>& S, float* acc) {
       wait_count(s_done + 1, S.dep, seen_st, a.flag);
-      const __amdgpu_buffer_rsrc_t ent = rsrc(a.ent + S.base, 16 * (int64_t)S.np);
+      Slice<GN> R0;  // (the place of the entries is not kept up to here)
+      take_info(at, load_info(at), R0);
+      const __amdgpu_buffer_rsrc_t ent = rsrc(a.ent + R0.base, 16 * (int64_t)R0.np);
       const uint32_t lo4 = 4u * (uint32_t)(max(S.lim - R, 0) + 1);
       int off = 0;
       for (int j = 0;; ++j) {
@@ -505,7 +554,7 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
     // issued after them are counted exactly, and nothing later waits for them).
     auto consume_old = [&]() {
 #pragma unroll
-      for (int q = 0; q < 2 * kPairs; ++q)
+      for (int q = 0; q < 2 * P; ++q)
 #pragma unroll
         for (int g = 0; g < GN; ++g) asm volatile("" : "+v"(f[q][g]));
 #pragma unroll
@@ -515,8 +564,8 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
     // One turn: slice S0 (entries E resolved) is solved, S1 (entries N in flight)
     // is resolved, S2's entries are loaded into E, and the loads of the
     // following slices are issued.
-    int i = wave;
-    auto turn = [&](Entries& E, Entries& N) {
+
+    auto turn = [&](Entries<P>& E, Entries<P>& N) {
       consume_old();
       // ring slot of the lane's result: the sink for lanes without a task and for
       // positions of a level wider than the ring that a later one of the level reuses
@@ -528,14 +577,17 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
       float acc[GN], v[GN];
 #pragma unroll
       for (int g = 0; g < GN; ++g) acc[g] = 0.0f;
-      if (bad) gather_slow(S0, acc);
-      else if (any) gather(S0, E, std::true_type{}, acc);
-      else gather(S0, E, std::false_type{}, acc);
+      if (P > 4 && mode == kUpTo6) gather(E, ring, c0, c6, acc);
+      else if (mode == kUpTo4) gather(E, ring, c0, c4, acc);
+      else if (P > 6 && mode == kUpTo8) gather(E, ring, c0, c8, acc);
+      else if (mode == kOlder) gather_older(S0, E, acc);
+      else gather_slow(i, S0, acc);
       const int n0 = S0.cnt > 0 ? 1 : 0;  // (past the wavefront's last slice a turn has no task)
 #pragma unroll
       for (int g = 0; g < GN; ++g) v[g] = __fdiv_rn(__fadd_rn(acc[g], S0.src[g]), S0.den[g]);
       lds_write<GN>(at, v);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      // (LDS operations of a wavefront are performed in order: no wait between the two)
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       if (lane < n0) __hip_atomic_fetch_add(s_done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       __builtin_amdgcn_s_setprio(0);
       st_gn<GN>(v, B.outs, act ? 4u * (uint32_t)(S0.k0 * a.G) + lane4G : kOob);
@@ -576,7 +628,7 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
     load_tasks(S1);
     load_tasks(S2);
 #pragma unroll
-    for (int q = 0; q < 2 * kPairs; ++q)
+    for (int q = 0; q < 2 * P; ++q)
 #pragma unroll
       for (int g = 0; g < GN; ++g) f[q][g] = 0.0f;
 #pragma unroll
@@ -597,7 +649,8 @@ template <int GN, bool REVERSE>
 hipError_t launch_sweep_g(const SweepArgs& a, int32_t grid, int32_t block, size_t lds,
                           hipStream_t s) {
   if (block < 64 || block % 64 != 0 || block > kSweepMaxBlock(GN)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_sweep<GN, REVERSE>), dim3(grid), dim3(block), lds, s, a);
+  auto kernel = a.max_row <= 4 ? k_sweep<GN, REVERSE, 2> : k_sweep<GN, REVERSE, kPairs>;
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), lds, s, a);
   return hipGetLastError();
 }
 
@@ -1140,8 +1193,11 @@ hipError_t launch_prep(const PrepArgs& a, int32_t n_blocks, hipStream_t s) {
 
 template <int GN, bool REVERSE>
 hipError_t set_lds_g(int32_t bytes) {
-  return hipFuncSetAttribute((const void*)k_sweep<GN, REVERSE>,
-                             hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  for (auto kernel : {k_sweep<GN, REVERSE, 2>, k_sweep<GN, REVERSE, kPairs>}) {
+    const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 template <int GN>

@@ -61,3 +61,22 @@ def test_rows_of_mixed_lengths(cells, wide):
     for x, r in zip((dk, de), oracle.adjoint(w, g, g)):
         assert np.linalg.norm(x.cpu().numpy() - r) <= 1e-5 * np.linalg.norm(r)
     dag.close()
+
+
+@pytest.mark.parametrize("G", [1, 2, 3])
+@pytest.mark.parametrize("n", [3, 5, 6, 8, 9, 10, 12, 13, 14, 16, 17])
+def test_row_lengths_of_the_sweep_kernels(n, G):
+    """Rows of up to n - 1 entries: the sweep holds two or eight pairs of entries per row in
+    registers and sums the first four, six or eight."""
+    import paper_2207_12848_amd as sw
+    w = W.many_faces(n, 5, G=G, seed=200 + n)
+    dag = sw.build_dag(w["meshes"], w["dirs"])
+    k, e = (torch.tensor(np.asarray(w[x], np.float32), device="cuda") for x in ("kappa", "emission"))
+    g = torch.ones_like(k)
+    J, _, _, saved = sw.forward(dag, k, e, save_for_adjoint=True, check=True)
+    dk, de = sw.adjoint(dag, k, e, saved, g, g, check=True)
+    ref = oracle.forward(w)["J"]
+    assert np.abs(J.cpu().numpy() - ref).sum() <= 1e-5 * np.abs(ref).sum()
+    for x, r in zip((dk, de), oracle.adjoint(w, g.cpu().numpy(), g.cpu().numpy())):
+        assert np.linalg.norm(x.cpu().numpy() - r) <= 1e-5 * np.linalg.norm(r)
+    dag.close()
