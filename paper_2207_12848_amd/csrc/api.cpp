@@ -159,9 +159,14 @@ struct Buf {
   Buf& operator=(const Buf&) = delete;
   ~Buf() { release(); }
   void release() {
-    if (p) cached_free(p, bytes);
+    if (p && bytes > 0) cached_free(p, bytes);
     p = nullptr;
     bytes = 0;
+  }
+  // part of another Buf, which owns it
+  void view(void* q) {
+    release();
+    p = q;
   }
   hipError_t alloc(size_t n) {
     if (n <= bytes && p) return hipSuccess;
@@ -176,6 +181,21 @@ struct Buf {
   }
   template <class T>
   T* as() const { return static_cast<T*>(p); }
+};
+
+// Host tables gathered into one upload: add() each, then copy() and at() their places.
+struct Tables {
+  std::vector<unsigned char> host;
+  size_t add(const void* src, size_t n) {
+    const size_t o = (host.size() + 255) / 256 * 256;
+    host.resize(o + n);
+    std::memcpy(host.data() + o, src, n);
+    return o;
+  }
+  template <class T>
+  size_t add(const std::vector<T>& v) {
+    return add(v.data(), sizeof(T) * v.size());
+  }
 };
 
 // ---------------------------------------------------------------- kernel timing
@@ -244,6 +264,7 @@ struct sweep_dag_s {
   std::vector<int32_t> identity;
   Buf units_d, order_d, identity_d, sched, inv, indeg, lp, len_up, len_dn, up, dn, slice_base, sl_up, sl_dn,
       aperp, aperp_s, vol_s, bnd, edge, vol, counter, blk_base;
+  Buf tables;  // of the units and meshes (blk_base, units_d and the like are parts of it)
   int64_t n_slices = 0;  // slices of the sweep over all units (sweep::SliceRec)
   int32_t n_blocks = 0;  // 256-task blocks over all units (prep kernel)
   int32_t max_depth = 0;
@@ -254,7 +275,7 @@ struct sweep_dag_s {
   Buf flag;               // device error bits (see internal.h) raised by asynchronous calls
   // reduction tables (depend on G)
   int32_t red_G = 0, red_blocks = 0, red_cpb = 0;
-  Buf blk_mesh, blk_cell0, mesh_off_d, mesh_cells_d, mesh_blk_base;
+  Buf red_tables, blk_mesh, blk_cell0, mesh_off_d, mesh_cells_d, mesh_blk_base;
   // workspaces
   Buf xpass, lam_b;  // periodic adjoint: recomputed passes, the other pass's lambda
   Buf jpass, jscr;   // merged adjoint: every pass's direction sums; J and absorbed scratch
@@ -358,29 +379,37 @@ sweep::MeshDev mesh_dev(const sweep_mesh_t& m) {
   return d;
 }
 
-// Checks meshes [0, n) on the device; a mesh that may be wrong is checked again on the
-// host, which finds and words the error.
-sweep_status_t validate_meshes(const sweep_mesh_t* meshes, int n, hipStream_t s) {
+// What the build needs to know of the meshes' faces: the most a cell has, and the overflow
+// room for rows of cap entries (k_face_stats).
+struct FaceStats {
+  int32_t cap, n_dirs;
+  unsigned long long most, overflow;
+};
+
+// Checks meshes [0, n) on the device (if asked to; a mesh that may be wrong is checked
+// again on the host, which finds and words the error) and takes their face statistics (if
+// asked for), with one copy back.
+sweep_status_t inspect_meshes(const sweep_mesh_t* meshes, int n, bool validate, FaceStats* fs, hipStream_t s) {
   if (n <= 0) return SWEEP_OK;
-  Buf bad;
-  HIP_TRY(bad.alloc(4 * (size_t)n));
-  HIP_TRY(sweep::launch_fill_i32(bad.as<int32_t>(), n, 0, s));
-  for (int m = 0; m < n; ++m) HIP_TRY(sweep::launch_check_mesh(mesh_dev(meshes[m]), bad.as<int32_t>() + m, s));
-  std::vector<int32_t> b(n);
-  HIP_TRY(hipMemcpyAsync(b.data(), bad.p, 4 * (size_t)n, hipMemcpyDeviceToHost, s));
+  Buf buf;  // two 64-bit statistics, then a flag per mesh
+  const size_t words = 4 + (size_t)n;
+  HIP_TRY(buf.alloc(4 * words));
+  HIP_TRY(sweep::launch_fill_i32(buf.as<int32_t>(), (int64_t)words, 0, s));
+  for (int m = 0; m < n; ++m) {
+    if (validate) HIP_TRY(sweep::launch_check_mesh(mesh_dev(meshes[m]), buf.as<int32_t>() + 4 + m, s));
+    if (fs != nullptr)
+      HIP_TRY(sweep::launch_face_stats(meshes[m].face_ptr, meshes[m].n_cells, fs->cap, fs->n_dirs,
+                                       buf.as<unsigned long long>(), s));
+  }
+  std::vector<int32_t> b(words);
+  HIP_TRY(hipMemcpyAsync(b.data(), buf.p, 4 * words, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   for (int m = 0; m < n; ++m)
-    if (b[m] != 0) ST_TRY(validate_mesh_host(meshes[m], m));
-  return SWEEP_OK;
-}
-
-// Per-mesh first cell and cell count on the device (for the reductions).
-sweep_status_t ensure_mesh_tables(sweep_dag_t d) {
-  if (d->mesh_off_d.p) return SWEEP_OK;
-  HIP_TRY(d->mesh_off_d.alloc(4 * d->mesh_off.size()));
-  HIP_TRY(d->mesh_cells_d.alloc(4 * d->mesh_cells.size()));
-  HIP_TRY(hipMemcpy(d->mesh_off_d.p, d->mesh_off.data(), 4 * d->mesh_off.size(), hipMemcpyHostToDevice));
-  HIP_TRY(hipMemcpy(d->mesh_cells_d.p, d->mesh_cells.data(), 4 * d->mesh_cells.size(), hipMemcpyHostToDevice));
+    if (b[4 + m] != 0) ST_TRY(validate_mesh_host(meshes[m], m));
+  if (fs != nullptr) {
+    std::memcpy(&fs->most, b.data(), 8);
+    std::memcpy(&fs->overflow, b.data() + 2, 8);
+  }
   return SWEEP_OK;
 }
 
@@ -397,12 +426,14 @@ sweep_status_t ensure_reduce_tables(sweep_dag_t d, int32_t G) {
     }
   }
   mbb[d->n_meshes] = (int32_t)bm.size();
-  HIP_TRY(d->blk_mesh.alloc(bm.size() * 4));
-  HIP_TRY(d->blk_cell0.alloc(bc.size() * 4));
-  HIP_TRY(d->mesh_blk_base.alloc(mbb.size() * 4));
-  HIP_TRY(hipMemcpy(d->blk_mesh.p, bm.data(), bm.size() * 4, hipMemcpyHostToDevice));
-  HIP_TRY(hipMemcpy(d->blk_cell0.p, bc.data(), bc.size() * 4, hipMemcpyHostToDevice));
-  HIP_TRY(hipMemcpy(d->mesh_blk_base.p, mbb.data(), mbb.size() * 4, hipMemcpyHostToDevice));
+  Tables tab;
+  const size_t o_mesh = tab.add(bm), o_cell = tab.add(bc), o_base = tab.add(mbb);
+  HIP_TRY(d->red_tables.alloc(tab.host.size()));
+  HIP_TRY(hipMemcpy(d->red_tables.p, tab.host.data(), tab.host.size(), hipMemcpyHostToDevice));
+  unsigned char* const tables = d->red_tables.as<unsigned char>();
+  d->blk_mesh.view(tables + o_mesh);
+  d->blk_cell0.view(tables + o_cell);
+  d->mesh_blk_base.view(tables + o_base);
   HIP_TRY(d->partial.alloc(bm.size() * (size_t)G * kNPart * sizeof(double)));
   d->red_G = G;
   d->red_blocks = (int32_t)bm.size();
@@ -861,11 +892,11 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
     // (an invalid mesh before this one is reported first)
     if (M.n_cells < 1 || M.n_half_faces < 1 || !M.face_ptr || !M.cell_volume || !M.face_nbr ||
         !M.face_area || !M.face_normal) {
-      if (validate) ST_TRY(validate_meshes(meshes, m, s));
+      if (validate) ST_TRY(inspect_meshes(meshes, m, true, nullptr, s));
       return fail(SWEEP_ERR_INVALID_ARG, "mesh %d: missing arrays, no cells or no faces", m);
     }
     if (scheme == SWEEP_SCHEME_ALIGNED && !M.face_twin) {
-      if (validate) ST_TRY(validate_meshes(meshes, m, s));
+      if (validate) ST_TRY(inspect_meshes(meshes, m, true, nullptr, s));
       return fail(SWEEP_ERR_INVALID_ARG, "mesh %d: the aligned transport scheme needs face_twin", m);
     }
     D->mesh_off.push_back((int32_t)off);
@@ -873,11 +904,19 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
     if (M.face_shift) D->has_shift = true;
     off += M.n_cells;
     if (off > INT32_MAX / 2) {
-      if (validate) ST_TRY(validate_meshes(meshes, m + 1, s));
+      if (validate) ST_TRY(inspect_meshes(meshes, m + 1, true, nullptr, s));
       return fail(SWEEP_ERR_INVALID_ARG, "too many cells");
     }
   }
-  if (validate) ST_TRY(validate_meshes(meshes, n_meshes, s));
+  // downwind rows are 16 entries wide (one 64-byte line segment each, so the
+  // whole row arrives with one line); longer lists continue in an overflow pool
+  // of fixed size.  If the pool runs out, the counts are redone with rows of
+  // kRowCap entries and a pool sized for every cell with more faces than that
+  // ((faces + 2) ints per direction).
+  constexpr int kRowNarrow = 16;
+  constexpr int kRowCap = 32;
+  FaceStats fs{kRowCap, n_dirs, 0, 0};
+  ST_TRY(inspect_meshes(meshes, n_meshes, validate != 0, &fs, s));
   D->mesh_off.push_back((int32_t)off);
   D->C_total = off;
   D->T = off * n_dirs;
@@ -907,28 +946,8 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   // cell-order tile tables (tiles never straddle meshes)
   std::vector<int32_t> cbm, cbc;
   int max_faces = 1, max_cells = 1;
-  // downwind rows are 16 entries wide (one 64-byte line segment each, so the
-  // whole row arrives with one line); longer lists continue in an overflow pool
-  // of fixed size.  If the pool runs out, the counts are redone with rows of
-  // kRowCap entries and a pool sized for every cell with more faces than that
-  // ((faces + 2) ints per direction).
-  constexpr int kRowNarrow = 16;
-  constexpr int kRowCap = 32;
-  int64_t ovf_cap = 2;
-  {
-    // face statistics on the device (one small copy back)
-    Buf fstat;
-    HIP_TRY(fstat.alloc(16));
-    HIP_TRY(hipMemsetAsync(fstat.p, 0, 16, s));
-    for (int m = 0; m < n_meshes; ++m)
-      HIP_TRY(sweep::launch_face_stats(meshes[m].face_ptr, meshes[m].n_cells, kRowCap, n_dirs,
-                                       fstat.as<unsigned long long>(), s));
-    unsigned long long fs[2] = {0, 0};
-    HIP_TRY(hipMemcpyAsync(fs, fstat.p, 16, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    max_faces = std::max<int>(max_faces, (int)fs[0]);
-    ovf_cap += (int64_t)fs[1];
-  }
+  max_faces = std::max<int>(max_faces, (int)fs.most);
+  const int64_t ovf_cap = 2 + (int64_t)fs.overflow;
   for (int m = 0; m < n_meshes; ++m) {
     for (int32_t c = 0; c < D->mesh_cells[m]; c += sweep::kTileCellsHost) {
       cbm.push_back(m);
@@ -970,20 +989,30 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
       fo += meshes[m].n_half_faces;
     }
   }
-  Buf cblk_mesh_d, cblk_c0_d, dnw, stats_d, meshes_d, dirs_d, rowlen_dn, cnt, depth_d, err_d, nsl_d, np_up, np_dn, pb_up, pb_dn, scan_tmp;
-  HIP_TRY(meshes_d.alloc(sizeof(sweep::MeshDev) * n_meshes));
-  HIP_TRY(dirs_d.alloc(sizeof(double) * 3 * n_dirs));
-  HIP_TRY(D->blk_base.alloc(sizeof(int32_t) * (n_units + 1)));
+  Buf dnw, rowlen_dn, cnt, np_up, np_dn, pb_up, pb_dn, scan_tmp;
+  // the host's tables in one upload (the units, without their depths yet, last: with the
+  // two schedules of the units behind them they go up once more at the end)
+  Tables tab;
+  const size_t o_cbm = tab.add(cbm), o_cbc = tab.add(cbc), o_md = tab.add(md);
+  const size_t o_dirs = tab.add(dirs, sizeof(double) * 3 * n_dirs), o_blk = tab.add(blk_base);
+  const size_t o_off = tab.add(D->mesh_off), o_cells = tab.add(D->mesh_cells), o_units = tab.add(D->units);
+  const size_t o_order = sizeof(Unit) * n_units;  // behind the units
+  HIP_TRY(D->tables.alloc(o_units + o_order + 2 * sizeof(int32_t) * (size_t)n_units));
+  HIP_TRY(hipMemcpyAsync(D->tables.p, tab.host.data(), tab.host.size(), hipMemcpyHostToDevice, s));
+  unsigned char* const tables = D->tables.as<unsigned char>();
+  D->blk_base.view(tables + o_blk);
+  D->mesh_off_d.view(tables + o_off);
+  D->mesh_cells_d.view(tables + o_cells);
+  D->units_d.view(tables + o_units);
+  D->order_d.view(tables + o_units + o_order);
+  D->identity_d.view(tables + o_units + o_order + sizeof(int32_t) * n_units);
   D->n_blocks = n_blocks;
-  HIP_TRY(D->units_d.alloc(sizeof(Unit) * n_units));
-  HIP_TRY(cblk_mesh_d.alloc(4 * cbm.size()));
-  HIP_TRY(cblk_c0_d.alloc(4 * cbc.size()));
-  HIP_TRY(hipMemcpyAsync(cblk_mesh_d.p, cbm.data(), 4 * cbm.size(), hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(cblk_c0_d.p, cbc.data(), 4 * cbc.size(), hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(meshes_d.p, md.data(), sizeof(sweep::MeshDev) * n_meshes, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(dirs_d.p, dirs, sizeof(double) * 3 * n_dirs, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(D->blk_base.p, blk_base.data(), sizeof(int32_t) * (n_units + 1), hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(D->units_d.p, D->units.data(), sizeof(Unit) * n_units, hipMemcpyHostToDevice, s));
+  // the counts' and levels' totals and flags in one place, cleared and read back together:
+  // [entries up, down (64 bits)] [longest row up, down] [large tasks] [overflow]
+  // [cycle flag, unused] [depth of every unit] [slices of every unit]
+  Buf words;
+  HIP_TRY(words.alloc(4 * (10 + 2 * (size_t)n_units)));
+  int32_t* const w = words.as<int32_t>();
   HIP_TRY(D->indeg.alloc(4 * T));
   HIP_TRY(rowlen_dn.alloc(4 * T));
   HIP_TRY(D->aperp.alloc(4 * T));
@@ -994,33 +1023,23 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   HIP_TRY(D->inv.alloc(4 * T));
   HIP_TRY(D->sched.alloc(4 * T));
   HIP_TRY(D->lp.alloc(4 * (T + 2 * (int64_t)n_units)));
-  HIP_TRY(depth_d.alloc(4 * n_units));
-  HIP_TRY(err_d.alloc(8));
-  HIP_TRY(sweep::launch_fill_i32(err_d.as<int32_t>(), 2, 0, s));
-  Buf dn_ovf, dn_ovf_top;
-  HIP_TRY(dn_ovf_top.alloc(4));
-  Buf ent_tot;  // row entries of all tasks (sizes the row arrays before the schedule exists)
-  HIP_TRY(ent_tot.alloc(16));
-  Buf big, big_top;  // tasks whose upwind count does not fit a 4-bit counter
+  Buf dn_ovf;
+  Buf big;  // tasks whose upwind count does not fit a 4-bit counter
   HIP_TRY(big.alloc(8 * T));
-  HIP_TRY(big_top.alloc(4));
-  HIP_TRY(sweep::launch_fill_i32(big_top.as<int32_t>(), 1, 0, s));
-  HIP_TRY(stats_d.alloc(8));
-  HIP_TRY(sweep::launch_fill_i32(stats_d.as<int32_t>(), 2, 0, s));
   sweep::DagBuildArgs a{};
   a.units = D->units_d.as<Unit>();
   a.n_units = n_units;
   a.D = n_dirs;
-  a.cblk_mesh = cblk_mesh_d.as<int32_t>();
-  a.cblk_c0 = cblk_c0_d.as<int32_t>();
+  a.cblk_mesh = reinterpret_cast<int32_t*>(tables + o_cbm);
+  a.cblk_c0 = reinterpret_cast<int32_t*>(tables + o_cbc);
   a.max_faces = max_faces;
-  a.dn_ovf_top = dn_ovf_top.as<int32_t>();
+  a.dn_ovf_top = w + 7;
   a.big = big.as<int64_t>();
-  a.big_top = big_top.as<int32_t>();
-  a.ent_tot = ent_tot.as<unsigned long long>();
-  a.stats = stats_d.as<int32_t>();
-  a.meshes = meshes_d.as<sweep::MeshDev>();
-  a.dirs = dirs_d.as<double>();
+  a.big_top = w + 6;
+  a.ent_tot = reinterpret_cast<unsigned long long*>(w);
+  a.stats = w + 4;
+  a.meshes = reinterpret_cast<sweep::MeshDev*>(tables + o_md);
+  a.dirs = reinterpret_cast<double*>(tables + o_dirs);
   a.eps = eps;
   a.scheme = scheme;
   a.n_aligned = n_aligned;
@@ -1036,8 +1055,9 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   a.inv = D->inv.as<int32_t>();
   a.sched = D->sched.as<int32_t>();
   a.lp = D->lp.as<int32_t>();
-  a.depth = depth_d.as<int32_t>();
-  a.err = err_d.as<int32_t>();
+  a.err = w + 8;
+  a.depth = w + 10;
+  a.n_unit_slices = w + 10 + n_units;
   int lds_limit = 65536;
   (void)hipDeviceGetAttribute(&lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, D->device);
   int32_t stats[2] = {0, 0};
@@ -1047,10 +1067,7 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
     HIP_TRY(dnw.alloc(4 * (size_t)T * dn_width));
     // the pool ends with room for one list that is written when it has run out
     HIP_TRY(dn_ovf.alloc(4 * (cap + max_faces + 2)));
-    HIP_TRY(sweep::launch_fill_i32(dn_ovf_top.as<int32_t>(), 1, 0, s));
-    HIP_TRY(sweep::launch_fill_i32(big_top.as<int32_t>(), 1, 0, s));
-    HIP_TRY(sweep::launch_fill_i32(stats_d.as<int32_t>(), 2, 0, s));
-    HIP_TRY(sweep::launch_fill_i32(ent_tot.as<int32_t>(), 4, 0, s));
+    HIP_TRY(sweep::launch_fill_i32(w, 10, 0, s));
     a.dn_width = dn_width;
     a.dnw = dnw.as<int32_t>();
     a.dn_ovf = dn_ovf.as<int32_t>();
@@ -1059,15 +1076,15 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
       ProfScope ps("count", s);
       HIP_TRY(sweep::launch_count(a, n_cblocks, lds_limit, s));
     }
-    int32_t top = 0;
-    int64_t tot[2] = {0, 0};
-    HIP_TRY(hipMemcpyAsync(tot, ent_tot.p, 16, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(stats, stats_d.p, 8, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(&n_big, big_top.p, 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(&top, dn_ovf_top.p, 4, hipMemcpyDeviceToHost, s));
+    int32_t got[8];
+    HIP_TRY(hipMemcpyAsync(got, w, sizeof(got), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    D->n_up = tot[0];
-    D->n_dn = tot[1];
+    std::memcpy(&D->n_up, got, 8);
+    std::memcpy(&D->n_dn, got + 2, 8);
+    stats[0] = got[4];
+    stats[1] = got[5];
+    n_big = got[6];
+    const int32_t top = got[7];
     if (top <= cap) break;
     if (dn_width >= kRowCap || attempt > 0)
       return fail(SWEEP_ERR_HIP, "downwind overflow pool exhausted (%d > %lld)", top, (long long)cap);
@@ -1077,8 +1094,6 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   HIP_TRY(D->len_dn.alloc(4 * T));
   a.len_up = D->len_up.as<int32_t>();
   a.len_dn = D->len_dn.as<int32_t>();
-  HIP_TRY(nsl_d.alloc(4 * n_units));
-  a.n_unit_slices = nsl_d.as<int32_t>();
   // Kahn counters in LDS as bytes or 4-bit fields when the mesh fits the LDS
   // (the kernel's static LDS holds two frontier copies of 2048 cells); with 4 bits the
   // rows' entries of cells with larger counts are flagged first
@@ -1106,13 +1121,12 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   HIP_TRY(sweep::launch_fill_i32(a.inv, T, -1, s));
   HIP_TRY(sweep::launch_sort_levels(a, s));
   // the depths, the slices per unit and the cycle flag
-  std::vector<int32_t> depth(n_units), nsl(n_units);
-  int32_t err = 0;
-  HIP_TRY(hipMemcpyAsync(depth.data(), depth_d.p, 4 * n_units, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(nsl.data(), nsl_d.p, 4 * n_units, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(&err, err_d.p, 4, hipMemcpyDeviceToHost, s));
+  std::vector<int32_t> levels(2 + 2 * (size_t)n_units);
+  HIP_TRY(hipMemcpyAsync(levels.data(), w + 8, 4 * levels.size(), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
-  if (err) return fail(SWEEP_ERR_CYCLE, "a dependency graph is cyclic: some tasks never become ready");
+  const int32_t* const depth = levels.data() + 2;
+  const int32_t* const nsl = depth + n_units;
+  if (levels[0] != 0) return fail(SWEEP_ERR_CYCLE, "a dependency graph is cyclic: some tasks never become ready");
   std::vector<int64_t> slice_base(n_units + 1, 0);
   for (int u = 0; u < n_units; ++u) slice_base[u + 1] = slice_base[u] + nsl[u];
   const int64_t ns = D->n_slices = slice_base[n_units];
@@ -1237,7 +1251,6 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
     D->units[u].depth = depth[u];
     D->max_depth = std::max(D->max_depth, depth[u]);
   }
-  HIP_TRY(hipMemcpyAsync(D->units_d.p, D->units.data(), sizeof(Unit) * n_units, hipMemcpyHostToDevice, s));
   // schedule of the units: deepest first
   D->order.resize(n_units);
   D->identity.resize(n_units);
@@ -1247,11 +1260,12 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
     const int64_t wy = (int64_t)D->units[y].depth * 1024 + D->units[y].n_cells / 1024;
     return wx > wy;
   });
-  HIP_TRY(D->order_d.alloc(4 * n_units));
-  HIP_TRY(D->identity_d.alloc(4 * n_units));
   HIP_TRY(D->counter.alloc(64));
-  HIP_TRY(hipMemcpyAsync(D->order_d.p, D->order.data(), 4 * n_units, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(D->identity_d.p, D->identity.data(), 4 * n_units, hipMemcpyHostToDevice, s));
+  std::vector<unsigned char> final_units(o_order + 2 * sizeof(int32_t) * (size_t)n_units);
+  std::memcpy(final_units.data(), D->units.data(), o_order);
+  std::memcpy(final_units.data() + o_order, D->order.data(), sizeof(int32_t) * n_units);
+  std::memcpy(final_units.data() + o_order + sizeof(int32_t) * n_units, D->identity.data(), sizeof(int32_t) * n_units);
+  HIP_TRY(hipMemcpyAsync(tables + o_units, final_units.data(), final_units.size(), hipMemcpyHostToDevice, s));
   {
     // LDS a sweep workgroup may use: the device limit less the kernel's static LDS
     int lds_max = 65536;
@@ -1444,7 +1458,6 @@ sweep_status_t sweep_forward(sweep_dag_t d, int32_t G, const float* kappa, const
   auto pass_slot = [&](int ps) -> float* {
     return (float*)saved + DCG + (int64_t)p.n_scat * CG + (int64_t)ps * DCG;
   };
-  ST_TRY(ensure_mesh_tables(d));
   HIP_TRY(d->tden.alloc(4 * (size_t)d->T * G));
   HIP_TRY(d->tsrc.alloc(4 * (size_t)d->T * G));
   HIP_TRY(d->crec.alloc(8 * (size_t)d->C_total * G));
@@ -1604,7 +1617,6 @@ sweep_status_t sweep_adjoint(sweep_dag_t d, int32_t G, const float* kappa,
   // (x^{P-1} first, the others after the checkpoints), earlier iterations'
   // are recomputed into phi_a (x^{P-1}) and xpass (the others)
   const int P = merge ? std::max(p.n_pbc, p.n_scat) : periodic ? p.n_pbc : 1;
-  ST_TRY(ensure_mesh_tables(d));
   const bool direct = reduce_direct(d, G);
   if (P > 1 || !direct) HIP_TRY(d->lam.alloc(4 * DCG));
   HIP_TRY(d->gsrc.alloc(4 * CG));
