@@ -1007,11 +1007,11 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   D->order_d.view(tables + o_units + o_order);
   D->identity_d.view(tables + o_units + o_order + sizeof(int32_t) * n_units);
   D->n_blocks = n_blocks;
-  // the counts' and levels' totals and flags in one place, cleared and read back together:
-  // [entries up, down (64 bits)] [longest row up, down] [large tasks] [overflow]
-  // [cycle flag, unused] [depth of every unit] [slices of every unit]
-  Buf words;
-  HIP_TRY(words.alloc(4 * (10 + 2 * (size_t)n_units)));
+  // the counts' and levels' totals and flags in one place, cleared and read back together;
+  // the two that tasks raise one by one have cache lines of their own
+  enum { kEntries = 0, kLongest = 4, kBig = 32, kOverflow = 64, kCycle = 96, kDepth = 98 };  // words
+  Buf words;  // (behind the depths: the slices of every unit)
+  HIP_TRY(words.alloc(4 * (kDepth + 2 * (size_t)n_units)));
   int32_t* const w = words.as<int32_t>();
   HIP_TRY(D->indeg.alloc(4 * T));
   HIP_TRY(rowlen_dn.alloc(4 * T));
@@ -1024,8 +1024,16 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   HIP_TRY(D->sched.alloc(4 * T));
   HIP_TRY(D->lp.alloc(4 * (T + 2 * (int64_t)n_units)));
   Buf dn_ovf;
-  Buf big;  // tasks whose upwind count does not fit a 4-bit counter
-  HIP_TRY(big.alloc(8 * T));
+  int lds_limit = 65536;
+  (void)hipDeviceGetAttribute(&lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, D->device);
+  // Kahn counters in LDS as bytes or 4-bit fields when the mesh fits the LDS
+  // (the kernel's static LDS holds two frontier copies of 2048 cells); with 4 bits the
+  // rows' entries of cells with larger counts are flagged first, from a list of them
+  const bool lds_fits = sweep::kahn_lds_bytes(4, max_cells) + 17 * 1024 <= (size_t)lds_limit;
+  const bool size_fits_bytes = sweep::kahn_lds_bytes(8, max_cells) + 17 * 1024 <= (size_t)lds_limit;
+  const bool list_big = lds_fits && kahn_counters != 2 && !(size_fits_bytes && max_faces <= 254);
+  Buf big;
+  if (list_big) HIP_TRY(big.alloc(8 * T));
   sweep::DagBuildArgs a{};
   a.units = D->units_d.as<Unit>();
   a.n_units = n_units;
@@ -1033,11 +1041,11 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   a.cblk_mesh = reinterpret_cast<int32_t*>(tables + o_cbm);
   a.cblk_c0 = reinterpret_cast<int32_t*>(tables + o_cbc);
   a.max_faces = max_faces;
-  a.dn_ovf_top = w + 7;
-  a.big = big.as<int64_t>();
-  a.big_top = w + 6;
-  a.ent_tot = reinterpret_cast<unsigned long long*>(w);
-  a.stats = w + 4;
+  a.dn_ovf_top = w + kOverflow;
+  a.big = big.as<int64_t>();  // (nullptr: not listed)
+  a.big_top = w + kBig;
+  a.ent_tot = reinterpret_cast<unsigned long long*>(w + kEntries);
+  a.stats = w + kLongest;
   a.meshes = reinterpret_cast<sweep::MeshDev*>(tables + o_md);
   a.dirs = reinterpret_cast<double*>(tables + o_dirs);
   a.eps = eps;
@@ -1055,11 +1063,9 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   a.inv = D->inv.as<int32_t>();
   a.sched = D->sched.as<int32_t>();
   a.lp = D->lp.as<int32_t>();
-  a.err = w + 8;
-  a.depth = w + 10;
-  a.n_unit_slices = w + 10 + n_units;
-  int lds_limit = 65536;
-  (void)hipDeviceGetAttribute(&lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, D->device);
+  a.err = w + kCycle;
+  a.depth = w + kDepth;
+  a.n_unit_slices = w + kDepth + n_units;
   int32_t stats[2] = {0, 0};
   int32_t n_big = 0;
   for (int attempt = 0;; ++attempt) {
@@ -1067,7 +1073,7 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
     HIP_TRY(dnw.alloc(4 * (size_t)T * dn_width));
     // the pool ends with room for one list that is written when it has run out
     HIP_TRY(dn_ovf.alloc(4 * (cap + max_faces + 2)));
-    HIP_TRY(sweep::launch_fill_i32(w, 10, 0, s));
+    HIP_TRY(sweep::launch_fill_i32(w, kDepth, 0, s));
     a.dn_width = dn_width;
     a.dnw = dnw.as<int32_t>();
     a.dn_ovf = dn_ovf.as<int32_t>();
@@ -1076,15 +1082,15 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
       ProfScope ps("count", s);
       HIP_TRY(sweep::launch_count(a, n_cblocks, lds_limit, s));
     }
-    int32_t got[8];
+    int32_t got[kOverflow + 1];
     HIP_TRY(hipMemcpyAsync(got, w, sizeof(got), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    std::memcpy(&D->n_up, got, 8);
-    std::memcpy(&D->n_dn, got + 2, 8);
-    stats[0] = got[4];
-    stats[1] = got[5];
-    n_big = got[6];
-    const int32_t top = got[7];
+    std::memcpy(&D->n_up, got + kEntries, 8);
+    std::memcpy(&D->n_dn, got + kEntries + 2, 8);
+    stats[0] = got[kLongest];
+    stats[1] = got[kLongest + 1];
+    n_big = got[kBig];
+    const int32_t top = got[kOverflow];
     if (top <= cap) break;
     if (dn_width >= kRowCap || attempt > 0)
       return fail(SWEEP_ERR_HIP, "downwind overflow pool exhausted (%d > %lld)", top, (long long)cap);
@@ -1094,11 +1100,7 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   HIP_TRY(D->len_dn.alloc(4 * T));
   a.len_up = D->len_up.as<int32_t>();
   a.len_dn = D->len_dn.as<int32_t>();
-  // Kahn counters in LDS as bytes or 4-bit fields when the mesh fits the LDS
-  // (the kernel's static LDS holds two frontier copies of 2048 cells); with 4 bits the
-  // rows' entries of cells with larger counts are flagged first
-  const bool lds_fits = sweep::kahn_lds_bytes(4, max_cells) + 17 * 1024 <= (size_t)lds_limit;
-  const bool bytes_fit = stats[0] <= 254 && sweep::kahn_lds_bytes(8, max_cells) + 17 * 1024 <= (size_t)lds_limit;
+  const bool bytes_fit = size_fits_bytes && stats[0] <= 254;
   if (kahn_counters == 1 && !lds_fits)
     return fail(SWEEP_ERR_UNSUPPORTED, "the counters of a %d-cell mesh do not fit in LDS", max_cells);
   const bool lds_cnt = kahn_counters == 2 ? false : lds_fits;
@@ -1122,7 +1124,7 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   HIP_TRY(sweep::launch_sort_levels(a, s));
   // the depths, the slices per unit and the cycle flag
   std::vector<int32_t> levels(2 + 2 * (size_t)n_units);
-  HIP_TRY(hipMemcpyAsync(levels.data(), w + 8, 4 * levels.size(), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipMemcpyAsync(levels.data(), w + kCycle, 4 * levels.size(), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   const int32_t* const depth = levels.data() + 2;
   const int32_t* const nsl = depth + n_units;

@@ -24,8 +24,7 @@ namespace sweep {
 namespace {
 
 constexpr int kCountBlock = 256;
-// k_count: 512 threads (16 directions of a 32-cell tile at a time) so that two
-// workgroups with their face tiles and staged rows keep 16 wavefronts per CU
+// k_count_aligned and k_count_in: 512 threads, 16 directions of a 32-cell tile at a time
 constexpr int kCountThreads = 512;
 constexpr int kTileCells = 32;  // cells per tile of the cell-order kernels
 __device__ __forceinline__ double orient(double ox, double oy, double oz, const double* n) {
@@ -103,16 +102,33 @@ __device__ __forceinline__ FaceTile stage_tile(const MeshDev& M, int c0, unsigne
 }
 
 // Per task: upwind/downwind counts, Aperp = sum of outflow w, boundary outflow
-// weights, the signed weight of every face and the fixed-width row of downwind
-// cells.  A row holds
-// dn_width entries padded with -1; a task with more downwind cells keeps
-// dn_width - 1 of them and stores -(o + 2) in the last slot, o being the
-// offset in dn_ovf of [count, rest of the list].  A thread handles one cell of
-// the tile for one direction; the rows of kCountBlock / kTileCells directions
-// are assembled in LDS and written out as contiguous blocks (STAGE), or
-// written straight to global memory.
+// weights, the signed weight of every face (NaN: neither inflow nor outflow) and
+// the fixed-width row of downwind cells.  A row holds dn_width entries padded
+// with -1; a task with more downwind cells keeps dn_width - 1 of them and stores
+// -(o + 2) in the last slot, o being the offset in dn_ovf of [count, rest of the
+// list].
+//
+// A workgroup takes a tile of kTileCells cells through the directions, kTileDirs at
+// a time: first a thread per face works out its FP64 orientation and signed weight
+// for those directions, then a thread per (cell, direction) goes over its faces'
+// weights.  The weights of a tile lie in LDS in between (from memory when it has more
+// than kTileFaces faces per cell).  The rows are assembled in LDS and written out as
+// contiguous blocks (STAGE), or written straight to global memory.
+//
+// Bound by its writes, in runs of 128 bytes to 2 KB (3.2 GB at 64^3 cells and 84
+// directions, 2.4 TB/s; a third of the issue slots are used).  64^3 cells, 84 directions:
+// 1.33 ms, and 1.45 with the orientations taken in the cells' loop from normals in LDS and
+// again for the weights; 2 M cells: 11.7 ms, and 13.3.
+constexpr int kTileDirs = 8;
+constexpr int kTileThreads = kTileDirs * kTileCells;
+constexpr int kTileCap = kTileCells * kTileFaces;
+
+size_t count_tile_bytes() {
+  return sizeof(int64_t) * (kTileCells + 2) + sizeof(int32_t) * kTileCap + sizeof(float) * kTileDirs * kTileCap;
+}
+
 template <bool STAGE>
-__global__ __launch_bounds__(kCountThreads) void k_count(DagBuildArgs a) {
+__global__ __launch_bounds__(kTileThreads) void k_count(DagBuildArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_max[2];
   __shared__ unsigned long long s_ent[2];
@@ -120,114 +136,115 @@ __global__ __launch_bounds__(kCountThreads) void k_count(DagBuildArgs a) {
     s_max[threadIdx.x] = 0;
     s_ent[threadIdx.x] = 0ull;
   }
-  const int m = a.cblk_mesh[blockIdx.x];
+  const int tile = xcd_block(blockIdx.x, gridDim.x);
+  const int m = a.cblk_mesh[tile];
   const MeshDev M = a.meshes[m];
-  const FaceTile T = stage_tile(M, a.cblk_c0[blockIdx.x], smem);
   const int W = a.dn_width;
-  int32_t* srow = reinterpret_cast<int32_t*>(smem + tile_lds_bytes());
-  __syncthreads();
+  const int c0 = a.cblk_c0[tile];
+  const int nc = min(kTileCells, M.n_cells - c0);
+  const int64_t f0 = M.face_ptr[c0];
+  const int nf = (int)(M.face_ptr[c0 + nc] - f0);
+  int64_t* s_fp = reinterpret_cast<int64_t*>(smem);
+  int32_t* s_code = reinterpret_cast<int32_t*>(s_fp + kTileCells + 2);
+  int32_t* srow = s_code + (kTileDirs + 1) * kTileCap;
+  // directions at a time: fewer for a tile of many faces
+  const int kd = min(kTileDirs, (kTileDirs + 1) * kTileCap / nf - 1);
+  const bool in_lds = kd > 0;
+  const int nd = in_lds ? kd : kTileDirs;
+  float* s_w = reinterpret_cast<float*>(s_code + nf);  // [direction][face]
+  for (int i = threadIdx.x; i <= nc; i += kTileThreads) s_fp[i] = M.face_ptr[c0 + i] - f0;
+  if (in_lds)
+    for (int f = threadIdx.x; f < nf; f += kTileThreads) s_code[f] = M.fcode[f0 + f];
   const int ci = threadIdx.x % kTileCells;
   const int dj = threadIdx.x / kTileCells;
-  constexpr int kDirs = kCountThreads / kTileCells;
-  const int c = T.c0 + ci;
-  const int nc = T.cend - T.c0;
-  const bool cell = c < T.cend;
-  const int fb = cell ? (int)T.fp[ci] : 0, fe = cell ? (int)T.fp[ci + 1] : 0;
+  const int c = c0 + ci;
+  const bool cell = ci < nc;
+  float* const wface = a.wface + (int64_t)a.D * M.face_off + f0;
   int mi = 0, mo = 0;
   unsigned long long eu = 0, ed = 0;  // row entries of the thread's tasks
-  auto run = [&](const double* nrm, const double* area, const int32_t* nbr, const int8_t* shift) {
-    for (int d0 = 0; d0 < a.D; d0 += kDirs) {
-      const int d = d0 + dj;
-      if (cell && d < a.D) {
-        const double ox = a.dirs[3 * d], oy = a.dirs[3 * d + 1], oz = a.dirs[3 * d + 2];
-        const int64_t t = a.units[m * a.D + d].task_base + c;
-        int32_t* row = STAGE ? srow + threadIdx.x * W : a.dnw + t * W;  // LDS: [dj][ci][W]
-        int32_t* ovf = nullptr;
-        int nup = 0, ndn = 0;
-        double ap = 0.0, wall = 0.0, per = 0.0;
-        for (int f = fb; f < fe; ++f) {
-          const double* n = nrm + 3 * f;
-          const double sv = orient(ox, oy, oz, n);
-          const int nb = nbr[f];
-          const bool periodic = shift != nullptr && shift[f] != 0;
-          const float w = face_w(area[f], sv);
-          if (sv > a.eps) {
-            ap += w;
-            if (nb < 0) wall += w;
-            else if (periodic) {
-              per += w;
-            } else {
-              if (ndn < W) {
-                row[ndn] = nb;
-              } else {
-                if (ndn == W) {  // the row is full: continue in an overflow list
-                  const int need = (fe - fb) + 2;
-                  const int o = atomicAdd(a.dn_ovf_top, need);
-                  // a pool that has run out gets the list in its spare end (the
-                  // host sees the count past the capacity and redoes the counts)
-                  ovf = a.dn_ovf + (o + need <= a.dn_ovf_cap ? o : a.dn_ovf_cap);
-                  ovf[1] = row[W - 1];
-                  row[W - 1] = -(o + 2);
-                }
-                ovf[1 + ndn - (W - 1)] = nb;
-              }
-              ++ndn;
-            }
-          } else if (sv < -a.eps && nb >= 0 && !periodic) {
-            ++nup;
-          }
-        }
-        if (ovf != nullptr) ovf[0] = ndn - (W - 1);
-        if (nup >= 15) a.big[atomicAdd(a.big_top, 1)] = t;  // counter too large for 4 bits
-        for (int q = ndn; q < W; ++q) row[q] = -1;
-        a.indeg[t] = nup;
-        a.rowlen_dn[t] = ndn;
-        a.aperp[t] = (float)ap;
-        a.bnd[t] = make_float2((float)wall, (float)per);
-        mi = max(mi, nup);
-        mo = max(mo, ndn);
-        eu += (unsigned long long)nup;
-        ed += (unsigned long long)ndn;
-      }
-      // the signed weight of every face of the tile for these directions (NaN:
-      // neither inflow nor outflow), consecutive threads on consecutive faces
-      const int nft = (int)T.fp[nc];
-      for (int i = threadIdx.x; i < kDirs * nft; i += kCountThreads) {
-        const int j = i / nft, f = i - j * nft;
-        const int dd = d0 + j;
-        if (dd < a.D) {
-          const double sv = orient(a.dirs[3 * dd], a.dirs[3 * dd + 1], a.dirs[3 * dd + 2], nrm + 3 * f);
-          const float w = face_w(area[f], sv);
-          a.wface[(int64_t)a.D * M.face_off + (int64_t)dd * M.n_faces + T.f0 + f] =
-              sv > a.eps ? w : (sv < -a.eps ? -w : __int_as_float(0x7fc00000));
-        }
-      }
-      if (STAGE) {
-        __syncthreads();
-        // the tile's rows of direction d0 + j are nc * W consecutive ints of dnw
-        const int per4 = nc * W / 4;
-        for (int i = threadIdx.x; i < kDirs * per4; i += kCountThreads) {
-          const int j = i / per4, r = i - j * per4;
-          if (d0 + j < a.D) {
-            const int64_t tb = a.units[m * a.D + d0 + j].task_base;
-            reinterpret_cast<int4*>(a.dnw + (tb + T.c0) * W)[r] =
-                reinterpret_cast<const int4*>(srow + j * kTileCells * W)[r];
-          }
-        }
-        __syncthreads();
+  for (int d0 = 0; d0 < a.D; d0 += nd) {
+    for (int f = threadIdx.x; f < nf; f += kTileThreads) {
+      const double n[3] = {M.face_normal[3 * (f0 + f)], M.face_normal[3 * (f0 + f) + 1], M.face_normal[3 * (f0 + f) + 2]};
+      const double A = M.face_area[f0 + f];
+#pragma unroll
+      for (int j = 0; j < kTileDirs; ++j) {
+        const int d = d0 + j;
+        if (d >= a.D || j >= nd) break;
+        const double sv = orient(a.dirs[3 * d], a.dirs[3 * d + 1], a.dirs[3 * d + 2], n);
+        const float w = face_w(A, sv);
+        const float x = sv > a.eps ? w : (sv < -a.eps ? -w : __int_as_float(0x7fc00000));
+        wface[(int64_t)d * M.n_faces + f] = x;
+        if (in_lds) s_w[j * nf + f] = x;
       }
     }
-  };
-  if (T.in_lds) {
-    constexpr int cap = kTileCells * kTileFaces;
-    const double* nrm = reinterpret_cast<const double*>(T.fp + kTileCells + 1);
-    const double* area = nrm + 3 * cap;
-    const int32_t* nbr = reinterpret_cast<const int32_t*>(area + cap);
-    const int8_t* shift = reinterpret_cast<const int8_t*>(nbr + cap);
-    run(nrm, area, nbr, shift);
-  } else {
-    run(M.face_normal + 3 * T.f0, M.face_area + T.f0, M.face_nbr + T.f0,
-        M.face_shift != nullptr ? M.face_shift + T.f0 : nullptr);
+    __syncthreads();
+    const int d = d0 + dj;
+    const bool mine = dj < nd && d < a.D;
+    if (cell && mine) {
+      const int fb = (int)s_fp[ci], fe = (int)s_fp[ci + 1];
+      const int64_t t = a.units[m * a.D + d].task_base + c;
+      int32_t* row = STAGE ? srow + threadIdx.x * W : a.dnw + t * W;  // LDS: [dj][ci][W]
+      int32_t* ovf = nullptr;
+      int nup = 0, ndn = 0;
+      double ap = 0.0, wall = 0.0, per = 0.0;
+      auto run = [&](auto* weights, auto* codes) {
+        for (int f = fb; f < fe; ++f) {
+          const float w = weights[f];
+          const int code = codes[f];
+          if (isnan(w)) continue;
+          if (signbit(w)) {
+            nup += code >= 0 ? 1 : 0;
+            continue;
+          }
+          ap += w;
+          if (code == -1) {
+            wall += w;
+          } else if (code < -1) {
+            per += w;
+          } else {
+            if (ndn < W) {
+              row[ndn] = code;
+            } else {
+              if (ndn == W) {  // the row is full: continue in an overflow list
+                const int need = (fe - fb) + 2;
+                const int o = atomicAdd(a.dn_ovf_top, need);
+                // a pool that has run out gets the list in its spare end (the
+                // host sees the count past the capacity and redoes the counts)
+                ovf = a.dn_ovf + (o + need <= a.dn_ovf_cap ? o : a.dn_ovf_cap);
+                ovf[1] = row[W - 1];
+                row[W - 1] = -(o + 2);
+              }
+              ovf[1 + ndn - (W - 1)] = code;
+            }
+            ++ndn;
+          }
+        }
+      };
+      if (in_lds) run(s_w + dj * nf, s_code);
+      else run(wface + (int64_t)d * M.n_faces, M.fcode + f0);
+      if (ovf != nullptr) ovf[0] = ndn - (W - 1);
+      if (nup >= 15 && a.big != nullptr) a.big[atomicAdd(a.big_top, 1)] = t;  // counter too large for 4 bits
+      for (int q = ndn; q < W; ++q) row[q] = -1;
+      a.indeg[t] = nup;
+      a.rowlen_dn[t] = ndn;
+      a.aperp[t] = (float)ap;
+      a.bnd[t] = make_float2((float)wall, (float)per);
+      mi = max(mi, nup);
+      mo = max(mo, ndn);
+      eu += (unsigned long long)nup;
+      ed += (unsigned long long)ndn;
+    }
+    __syncthreads();
+    if (STAGE) {
+      // the tile's rows of direction d0 + j are nc * W consecutive ints of dnw; 32
+      // threads write one direction's
+      if (mine) {
+        int4* out = reinterpret_cast<int4*>(a.dnw + (a.units[m * a.D + d].task_base + c0) * W);
+        const int4* in = reinterpret_cast<const int4*>(srow + dj * kTileCells * W);
+        for (int r = ci; r < nc * W / 4; r += kTileCells) out[r] = in[r];
+      }
+      // (the next rows are written behind the next barrier)
+    }
   }
   atomicMax(&s_max[0], mi);
   atomicMax(&s_max[1], mo);
@@ -386,7 +403,7 @@ __global__ __launch_bounds__(kCountThreads) void k_count_in(DagBuildArgs a) {
         if (M.face_shift == nullptr || M.face_shift[f] == 0) ++nup;
       }
       const int64_t t = a.units[m * a.D + d].task_base + c;
-      if (nup >= 15) a.big[atomicAdd(a.big_top, 1)] = t;  // counter too large for 4 bits
+      if (nup >= 15 && a.big != nullptr) a.big[atomicAdd(a.big_top, 1)] = t;  // counter too large for 4 bits
       a.indeg[t] = nup;
       mi = max(mi, nup);
       eu += (unsigned long long)nup;
@@ -1487,12 +1504,6 @@ inline unsigned grid1d(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 }  // namespace
 
-// LDS of k_count: the face tile, then (when it fits) one downwind row per thread.
-size_t count_lds_bytes(int max_faces, int dn_width) {
-  (void)max_faces;
-  return tile_lds_bytes();
-}
-
 hipError_t launch_count(const DagBuildArgs& a, int32_t n_cblocks, int32_t lds_limit, hipStream_t s) {
   if (n_cblocks <= 0) return hipSuccess;
   if (a.scheme == SWEEP_SCHEME_ALIGNED) {
@@ -1506,15 +1517,14 @@ hipError_t launch_count(const DagBuildArgs& a, int32_t n_cblocks, int32_t lds_li
     hipLaunchKernelGGL(k_count_in, dim3(n_cblocks), dim3(kCountThreads), 0, s, a);
     return hipGetLastError();
   }
-  const size_t tile = tile_lds_bytes();
-  const size_t staged = tile + (size_t)kCountThreads * a.dn_width * 4;
+  const size_t tile = count_tile_bytes();
+  const size_t staged = tile + (size_t)kTileThreads * a.dn_width * 4;
   const bool stage = staged <= (size_t)lds_limit - 64;
   const size_t lds = stage ? staged : tile;
-  const void* fn = stage ? (const void*)k_count<true> : (const void*)k_count<false>;
-  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  auto kernel = stage ? k_count<true> : k_count<false>;
+  hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  if (stage) hipLaunchKernelGGL(k_count<true>, dim3(n_cblocks), dim3(kCountThreads), lds, s, a);
-  else hipLaunchKernelGGL(k_count<false>, dim3(n_cblocks), dim3(kCountThreads), lds, s, a);
+  hipLaunchKernelGGL(kernel, dim3(n_cblocks), dim3(kTileThreads), lds, s, a);
   return hipGetLastError();
 }
 

@@ -314,7 +314,6 @@ hipError_t launch_count_slices(const DagBuildArgs& a, hipStream_t s);
 hipError_t launch_slices(const DagBuildArgs& a, hipStream_t s);
 hipError_t launch_gather_tasks(const DagBuildArgs& a, hipStream_t s);
 hipError_t launch_mark(const DagBuildArgs& a, int32_t n_big, hipStream_t s);
-size_t count_lds_bytes(int max_faces, int dn_width);
 // out[2u], out[2u + 1]: upwind and downwind row entries of unit u
 hipError_t launch_unit_entries(const Unit* units, int32_t n_units, const int32_t* len_up,
                                const int32_t* len_dn, int64_t* out, hipStream_t s);
