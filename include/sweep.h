@@ -299,13 +299,12 @@ sweep_status_t sweep_dag_level_widths(sweep_dag_t dag, int32_t mesh, int64_t* wi
 
 /* Autotuner of the sweep's launch shape: times `reps` forward sweeps (after
  * one untimed sweep) of the batched form for every candidate number of threads
- * per workgroup (256, 512, 1024) and LDS ring capacity (a quarter to twice the
- * default, those that fit the LDS), with HIP events on `stream`, and writes
+ * per workgroup (256, 512, 1024) and LDS ring capacity (a quarter, half and all
+ * of the largest that fits the LDS), with HIP events on `stream`, and writes
  * into `best` a copy of `opts` (NULL: defaults) with the fastest `block` and
  * `ring`, and into `best_ms` its time per sweep.  The DAG keeps nothing: pass
- * `best` to sweep_forward / sweep_adjoint.  Results of different shapes agree
- * to FP32 rounding (the ring capacity changes the order in which a task's
- * ring misses are added).  Synchronises `stream`.
+ * `best` to sweep_forward / sweep_adjoint.  Every shape gives the same bits.
+ * Synchronises `stream`.
  * Errors: INVALID_ARG, UNSUPPORTED (nothing fits), HIP. */
 sweep_status_t sweep_tune(sweep_dag_t dag, int32_t G, const float* kappa, const float* emission,
                           const sweep_fwd_opts_t* opts, int32_t reps, sweep_fwd_opts_t* best,

@@ -56,7 +56,7 @@ __device__ __forceinline__ int xcd_block(int b, int nb) {
 
 // The cell-order kernel stages a tile of kTileCells consecutive cells' faces
 // in LDS with coalesced loads (room for kTileFaces faces per cell on average,
-// above the ~15.5 of a Voronoi cell and small enough for three workgroups per CU;
+// above the ~15.5 of a Voronoi cell and small enough for several workgroups per CU;
 // a tile with more faces is read from global memory instead); the workgroup
 // then covers every direction, 32 consecutive lanes handling the tile's cells
 // for one direction.
@@ -1159,7 +1159,8 @@ __global__ __launch_bounds__(256) void k_count_slices(DagBuildArgs a) {
 
 // The slice tables of both walks (SliceRec but for the entries' place, which
 // k_fill adds), one workgroup per unit: a scan over the levels gives each its
-// first slice.
+// first slice.  A chain of scans over 256 levels at a time: 23 us at 64^3 cells x 84
+// directions (about 1,000 levels).
 constexpr int kSlicesBlock = 256;
 __global__ __launch_bounds__(kSlicesBlock) void k_slices(DagBuildArgs a) {
   __shared__ int s_scan[kSlicesBlock];
@@ -1202,7 +1203,8 @@ __global__ __launch_bounds__(kSlicesBlock) void k_slices(DagBuildArgs a) {
 
 // Per task in schedule order: row lengths, Aperp and the cell's volume; per
 // slice: its rows' entry pairs (the input of the scan that places them).  One
-// wavefront per slice.
+// wavefront per slice.  Bound by four gathers per task, a line request each: 64^3 cells
+// x 84 directions 0.55 ms (22 M tasks), 2 M cells 4.8 ms.
 __global__ __launch_bounds__(kCountBlock) void k_gather_tasks(DagBuildArgs a) {
   const int64_t i = (int64_t)xcd_block(blockIdx.x, gridDim.x) * (kCountBlock / 64) + (threadIdx.x >> 6);
   if (i >= a.n_slices) return;

@@ -92,8 +92,8 @@ struct DagBuildArgs {
   int32_t* indeg;
   int32_t* rowlen_dn;
   float* aperp;
-  float* aperp_s;  // the same per task in schedule order (written by k_gather_len)
-  float* vol_s;    // the cell's volume per task, schedule order (written by k_gather_len)
+  float* aperp_s;  // the same per task in schedule order (written by k_gather_tasks)
+  float* vol_s;    // the cell's volume per task, schedule order (written by k_gather_tasks)
   // per (direction, face) of every mesh, at D * face_off + d * n_faces + f: the face
   // weight w = A |Omega . n| rounded once to FP32 from FP64, with the face's class
   // in its sign: outflow +w, inflow -w, neither NaN
