@@ -1031,7 +1031,9 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   // rows' entries of cells with larger counts are flagged first, from a list of them
   const bool lds_fits = sweep::kahn_lds_bytes(4, max_cells) + 17 * 1024 <= (size_t)lds_limit;
   const bool size_fits_bytes = sweep::kahn_lds_bytes(8, max_cells) + 17 * 1024 <= (size_t)lds_limit;
-  const bool list_big = lds_fits && kahn_counters != 2 && !(size_fits_bytes && max_faces <= 254);
+  // (or, with the hash table, of cells with more dependencies than its counts hold)
+  const bool lds_counters = lds_fits && kahn_counters != 2;
+  const bool list_big = lds_counters ? !(size_fits_bytes && max_faces <= 254) : max_faces > sweep::kHashMaxDeps;
   Buf big;
   if (list_big) HIP_TRY(big.alloc(8 * T));
   sweep::DagBuildArgs a{};
@@ -1043,6 +1045,7 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   a.max_faces = max_faces;
   a.dn_ovf_top = w + kOverflow;
   a.big = big.as<int64_t>();  // (nullptr: not listed)
+  a.big_min = lds_counters ? 15 : sweep::kHashMaxDeps + 1;
   a.big_top = w + kBig;
   a.ent_tot = reinterpret_cast<unsigned long long*>(w + kEntries);
   a.stats = w + kLongest;
@@ -1103,9 +1106,10 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   const bool bytes_fit = size_fits_bytes && stats[0] <= 254;
   if (kahn_counters == 1 && !lds_fits)
     return fail(SWEEP_ERR_UNSUPPORTED, "the counters of a %d-cell mesh do not fit in LDS", max_cells);
-  const bool lds_cnt = kahn_counters == 2 ? false : lds_fits;
+  const bool lds_cnt = lds_counters;
   // otherwise in an LDS hash table of the cells being counted, or as bytes in global memory
-  a.hash_bits = lds_cnt ? 0 : sweep::kahn_hash_bits(max_cells, stats[0]);
+  a.hash_bits = lds_cnt ? 0 : sweep::kahn_hash_bits(max_cells);
+  a.hash_big = a.hash_bits > 0 && n_big > 0;
   D->max_up = stats[0];
   D->max_dn = stats[1];
   if (!lds_cnt && stats[0] > 254)
@@ -1113,7 +1117,7 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
                 "(at most 254 when the mesh's counters do not fit in LDS)", stats[0]);
   D->kahn_lds = lds_cnt ? 1 : 0;
   const int lds_bits = !lds_cnt ? 0 : bytes_fit ? 8 : 4;
-  if (lds_bits == 4) HIP_TRY(sweep::launch_mark(a, n_big, s));
+  if (lds_bits == 4 || a.hash_big) HIP_TRY(sweep::launch_mark(a, n_big, s));
   {
     ProfScope ps("kahn", s);
     HIP_TRY(sweep::launch_kahn(a, lds_bits, max_cells, s));

@@ -223,7 +223,7 @@ __global__ __launch_bounds__(kTileThreads) void k_count(DagBuildArgs a) {
       if (in_lds) run(s_w + dj * nf, s_code);
       else run(wface + (int64_t)d * M.n_faces, M.fcode + f0);
       if (ovf != nullptr) ovf[0] = ndn - (W - 1);
-      if (nup >= 15 && a.big != nullptr) a.big[atomicAdd(a.big_top, 1)] = t;  // counter too large for 4 bits
+      if (nup >= a.big_min && a.big != nullptr) a.big[atomicAdd(a.big_top, 1)] = t;  // count too large for its place
       for (int q = ndn; q < W; ++q) row[q] = -1;
       a.indeg[t] = nup;
       a.rowlen_dn[t] = ndn;
@@ -403,7 +403,7 @@ __global__ __launch_bounds__(kCountThreads) void k_count_in(DagBuildArgs a) {
         if (M.face_shift == nullptr || M.face_shift[f] == 0) ++nup;
       }
       const int64_t t = a.units[m * a.D + d].task_base + c;
-      if (nup >= 15 && a.big != nullptr) a.big[atomicAdd(a.big_top, 1)] = t;  // counter too large for 4 bits
+      if (nup >= a.big_min && a.big != nullptr) a.big[atomicAdd(a.big_top, 1)] = t;  // count too large for its place
       a.indeg[t] = nup;
       mi = max(mi, nup);
       eu += (unsigned long long)nup;
@@ -418,8 +418,8 @@ __global__ __launch_bounds__(kCountThreads) void k_count_in(DagBuildArgs a) {
   }
 }
 
-// Tasks with 15 or more upwind dependencies keep their counter in global
-// memory; the entries that point at them in their upwind cells' downwind rows
+// Tasks with more upwind dependencies than their counter's place holds (15 with 4-bit
+// fields) keep it in global memory; the entries that point at them in their upwind cells' downwind rows
 // get bit 30 set, so that Kahn's algorithm sends those decrements there without
 // first reading the LDS counter.  One wavefront per such task, one face per lane.
 constexpr int32_t kBigFlag = 0x40000000;
@@ -465,7 +465,7 @@ __global__ __launch_bounds__(256) void k_mark(DagBuildArgs a, int32_t n_big) {
 constexpr int kFrontierCap = 2048;  // frontier entries kept in LDS per level
 
 // Where Kahn's counters live (k_kahn).
-enum KahnMode { kKahnLds4 = 0, kKahnLds8 = 1, kKahnGlobal = 2, kKahnHash = 3 };
+enum KahnMode { kKahnLds4 = 0, kKahnLds8 = 1, kKahnGlobal = 2, kKahnHash = 3, kKahnHashBig = 4 };
 
 // The hash table of counters: a bucket is two words, four tag bytes and four
 // counts.  Cell c belongs to one bucket, and its tag c / buckets + 1 (0: free way)
@@ -473,6 +473,7 @@ enum KahnMode { kKahnLds4 = 0, kKahnLds8 = 1, kKahnGlobal = 2, kKahnHash = 3 };
 // space-filling curve) lie in different buckets.  A free way's count is kHashBias.
 constexpr int kHashBits = 14;  // at most 2^14 buckets (128 KB)
 constexpr uint32_t kHashBias = 128;
+static_assert(kHashMaxDeps < (int)kHashBias - 4, "counts stay above 0 while they count down from the bias");
 constexpr int kMissCap = 2048;  // a level's decrements that did not find their cell, listed in LDS
 
 using lds_int = int __attribute__((address_space(3)));
@@ -521,8 +522,11 @@ __device__ __forceinline__ int zero_byte(uint32_t w) {
 //               are inserted full buckets stay full and every lane of a cell comes to
 //               the same decision.  A cell whose bucket is full is decremented in
 //               global memory, where a later insertion finds its remaining count.
-//  kKahnGlobal  bytes in global memory, four to a word: cells with more dependencies
-//               than the hash table's count holds, or meshes too large for its keys.
+//  kKahnHashBig the same for meshes with a few cells of more dependencies than the
+//               table's counts hold (kHashMaxDeps): their entries are flagged beforehand
+//               (k_mark), and they are always counted in global memory.
+//  kKahnGlobal  bytes in global memory, four to a word: meshes too large for the
+//               table's keys.
 //
 // What bounds it: narrow levels, the chain from a level's barrier to the next (the
 // rows come from HBM); wider ones, the instructions of 16 wavefronts (about 90 per
@@ -534,6 +538,7 @@ __device__ __forceinline__ int zero_byte(uint32_t w) {
 // L2, made it 7 to 9 % slower.
 template <int MODE>
 __global__ __launch_bounds__(1024) void k_kahn(DagBuildArgs a) {
+  constexpr bool HASH = MODE == kKahnHash || MODE == kKahnHashBig;
   extern __shared__ __align__(16) uint32_t tab[];  // counters or hash table
   constexpr bool LDS = MODE == kKahnLds4 || MODE == kKahnLds8;
   constexpr int B = MODE == kKahnLds4 ? 4 : 8;  // bits of a counter in LDS, 32 / B to a word
@@ -542,7 +547,7 @@ __global__ __launch_bounds__(1024) void k_kahn(DagBuildArgs a) {
   constexpr uint32_t M = (1u << B) - 1u;
   __shared__ int fr[2][kFrontierCap + 64];  // and 64 dummy words
   __shared__ int s_cnt[3];
-  __shared__ int misses[MODE == kKahnHash ? kMissCap + 64 : 1];
+  __shared__ int misses[HASH ? kMissCap + 64 : 1];
   __shared__ int s_nmiss[2];
   const Unit U = a.units[blockIdx.x];
   const int C = U.n_cells;
@@ -582,7 +587,7 @@ __global__ __launch_bounds__(1024) void k_kahn(DagBuildArgs a) {
       tab[wi] = v;
     }
   }
-  if (MODE == kKahnHash) {
+  if (HASH) {
     for (uint32_t i = tid; i < 2u << hbits; i += nthr) tab[i] = (i & 1u) ? kHashBias * 0x01010101u : 0u;
     if (tid < 64) tab[(2u << hbits) + tid] = 0u;  // dummy words
   }
@@ -701,7 +706,7 @@ __global__ __launch_bounds__(1024) void k_kahn(DagBuildArgs a) {
       const uint32_t sb = (uint32_t)(nb & (PW - 1)) * B;
       return ((atomicSub(&tab[nb >> LPW], 1u << sb) >> sb) & M) == 1u;
     }
-    if (MODE == kKahnGlobal) return dec_global(nb);
+    if (MODE == kKahnGlobal || (MODE == kKahnHashBig && (e & kBigFlag) != 0)) return dec_global(nb);
     return dec_new(nb);
   };
 
@@ -815,7 +820,15 @@ __global__ __launch_bounds__(1024) void k_kahn(DagBuildArgs a) {
         for (int i = 0; i < 4; ++i)
           ready[i] = xs[i] >= 0 && ((old[i] >> ((uint32_t)(xs[i] & 3) * 8u)) & 255u) == 1u;
       } else {
-        // entries in the table are decremented, the others listed
+        // entries in the table are decremented, the others listed (flagged ones: at once)
+        int x[4];
+        bool any_big = false;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const bool big = MODE == kKahnHashBig && xs[i] >= kBigFlag;
+          x[i] = big ? -1 : xs[i];
+          any_big |= big;
+        }
         uint32_t bk[4];
         uint2 w[4];
         int at[4];
@@ -823,19 +836,24 @@ __global__ __launch_bounds__(1024) void k_kahn(DagBuildArgs a) {
         uint32_t old[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          bk[i] = bucket_of(max(xs[i], 0));
+          bk[i] = bucket_of(max(x[i], 0));
           w[i] = *reinterpret_cast<const uint2*>(tab + bk[i]);
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          at[i] = zero_byte(w[i].x ^ tags_of(max(xs[i], 0)));
-          const bool hit = xs[i] >= 0 && at[i] >= 0;
-          miss[i] = xs[i] >= 0 && at[i] < 0;
+          at[i] = zero_byte(w[i].x ^ tags_of(max(x[i], 0)));
+          const bool hit = x[i] >= 0 && at[i] >= 0;
+          miss[i] = x[i] >= 0 && at[i] < 0;
           // (lanes without a hit: their own dummy word; one address would serialise them)
           old[i] = atomicSub(&tab[hit ? bk[i] + 1 : (2u << hbits) + lane], hit ? 1u << (at[i] & 31) : 0u);
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) ready[i] = ((old[i] >> (at[i] & 31)) & 255u) == 1u;  // (no hit: 0)
+        if (MODE == kKahnHashBig && __ballot(any_big) != 0ull) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (xs[i] >= kBigFlag) ready[i] = dec_global(xs[i] & ~kBigFlag);
+        }
         unsigned long long m[4];
         int total = 0;
 #pragma unroll
@@ -851,14 +869,14 @@ __global__ __launch_bounds__(1024) void k_kahn(DagBuildArgs a) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int q = base + rank_in(m[i]);
-            misses[miss[i] && q < kMissCap ? q : kMissCap + lane] = xs[i];
+            misses[miss[i] && q < kMissCap ? q : kMissCap + lane] = x[i];
             base += __popcll(m[i]);
           }
           if (!fits) {  // past the list: at once
             base -= total;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-              if (miss[i] && base + rank_in(m[i]) >= kMissCap) ready[i] = dec_new(xs[i]);
+              if (miss[i] && base + rank_in(m[i]) >= kMissCap) ready[i] = dec_new(x[i]);
               base += __popcll(m[i]);
             }
           }
@@ -890,7 +908,7 @@ __global__ __launch_bounds__(1024) void k_kahn(DagBuildArgs a) {
 #pragma unroll
       for (int b = 0; b < kBatch; ++b) v[b] = load(tid + b * nwork);
     }
-    if (MODE == kKahnHash) {
+    if (HASH) {
       // the frontier's cells leave the table (while the rows arrive)
       if (!writer)
         for (int i = tid; i < n; i += nwork) remove(cell_at(i));
@@ -911,7 +929,7 @@ __global__ __launch_bounds__(1024) void k_kahn(DagBuildArgs a) {
       }
     }
     __syncthreads();
-    if (MODE == kKahnHash) {
+    if (HASH) {
       const int nm = min(*s_miss, kMissCap);
       if (!writer)
         for (int i = tid, iw = wfirst; iw < nm; i += nwork, iw += nwork) {  // (whole wavefronts)
@@ -1592,18 +1610,20 @@ hipError_t launch_kahn(const DagBuildArgs& a, int32_t lds_bits, int32_t max_cell
   };
   if (lds_bits == 8) return launch(k_kahn<kKahnLds8>, kahn_lds_bytes(8, max_cells));
   if (lds_bits == 4) return launch(k_kahn<kKahnLds4>, kahn_lds_bytes(4, max_cells));
-  if (a.hash_bits > 0) return launch(k_kahn<kKahnHash>, sizeof(uint32_t) * (((size_t)2 << a.hash_bits) + 64));
+  if (a.hash_bits > 0) {
+    const size_t lds = sizeof(uint32_t) * (((size_t)2 << a.hash_bits) + 64);
+    return a.hash_big ? launch(k_kahn<kKahnHashBig>, lds) : launch(k_kahn<kKahnHash>, lds);
+  }
   return launch(k_kahn<kKahnGlobal>, 0);
 }
 
-// log2 of k_kahn's hash buckets for meshes of up to max_cells cells whose tasks have
-// at most max_indeg dependencies: at least a bucket (four ways) per 128 cells, at
-// most 2^kHashBits.  0: the table cannot hold them (tags of one byte, and counts that
-// stay above 0 while they count down from the bias).
-int kahn_hash_bits(int32_t max_cells, int32_t max_indeg) {
+// log2 of k_kahn's hash buckets for meshes of up to max_cells cells: at least a bucket
+// (four ways) per 128 cells, at most 2^kHashBits.  0: the table cannot hold them (tags of
+// one byte).
+int kahn_hash_bits(int32_t max_cells) {
   int bits = 3;
   while (bits < kHashBits && (max_cells >> bits) >= 128) ++bits;
-  return (max_cells >> bits) < 254 && max_indeg < (int)kHashBias - 4 ? bits : 0;
+  return (max_cells >> bits) < 254 ? bits : 0;
 }
 
 hipError_t launch_mark(const DagBuildArgs& a, int32_t n_big, hipStream_t s) {

@@ -65,6 +65,9 @@ struct MeshDev {
   int32_t cell_off;
 };
 
+// Dependencies that a count in k_kahn's hash table holds.
+constexpr int kHashMaxDeps = 123;
+
 struct DagBuildArgs {
   const Unit* units;
   int32_t n_units;
@@ -79,10 +82,12 @@ struct DagBuildArgs {
   const int32_t* cblk_c0;
   int32_t dn_width;          // width of the fixed-width downwind rows (4, 8, 16 or 32)
   int32_t hash_bits;         // Kahn's counters in an LDS hash table of 2^hash_bits buckets (0: not)
+  bool hash_big;           // some cells have more than kHashMaxDeps dependencies (their entries are flagged)
+  int32_t big_min;         // dependencies from which on tasks are listed in `big`
   int32_t* dn_ovf;           // overflow lists of full rows: [count, cells...]
   int32_t* dn_ovf_top;       // next free int of dn_ovf (atomic)
   int64_t dn_ovf_cap;        // ints of dn_ovf for lists (more: the pool has run out)
-  int64_t* big;              // tasks with 15 or more upwind dependencies
+  int64_t* big;              // tasks with big_min or more upwind dependencies, or nullptr
   int32_t* big_top;          // their number (atomic)
   int32_t max_faces;         // most half-faces of any cell
   int32_t* dnw;              // [T][dn_width] downwind cells of every task (-1 padded)
@@ -293,7 +298,7 @@ hipError_t launch_ion_update(const IonArgs& a, double dt, hipStream_t s);
 constexpr int kTileCellsHost = 32;  // cells per tile of the cell-order build kernels
 hipError_t launch_count(const DagBuildArgs& a, int32_t n_cblocks, int32_t lds_limit, hipStream_t s);
 constexpr int kMaxAligned = 4;  // most faces scheme (b) may share the outflow over
-int kahn_hash_bits(int32_t max_cells, int32_t max_indeg);
+int kahn_hash_bits(int32_t max_cells);
 // Dynamic LDS of k_kahn with a counter of `bits` bits per cell (and 64 dummy words).
 constexpr size_t kahn_lds_bytes(int bits, int64_t cells) { return 4 * (size_t)((cells * bits + 31) / 32 + 64); }
 // lds_bits: bits of the counters in LDS (8 or 4), 0: in a hash table or in global memory
