@@ -359,7 +359,9 @@ hipError_t set_sweep_lds_limit(int32_t bytes);
 // registers (128 VGPRs each), more groups need the 256 VGPRs of 512 threads.
 constexpr int kSweepMaxBlock(int gn) { return gn == 1 ? 1024 : 512; }
 // Dynamic LDS bytes of a sweep workgroup: the ring of `ring` results x gn FP32, a
-// slot of zeros and a sink, then the counters.
-constexpr size_t sweep_lds_bytes(int32_t gn, int32_t ring) { return (size_t)gn * (ring + 2) * sizeof(float) + 16; }
+// slot of zeros and a sink, then the counters (two, and one per wavefront).
+constexpr size_t sweep_lds_bytes(int32_t gn, int32_t ring) {
+  return (size_t)gn * (ring + 2) * sizeof(float) + sizeof(int32_t) * (2 + 1024 / 64);
+}
 
 }  // namespace sweep

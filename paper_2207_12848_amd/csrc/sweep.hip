@@ -230,6 +230,22 @@ __device__ __forceinline__ void wait_count(lds_int* counter, int need, int& seen
   }
 }
 
+// Waits until every wavefront has stored its slices before `need`: next[w] is the first
+// slice of wavefront w (of nw) that is not stored yet.  All of these slices are counted by
+// then, and a counted slice waits for nothing before its store.
+__device__ __forceinline__ void wait_stored(lds_int* next, int nw, int need, int32_t* flag) {
+  int w = rank_in(~0ull);  // the lane
+  asm volatile("" : "+v"(w));  // (computed here, or it takes registers of the common path)
+  for (int it = 0;; ++it) {
+    const int n = w < nw ? __hip_atomic_load(next + w, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) : INT_MAX;
+    if (__ballot(n < need) == 0ull) return;
+    if (it >= kSpinLimit) {
+      atomicOr(flag, kErrStall);
+      return;
+    }
+  }
+}
+
 // One workgroup sweeps one (mesh, direction, group chunk) work item at a time.
 // The tasks of every level are cut into slices of at most 64 (k_slices), one
 // task per lane, and slice i belongs to wavefront i mod (wavefronts).  A slice
@@ -262,9 +278,12 @@ __device__ __forceinline__ void wait_count(lds_int* counter, int need, int& seen
 // the positions whose slices may have been counted but not yet stored (one slice
 // per wavefront: 64 x wavefronts).  A slice with an older result that is neither
 // (very wide levels, tiny rings), or with more row entries than the registers
-// hold, is summed after its wait straight from memory, once a second counter
-// shows the stores of the earlier levels; same terms in the same order, so every
-// path gives the same bits.
+// hold, is summed after its wait straight from memory, once every wavefront has
+// stored its slices of the earlier levels (each keeps its first slice that is not
+// stored yet in LDS.  The number of stored slices would not do: other slices of the
+// same level, which do not wait for stores, may be among them while one of an earlier
+// level is counted but not yet stored); same terms in the same order, so every path
+// gives the same bits.
 //
 // The adjoint walks the slices backwards; its rows name reversed positions, so
 // the same code serves both.
@@ -293,15 +312,16 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
   const uint32_t lane4G = 4u * (uint32_t)(lane * a.G);
   const int zero = R * GN * 4;  // the zero slot's address
   if (tid < GN) *lds_at<float>(zero + 4 * tid) = 0.0f;
-  // behind the ring, the zero slot and the sink: the counts of finished and of stored
-  // slices, the next work item
+  // behind the ring, the zero slot and the sink: the count of finished slices, the next
+  // work item, every wavefront's first slice that is not stored yet
   lds_int* s_done = lds_at<int>(zero + 2 * GN * 4);
-  lds_int* s_unit = s_done + 2;
+  lds_int* s_unit = s_done + 1;
+  lds_int* s_next = s_done + 2;
   for (int it = 0;; ++it) {
     __syncthreads();  // the previous item's counters and ring are no longer read
+    if (tid < nw) s_next[tid] = tid;
     if (tid == 0) {
-      s_done[0] = 0;
-      s_done[1] = 0;
+      *s_done = 0;
       if (a.work_counter != nullptr) *s_unit = atomicAdd(a.work_counter, 1);
     }
     __syncthreads();
@@ -378,7 +398,7 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
     // one of those is not visible yet, or rows go on still longer
     enum { kUpTo4, kUpTo6, kUpTo8, kOlder, kSlow };
     int mode = kUpTo4;
-    int seen = 0, seen_st = 0;           // the counters as last read
+    int seen = 0;                        // the count as last read
     int vis = 0;                         // results before this position are in out_s
 
     // Window test, early loads of the older results and LDS offsets of a slice
@@ -517,7 +537,7 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
     // The same sum straight from memory (after the wait for the stores of the
     // earlier levels), of slice `at`.
     auto gather_slow = [&](int at, const Slice<GN>& S, float* acc) {
-      wait_count(s_done + 1, S.dep, seen_st, a.flag);
+      wait_stored(s_next, nw, S.dep, a.flag);
       Slice<GN> R0;  // (the place of the entries is not kept up to here)
       take_info(at, load_info(at), R0);
       const __amdgpu_buffer_rsrc_t ent = rsrc(a.ent + R0.base, 16 * (int64_t)R0.np);
@@ -593,7 +613,9 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
       st_gn<GN>(v, B.outs, act ? 4u * (uint32_t)(S0.k0 * a.G) + lane4G : kOob);
       int n1 = n0;
       asm volatile("" : "+v"(n1));  // (its own condition, or the compiler splits the code between the two)
-      if (lane < n1) __hip_atomic_fetch_add(s_done + 1, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+      int mine = wave;
+      asm volatile("" : "+s"(mine));  // (its address is not kept in a register)
+      if (lane < n1) __hip_atomic_store(s_next + mine, i + nw, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
       vis = S0.ks - lag;
       Slice<GN> next = S2;
       resolve(S1, N, [&]() {
