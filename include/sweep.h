@@ -108,7 +108,10 @@ enum { SWEEP_SCHEME_AREA = 0, SWEEP_SCHEME_ALIGNED = 1 };
 
 typedef struct {
   double eps_tie;   /* |Omega.n| <= eps_tie: the face carries nothing (default 1e-12) */
-  int32_t validate; /* 1: check the mesh and directions on the host first (default 1) */
+  int32_t validate; /* 1: check the meshes first (default 1).  0: what they hold is the
+                       caller's responsibility; a face with a negative or undefined area
+                       leaves its cell without a valid Aperp, which sweep calls report
+                       like other invalid inputs the kernels see */
   int32_t kahn_counters; /* where the level computation keeps its per-cell dependency
                             counters: 0 = LDS when the largest mesh fits (4 bits per
                             cell), else global memory; 1 = LDS (UNSUPPORTED if the mesh

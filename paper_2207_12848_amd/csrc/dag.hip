@@ -43,6 +43,17 @@ __device__ __forceinline__ double orient(double ox, double oy, double oz, const 
 // exactly what its neighbour receives.
 __device__ __forceinline__ float face_w(double A, double s) { return (float)(A * fabs(s)); }
 
+// Signed weight of a face: its class, by the orientation, in the sign (outflow +, inflow -,
+// also of a zero weight); kNoFace, a NaN, for neither.  A negative or undefined area (meshes
+// that were not checked) gives another NaN with the class in its sign: the face still orders
+// its cells, and makes its cell's Aperp NaN, which the sweep reports.
+constexpr int kNoFace = 0x7fc00000, kBadFace = 0x7fc00001;
+__device__ __forceinline__ float signed_w(double A, double s, double eps) {
+  if (!(s > eps || s < -eps)) return __int_as_float(kNoFace);
+  return copysignf(A >= 0.0 ? face_w(A, s) : __int_as_float(kBadFace), (float)s);
+}
+__device__ __forceinline__ bool carries(float w) { return __float_as_int(w) != kNoFace; }
+
 // Workgroups are dispatched round-robin over the 8 XCDs, each with its own L2
 // cache: this renumbering gives each XCD one contiguous range of the grid, so
 // the workgroups an XCD runs together belong to few units and share those
@@ -171,8 +182,7 @@ __global__ __launch_bounds__(kTileThreads) void k_count(DagBuildArgs a) {
         const int d = d0 + j;
         if (d >= a.D || j >= nd) break;
         const double sv = orient(a.dirs[3 * d], a.dirs[3 * d + 1], a.dirs[3 * d + 2], n);
-        const float w = face_w(A, sv);
-        const float x = sv > a.eps ? w : (sv < -a.eps ? -w : __int_as_float(0x7fc00000));
+        const float x = signed_w(A, sv, a.eps);
         wface[(int64_t)d * M.n_faces + f] = x;
         if (in_lds) s_w[j * nf + f] = x;
       }
@@ -191,9 +201,10 @@ __global__ __launch_bounds__(kTileThreads) void k_count(DagBuildArgs a) {
         for (int f = fb; f < fe; ++f) {
           const float w = weights[f];
           const int code = codes[f];
-          if (isnan(w)) continue;
+          if (!carries(w)) continue;
           if (signbit(w)) {
             nup += code >= 0 ? 1 : 0;
+            if (isnan(w)) ap = w;
             continue;
           }
           ap += w;
@@ -326,7 +337,8 @@ __global__ __launch_bounds__(kCountThreads) void k_count_aligned(DagBuildArgs a)
           top_insert(bs, bf, sv, f);
         }
       }
-      const int n = min(nout, a.n_aligned);
+      // (an undefined Aperp, which the sweep reports, leaves no shares to carry)
+      const int n = isnan(ap) ? 0 : min(nout, a.n_aligned);
       const float wb = n > 0 ? (float)(ap / n) : 0.0f;
       int32_t* row = a.dnw + t * W;
       int ndn = 0;
@@ -335,7 +347,7 @@ __global__ __launch_bounds__(kCountThreads) void k_count_aligned(DagBuildArgs a)
         bool chosen = false;
 #pragma unroll
         for (int k = 0; k < kMaxAligned; ++k) chosen |= k < n && bf[k] == f;
-        wf[f] = chosen ? wb : __int_as_float(0x7fc00000);
+        wf[f] = chosen ? wb : __int_as_float(kNoFace);
         if (!chosen) continue;
         const int nb = nbr[f];
         if (nb < 0) wall += wb;
@@ -1351,7 +1363,7 @@ __global__ __launch_bounds__(kFillBlock) __attribute__((amdgpu_waves_per_eu(5)))
       dn = has && !isnan(ws);
       w = up ? wi : ws;
     } else {
-      has = has && !isnan(ws);
+      has = has && carries(ws);
       up = has && signbit(ws);   // interior inflow
       dn = has && !signbit(ws);  // interior outflow
       w = fabsf(ws);
@@ -1533,7 +1545,7 @@ __global__ void k_pdir(DagBuildArgs a, MeshDev M, int mesh) {
       aw = isnan(ws) ? 0.0f : ws;
     } else {
       const float ws = wf[f];
-      const bool has = !isnan(ws);
+      const bool has = carries(ws);
       const bool in = has && signbit(ws);
       fw = in ? fabsf(ws) : 0.0f;
       aw = has && !in ? fabsf(ws) : 0.0f;
