@@ -413,9 +413,11 @@ sweep_status_t inspect_meshes(const sweep_mesh_t* meshes, int n, bool validate, 
   return SWEEP_OK;
 }
 
-// Reduction block tables for G groups: blocks never straddle meshes.
-sweep_status_t ensure_reduce_tables(sweep_dag_t d, int32_t G) {
+// Reduction block tables for G groups: blocks never straddle meshes.  They take the place
+// of those of another G in the order of `s`, on which an earlier call may still read these.
+sweep_status_t ensure_reduce_tables(sweep_dag_t d, int32_t G, hipStream_t s) {
   if (d->red_G == G) return SWEEP_OK;
+  d->red_G = 0;
   const int cpb = std::max(1, kRedBlock / G);
   std::vector<int32_t> bm, bc, mbb(d->n_meshes + 1, 0);
   for (int m = 0; m < d->n_meshes; ++m) {
@@ -429,7 +431,8 @@ sweep_status_t ensure_reduce_tables(sweep_dag_t d, int32_t G) {
   Tables tab;
   const size_t o_mesh = tab.add(bm), o_cell = tab.add(bc), o_base = tab.add(mbb);
   HIP_TRY(d->red_tables.alloc(tab.host.size()));
-  HIP_TRY(hipMemcpy(d->red_tables.p, tab.host.data(), tab.host.size(), hipMemcpyHostToDevice));
+  HIP_TRY(hipMemcpyAsync(d->red_tables.p, tab.host.data(), tab.host.size(), hipMemcpyHostToDevice, s));
+  HIP_TRY(hipStreamSynchronize(s));
   unsigned char* const tables = d->red_tables.as<unsigned char>();
   d->blk_mesh.view(tables + o_mesh);
   d->blk_cell0.view(tables + o_cell);
@@ -1439,7 +1442,7 @@ sweep_status_t sweep_forward(sweep_dag_t d, int32_t G, const float* kappa, const
   StreamScope stream_scope(s);
   const int64_t CG = d->C_total * G;
   const int64_t DCG = CG * d->D;
-  ST_TRY(ensure_reduce_tables(d, G));
+  ST_TRY(ensure_reduce_tables(d, G, s));
   const bool direct = reduce_direct(d, G);
   if (!saved && (n_inner > 1 || !direct)) HIP_TRY(d->phi_a.alloc(4 * DCG));
   if (periodic && n_inner > 1) HIP_TRY(d->phi_b.alloc(4 * DCG));
@@ -1629,7 +1632,7 @@ sweep_status_t sweep_adjoint(sweep_dag_t d, int32_t G, const float* kappa,
   HIP_TRY(d->dk64.alloc(8 * CG));
   HIP_TRY(d->de64.alloc(8 * CG));
   if (merge) {
-    ST_TRY(ensure_reduce_tables(d, G));
+    ST_TRY(ensure_reduce_tables(d, G, s));
     HIP_TRY(d->xpass.alloc(4 * DCG * P));
     HIP_TRY(d->jpass.alloc(4 * CG * P));
     HIP_TRY(d->jscr.alloc(8 * CG));
