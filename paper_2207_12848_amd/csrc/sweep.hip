@@ -127,6 +127,18 @@ __device__ __forceinline__ int rank_in(uint64_t m) {
   return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
+// Values of other lanes: lane `from` mod 64 (__shfl without its width, which takes
+// registers), lane `from` for a uniform `from`, the lane below.
+__device__ __forceinline__ float lane_value(float v, int from) {
+  return __int_as_float(__builtin_amdgcn_ds_bpermute(4 * from, __float_as_int(v)));
+}
+__device__ __forceinline__ float lane_scalar(float v, int from) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), from));
+}
+__device__ __forceinline__ float lane_below(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));  // wave_shr:1
+}
+
 // Entry pairs of a row held in registers, the kernel's P: kPairs (16 entries), or 2 where no
 // row of the walk is longer (regular grids, tetrahedra), which leaves out the loads and the
 // work for columns that nobody has.  128^3 lattice cells x 84 directions: 2.70 ms with 2
@@ -230,15 +242,16 @@ __device__ __forceinline__ void wait_count(lds_int* counter, int need, int& seen
   }
 }
 
-// Waits until every wavefront has stored its slices before `need`: next[w] is the first
-// slice of wavefront w (of nw) that is not stored yet.  All of these slices are counted by
-// then, and a counted slice waits for nothing before its store.
-__device__ __forceinline__ void wait_stored(lds_int* next, int nw, int need, int32_t* flag) {
-  int w = rank_in(~0ull);  // the lane
-  asm volatile("" : "+v"(w));  // (computed here, or it takes registers of the common path)
+// Waits until every wavefront has stored its slices before `need`: last[w] is the slice
+// that wavefront w (of nw) stored last.  All of these slices are counted by then, and a
+// counted slice waits for nothing before its store.
+__device__ __forceinline__ void wait_stored(lds_int* last, int nw, int lane, int need, int32_t* flag) {
+  int w = lane;
+  asm volatile("" : "+v"(w));  // (nothing of it is kept in registers of the common path)
+  w = min(w, nw - 1);          // (no branch: the turn's control flow stays uniform)
   for (int it = 0;; ++it) {
-    const int n = w < nw ? __hip_atomic_load(next + w, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) : INT_MAX;
-    if (__ballot(n < need) == 0ull) return;
+    const int next = __hip_atomic_load(last + w, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) + nw;
+    if (__ballot(next < need) == 0ull) return;
     if (it >= kSpinLimit) {
       atomicOr(flag, kErrStall);
       return;
@@ -278,9 +291,9 @@ __device__ __forceinline__ void wait_stored(lds_int* next, int nw, int need, int
 // the positions whose slices may have been counted but not yet stored (one slice
 // per wavefront: 64 x wavefronts).  A slice with an older result that is neither
 // (very wide levels, tiny rings), or with more row entries than the registers
-// hold, is summed after its wait straight from memory, once every wavefront has
-// stored its slices of the earlier levels (each keeps its first slice that is not
-// stored yet in LDS.  The number of stored slices would not do: other slices of the
+// hold, loads such results after its wait, once every wavefront has
+// stored its slices of the earlier levels (each keeps the slice that it stored last
+// in LDS.  The number of stored slices would not do: other slices of the
 // same level, which do not wait for stores, may be among them while one of an earlier
 // level is counted but not yet stored); same terms in the same order, so every path
 // gives the same bits.
@@ -313,14 +326,17 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
   const int zero = R * GN * 4;  // the zero slot's address
   if (tid < GN) *lds_at<float>(zero + 4 * tid) = 0.0f;
   // behind the ring, the zero slot and the sink: the count of finished slices, the next
-  // work item, every wavefront's first slice that is not stored yet
+  // work item, the slice that every wavefront stored last
   lds_int* s_done = lds_at<int>(zero + 2 * GN * 4);
-  lds_int* s_unit = s_done + 1;
-  lds_int* s_next = s_done + 2;
+  lds_int* s_last = s_done + 2;
+  const int my_last = zero + 2 * GN * 4 + 8 + 4 * wave;  // (its address)
   for (int it = 0;; ++it) {
     __syncthreads();  // the previous item's counters and ring are no longer read
-    if (tid < nw) s_next[tid] = tid;
-    if (tid == 0) {
+    int mine = wave, z = zero;
+    asm volatile("" : "+s"(mine), "+s"(z));  // (or addresses made of them are kept in vector registers)
+    lds_int* const s_unit = lds_at<int>(z + 2 * GN * 4) + 1;
+    if (lane == 0) s_last[mine] = mine - nw;
+    if (lane + mine == 0) {
       *s_done = 0;
       if (a.work_counter != nullptr) *s_unit = atomicAdd(a.work_counter, 1);
     }
@@ -395,12 +411,17 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
     float f[2 * P][GN], ft[2][GN];  // results from outside the window (else 0), of the slice resolved last
     // how the slice resolved last is summed: its rows have up to P4, P6 or P pairs, all in
     // the window; kOlder: some entry lies outside it, or rows go past the registers; kSlow:
-    // one of those is not visible yet, or rows go on still longer
+    // one of those is not visible yet, or rows go on still longer (not resolved: codes)
     enum { kUpTo4, kUpTo6, kUpTo8, kOlder, kSlow };
     int mode = kUpTo4;
     int seen = 0;                        // the count as last read
     int vis = 0;                         // results before this position are in out_s
 
+    // LDS address of the entry with position code x (outside the window: the zero slot).
+    auto slot = [&](int& x, uint32_t lo4) {
+      x = (uint32_t)x < lo4 ? zero : slot_of<GN>(x, mask4);
+      asm volatile("" : "+v"(x));
+    };
     // Window test, early loads of the older results and LDS offsets of a slice
     // (entries outside the window, and lanes without an entry, name the zero slot).
     auto resolve = [&](const Slice<GN>& S, Entries<P>& E, auto&& between) {
@@ -454,26 +475,23 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
 #pragma unroll
         for (int g = 0; g < GN; ++g) ft[0][g] = ft[1][g] = 0.0f;
       }
+      mode = bad ? kSlow : any || S.nt > 0 ? kOlder : past6 ? kUpTo8 : past4 ? kUpTo6 : kUpTo4;
+      if (bad) return;  // (its codes are resolved after the wait)
       // (computed now, not after the wait for the slice's turn, where they are used)
-      auto slot = [&](int& x) {
-        x = (uint32_t)x < lo4 ? zero : slot_of<GN>(x, mask4);
-        asm volatile("" : "+v"(x));
-      };
       auto slots = [&](int j0, int j1) {
 #pragma unroll
         for (int j = j0; j < j1; ++j) {
-          slot(E.e[j].x);
-          slot(E.e[j].z);
+          slot(E.e[j].x, lo4);
+          slot(E.e[j].z, lo4);
         }
       };
       slots(0, P4);
       if (past4 || any) slots(P4, P6);
       if (past6 || any) slots(P6, P);
       if (any || S.nt > 0) {
-        slot(E.t.x);
-        slot(E.t.z);
+        slot(E.t.x, lo4);
+        slot(E.t.z, lo4);
       }
-      mode = bad ? kSlow : any || S.nt > 0 ? kOlder : past6 ? kUpTo8 : past4 ? kUpTo6 : kUpTo4;
     };
 
     // Inflow of a resolved slice, the terms of each row in order: its first J1 pairs, every
@@ -522,10 +540,10 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
           const bool has = S.len > 2 * j;
           const uint64_t m = __ballot(has);
           const int from = at + rank_in(m);
-          const float w0 = __shfl(__int_as_float(E.t.y), from), w1 = __shfl(__int_as_float(E.t.w), from);
+          const float w0 = lane_value(__int_as_float(E.t.y), from), w1 = lane_value(__int_as_float(E.t.w), from);
 #pragma unroll
           for (int g = 0; g < GN; ++g) {
-            const float y0 = __shfl(x0[g], from), y1 = __shfl(x1[g], from);
+            const float y0 = lane_value(x0[g], from), y1 = lane_value(x1[g], from);
             const float s = __builtin_fmaf(w1, y1, __builtin_fmaf(w0, y0, acc[g]));
             acc[g] = has ? s : acc[g];
           }
@@ -534,35 +552,120 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
       }
     };
 
-    // The same sum straight from memory (after the wait for the stores of the
-    // earlier levels), of slice `at`.
-    auto gather_slow = [&](int at, const Slice<GN>& S, float* acc) {
-      wait_stored(s_next, nw, S.dep, a.flag);
-      Slice<GN> R0;  // (the place of the entries is not kept up to here)
-      take_info(at, load_info(at), R0);
-      const __amdgpu_buffer_rsrc_t ent = rsrc(a.ent + R0.base, 16 * (int64_t)R0.np);
+    // The same sum after the wait for the stores of the earlier levels, when every older
+    // result can be loaded, of slice `at`: the columns in registers by halves, then the pairs
+    // past them 64 at a time, the next ones on their way meanwhile.  (All pairs one after the
+    // other, from memory, took five times as long: 400 cells that all border each other x 8
+    // directions 8.9 ms, now 1.5; 8,000 cells x 24 directions with a ring of 64 results 0.93
+    // and 0.34.)
+    auto gather_slow = [&](int at, const Slice<GN>& S, Entries<P>& E, float* acc) {
+      wait_stored(s_last, nw, lane, S.dep, a.flag);
       const uint32_t lo4 = 4u * (uint32_t)(max(S.lim - R, 0) + 1);
-      int off = 0;
-      for (int j = 0;; ++j) {
-        const bool has = S.len > 2 * j;
-        const uint64_t m = __ballot(has);
-        if (m == 0ull) break;
-        const int4 e = ld_b128(ent, has ? 16u * (uint32_t)(off + rank_in(m)) : kOob, 0);
-        off += __popcll(m);
+      auto old = [&](int x, float* v) {
+        const uint32_t y = (uint32_t)x - 4u;
+        const uint32_t d = REVERSE ? 4u * (uint32_t)B.C - (uint32_t)x : y;
+        ld_gn<GN>(B.outs, y < lo4 - 4u ? d * (uint32_t)a.G : kOob, 0, v);
+      };
+      auto columns = [&](auto j0_c, auto j1_c) {
+        constexpr int J0 = decltype(j0_c)::value, N = 2 * (decltype(j1_c)::value - J0);
+        float o[N][GN], v[N][GN];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int x = h ? e.z : e.x;
-          const float w = __int_as_float(h ? e.w : e.y);
-          const bool old = has && (uint32_t)x < lo4;
-          const uint32_t d = REVERSE ? 4u * (uint32_t)B.C - (uint32_t)x : (uint32_t)x - 4u;
-          float v[GN], o[GN];
-          ld_gn<GN>(B.outs, old ? d * (uint32_t)a.G : kOob, 0, o);
-          lds_read<GN>(slot_of<GN>(x, mask4), v);
+        for (int q = 0; q < N; ++q) {
+          int& x = q & 1 ? E.e[J0 + q / 2].z : E.e[J0 + q / 2].x;
+          old(x, o[q]);
+          slot(x, lo4);
+        }
+#pragma unroll
+        for (int q = 0; q < N; ++q) lds_read<GN>(q & 1 ? E.e[J0 + q / 2].z : E.e[J0 + q / 2].x, v[q]);
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+          const float w = __int_as_float(q & 1 ? E.e[J0 + q / 2].w : E.e[J0 + q / 2].y);
+#pragma unroll
+          for (int g = 0; g < GN; ++g) acc[g] = __builtin_fmaf(w, join(older, v[q][g], o[q][g]), acc[g]);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // (or both halves' values take registers at once)
+      };
+      columns(c0, c4);
+      if constexpr (P > 4) columns(c4, c8);
+      if (S.nt > 0) {
+        const int rec = load_info(at);  // (the place of the entries is not kept up to here)
+        int4& t = E.t;
+        int j = P, first = 0;  // the column, and its first pair of the S.nt
+        for (int b = 0; b < S.nt; b += 64) {
+          float x0[GN], x1[GN], o0[GN], o1[GN];
+          old(t.x, o0);
+          old(t.z, o1);
+          slot(t.x, lo4);
+          slot(t.z, lo4);
+          lds_read<GN>(t.x, x0);
+          lds_read<GN>(t.z, x1);
+          Slice<GN> R0;
+          take_info(at, rec, R0);
+          const __amdgpu_buffer_rsrc_t ent = rsrc(a.ent + R0.base, 16 * (int64_t)R0.np);
+          int l = lane;
+          asm volatile("" : "+v"(l));  // (nothing of it is kept in registers of the common path)
+          const int at64 = R0.np - S.nt + b + 64;
+          const int4 next = ld_b128(ent, at64 + l < R0.np ? 16u * (uint32_t)(at64 + l) : kOob, 0);
 #pragma unroll
           for (int g = 0; g < GN; ++g) {
-            const float s = __builtin_fmaf(w, old ? o[g] : v[g], acc[g]);
-            acc[g] = has ? s : acc[g];
+            x0[g] = join(older, x0[g], o0[g]);
+            x1[g] = join(older, x1[g], o1[g]);
           }
+          // lane i holds pair b + i; kCols columns at a time, whose values are under way
+          // together; one that goes on behind the pairs at hand is taken up again there
+          constexpr int kCols = GN > 2 ? 2 : 4;
+          const int end = min(b + 64, S.nt);
+          int rows = __popcll(__ballot(S.len > 2 * j));
+          for (bool more = true; more && first < end && rows > 1;) {
+            float w0[kCols], w1[kCols], y0[kCols][GN], y1[kCols][GN];
+            bool in[kCols];
+#pragma unroll
+            for (int u = 0; u < kCols; ++u) {
+              const bool has = S.len > 2 * j;
+              const uint64_t m = __ballot(has);
+              const int n = __popcll(m), from = first + rank_in(m) - b;
+              in[u] = has && more && (uint32_t)from < 64u;
+              w0[u] = lane_value(__int_as_float(t.y), from);
+              w1[u] = lane_value(__int_as_float(t.w), from);
+#pragma unroll
+              for (int g = 0; g < GN; ++g) {
+                y0[u][g] = lane_value(x0[g], from);
+                y1[u][g] = lane_value(x1[g], from);
+              }
+              more = more && first + n <= end;
+              first += more ? n : 0;
+              j += more ? 1 : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < kCols; ++u)
+#pragma unroll
+              for (int g = 0; g < GN; ++g) {
+                const float s = __builtin_fmaf(w1[u], y1[u][g], __builtin_fmaf(w0[u], y0[u][g], acc[g]));
+                acc[g] = in[u] ? s : acc[g];
+              }
+            rows = __popcll(__ballot(S.len > 2 * j));
+          }
+          if (rows == 1 && first < end) {
+            // the longest row alone: its sum goes from lane to lane
+            const uint64_t m = __ballot(S.len > 2 * j);
+            const int owner = __ffsll((long long)m) - 1;
+            float r[GN];
+#pragma unroll
+            for (int g = 0; g < GN; ++g) {
+              r[g] = lane_scalar(acc[g], owner);
+              r[g] = __builtin_fmaf(__int_as_float(t.w), x1[g], __builtin_fmaf(__int_as_float(t.y), x0[g], r[g]));
+            }
+            for (int q = first + 1; q < end; ++q) {
+#pragma unroll
+              for (int g = 0; g < GN; ++g)
+                r[g] = __builtin_fmaf(__int_as_float(t.w), x1[g], __builtin_fmaf(__int_as_float(t.y), x0[g], lane_below(r[g])));
+            }
+#pragma unroll
+            for (int g = 0; g < GN; ++g) acc[g] = lane == owner ? lane_scalar(r[g], end - 1 - b) : acc[g];
+            j += end - first;
+            first = end;
+          }
+          t = next;
         }
       }
       // no memory operation of this path stays in flight, so the waits of the
@@ -597,11 +700,20 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
       float acc[GN], v[GN];
 #pragma unroll
       for (int g = 0; g < GN; ++g) acc[g] = 0.0f;
-      if (P > 4 && mode == kUpTo6) gather(E, ring, c0, c6, acc);
-      else if (mode == kUpTo4) gather(E, ring, c0, c4, acc);
-      else if (P > 6 && mode == kUpTo8) gather(E, ring, c0, c8, acc);
-      else if (mode == kOlder) gather_older(S0, E, acc);
-      else gather_slow(i, S0, acc);
+      // (the slow path by itself behind the others: in one chain with them it makes these
+      // up to 4 % slower, 4,096 cells x 8 directions 78.7 instead of 75.9 us; with two pairs
+      // it is the other way round, 64^3 lattice cells along an axis 262 and 276)
+      if constexpr (P <= 4) {
+        if (__builtin_expect(mode < kOlder, 1)) gather(E, ring, c0, c4, acc);
+        else if (__builtin_expect(mode == kOlder, 1)) gather_older(S0, E, acc);
+        else gather_slow(i, S0, E, acc);
+      } else {
+        if (mode == kUpTo6) gather(E, ring, c0, c6, acc);
+        else if (mode == kUpTo4) gather(E, ring, c0, c4, acc);
+        else if (mode == kUpTo8) gather(E, ring, c0, c8, acc);
+        else if (mode == kOlder) gather_older(S0, E, acc);
+        if (__builtin_expect(mode == kSlow, 0)) gather_slow(i, S0, E, acc);
+      }
       const int n0 = S0.cnt > 0 ? 1 : 0;  // (past the wavefront's last slice a turn has no task)
 #pragma unroll
       for (int g = 0; g < GN; ++g) v[g] = __fdiv_rn(__fadd_rn(acc[g], S0.src[g]), S0.den[g]);
@@ -613,9 +725,9 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
       st_gn<GN>(v, B.outs, act ? 4u * (uint32_t)(S0.k0 * a.G) + lane4G : kOob);
       int n1 = n0;
       asm volatile("" : "+v"(n1));  // (its own condition, or the compiler splits the code between the two)
-      int mine = wave;
-      asm volatile("" : "+s"(mine));  // (its address is not kept in a register)
-      if (lane < n1) __hip_atomic_store(s_next + mine, i + nw, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+      int mine = my_last;
+      asm volatile("" : "+s"(mine));  // (not kept in a vector register)
+      if (lane < n1) __hip_atomic_store(lds_at<int>(mine), i, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
       vis = S0.ks - lag;
       Slice<GN> next = S2;
       resolve(S1, N, [&]() {
