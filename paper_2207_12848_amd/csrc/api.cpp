@@ -1012,7 +1012,8 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   D->n_blocks = n_blocks;
   // the counts' and levels' totals and flags in one place, cleared and read back together;
   // the two that tasks raise one by one have cache lines of their own
-  enum { kEntries = 0, kLongest = 4, kBig = 32, kOverflow = 64, kCycle = 96, kDepth = 98 };  // words
+  constexpr int kTotals = sizeof(sweep::CountTotals) / 4 * sweep::kCountTotals;
+  enum { kBig = kTotals, kOverflow = kBig + 32, kCycle = kOverflow + 32, kDepth = kCycle + 2 };  // words
   Buf words;  // (behind the depths: the slices of every unit)
   HIP_TRY(words.alloc(4 * (kDepth + 2 * (size_t)n_units)));
   int32_t* const w = words.as<int32_t>();
@@ -1050,8 +1051,7 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   a.big = big.as<int64_t>();  // (nullptr: not listed)
   a.big_min = lds_counters ? 15 : sweep::kHashMaxDeps + 1;
   a.big_top = w + kBig;
-  a.ent_tot = reinterpret_cast<unsigned long long*>(w + kEntries);
-  a.stats = w + kLongest;
+  a.totals = words.as<sweep::CountTotals>();
   a.meshes = reinterpret_cast<sweep::MeshDev*>(tables + o_md);
   a.dirs = reinterpret_cast<double*>(tables + o_dirs);
   a.eps = eps;
@@ -1072,7 +1072,6 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   a.err = w + kCycle;
   a.depth = w + kDepth;
   a.n_unit_slices = w + kDepth + n_units;
-  int32_t stats[2] = {0, 0};
   int32_t n_big = 0;
   for (int attempt = 0;; ++attempt) {
     const int64_t cap = dn_width == kRowNarrow ? ovf_cap_narrow : ovf_cap;
@@ -1091,10 +1090,15 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
     int32_t got[kOverflow + 1];
     HIP_TRY(hipMemcpyAsync(got, w, sizeof(got), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    std::memcpy(&D->n_up, got + kEntries, 8);
-    std::memcpy(&D->n_dn, got + kEntries + 2, 8);
-    stats[0] = got[kLongest];
-    stats[1] = got[kLongest + 1];
+    D->n_up = D->n_dn = D->max_up = D->max_dn = 0;
+    for (int i = 0; i < sweep::kCountTotals; ++i) {
+      sweep::CountTotals t;
+      std::memcpy(&t, got + i * (sizeof(t) / 4), sizeof(t));
+      D->n_up += (int64_t)t.entries[0];
+      D->n_dn += (int64_t)t.entries[1];
+      D->max_up = std::max(D->max_up, t.longest[0]);
+      D->max_dn = std::max(D->max_dn, t.longest[1]);
+    }
     n_big = got[kBig];
     const int32_t top = got[kOverflow];
     if (top <= cap) break;
@@ -1106,18 +1110,16 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   HIP_TRY(D->len_dn.alloc(4 * T));
   a.len_up = D->len_up.as<int32_t>();
   a.len_dn = D->len_dn.as<int32_t>();
-  const bool bytes_fit = size_fits_bytes && stats[0] <= 254;
+  const bool bytes_fit = size_fits_bytes && D->max_up <= 254;
   if (kahn_counters == 1 && !lds_fits)
     return fail(SWEEP_ERR_UNSUPPORTED, "the counters of a %d-cell mesh do not fit in LDS", max_cells);
   const bool lds_cnt = lds_counters;
   // otherwise in an LDS hash table of the cells being counted, or as bytes in global memory
   a.hash_bits = lds_cnt ? 0 : sweep::kahn_hash_bits(max_cells);
   a.hash_big = a.hash_bits > 0 && n_big > 0;
-  D->max_up = stats[0];
-  D->max_dn = stats[1];
-  if (!lds_cnt && stats[0] > 254)
+  if (!lds_cnt && D->max_up > 254)
     return fail(SWEEP_ERR_UNSUPPORTED, "a cell with %d upwind dependencies in one direction "
-                "(at most 254 when the mesh's counters do not fit in LDS)", stats[0]);
+                "(at most 254 when the mesh's counters do not fit in LDS)", D->max_up);
   D->kahn_lds = lds_cnt ? 1 : 0;
   const int lds_bits = !lds_cnt ? 0 : bytes_fit ? 8 : 4;
   if (lds_bits == 4 || a.hash_big) HIP_TRY(sweep::launch_mark(a, n_big, s));

@@ -262,11 +262,10 @@ __global__ __launch_bounds__(kTileThreads) void k_count(DagBuildArgs a) {
   atomicAdd(&s_ent[0], eu);
   atomicAdd(&s_ent[1], ed);
   __syncthreads();
-  if (threadIdx.x == 0) {
-    atomicMax(a.stats, s_max[0]);
-    atomicMax(a.stats + 1, s_max[1]);
-    atomicAdd(a.ent_tot, s_ent[0]);
-    atomicAdd(a.ent_tot + 1, s_ent[1]);
+  if (threadIdx.x < 2) {
+    CountTotals& t = a.totals[blockIdx.x % kCountTotals];
+    atomicMax(&t.longest[threadIdx.x], s_max[threadIdx.x]);
+    atomicAdd(&t.entries[threadIdx.x], s_ent[threadIdx.x]);
   }
 }
 
@@ -380,8 +379,9 @@ __global__ __launch_bounds__(kCountThreads) void k_count_aligned(DagBuildArgs a)
   atomicAdd(&s_ent, ed);
   __syncthreads();
   if (threadIdx.x == 0) {
-    atomicMax(a.stats + 1, s_max);
-    atomicAdd(a.ent_tot + 1, s_ent);
+    CountTotals& t = a.totals[blockIdx.x % kCountTotals];
+    atomicMax(&t.longest[1], s_max);
+    atomicAdd(&t.entries[1], s_ent);
   }
 }
 
@@ -425,8 +425,9 @@ __global__ __launch_bounds__(kCountThreads) void k_count_in(DagBuildArgs a) {
   atomicAdd(&s_ent, eu);
   __syncthreads();
   if (threadIdx.x == 0) {
-    atomicMax(a.stats, s_max);
-    atomicAdd(a.ent_tot, s_ent);
+    CountTotals& t = a.totals[blockIdx.x % kCountTotals];
+    atomicMax(&t.longest[0], s_max);
+    atomicAdd(&t.entries[0], s_ent);
   }
 }
 

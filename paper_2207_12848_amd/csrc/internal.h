@@ -68,6 +68,17 @@ struct MeshDev {
 // Dependencies that a count in k_kahn's hash table holds.
 constexpr int kHashMaxDeps = 123;
 
+// Totals of the counts, a cache line each: a workgroup per 32 cells adds its own, and all of
+// them in one line wait for each other (128^3 cells x 8 directions: 3.3 ms, with 16 lines
+// 1.2 ms).
+struct CountTotals {
+  unsigned long long entries[2];  // upwind-row entries, downwind-row entries
+  int32_t longest[2];             // largest in-degree, largest out-degree
+  int32_t pad[26];
+};
+static_assert(sizeof(CountTotals) == 128, "a cache line");
+constexpr int kCountTotals = 16;
+
 struct DagBuildArgs {
   const Unit* units;
   int32_t n_units;
@@ -91,8 +102,7 @@ struct DagBuildArgs {
   int32_t* big_top;          // their number (atomic)
   int32_t max_faces;         // most half-faces of any cell
   int32_t* dnw;              // [T][dn_width] downwind cells of every task (-1 padded)
-  int32_t* stats;            // [0] max in-degree, [1] max out-degree (atomic max)
-  unsigned long long* ent_tot;  // [0] upwind-row entries, [1] downwind-row entries (all tasks)
+  CountTotals* totals;       // [kCountTotals] which the counts' workgroups take by turns
   // per task, cell order within the unit (the upwind row's length is indeg)
   int32_t* indeg;
   int32_t* rowlen_dn;
