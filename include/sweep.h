@@ -115,9 +115,9 @@ typedef struct {
   int32_t kahn_counters; /* where the level computation keeps its per-cell dependency
                             counters: 0 = LDS when the largest mesh fits (4 bits per
                             cell), else global memory; 1 = LDS (UNSUPPORTED if the mesh
-                            does not fit); 2 = global memory (a hash table in LDS holds
-                            those being counted, where it can).  The levels do not
-                            depend on it */
+                            does not fit); 2 = global memory (with many graphs a hash
+                            table in LDS holds those being counted, where it can).  The
+                            levels do not depend on it */
   int32_t scheme;   /* SWEEP_SCHEME_AREA (default): scheme (a), each outflow face i gets
                        the share A_i (n_i . Omega) / Aperp (weight w = A |s|).
                        SWEEP_SCHEME_ALIGNED: scheme (b), direction-conserving transport:

@@ -1114,8 +1114,14 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   if (kahn_counters == 1 && !lds_fits)
     return fail(SWEEP_ERR_UNSUPPORTED, "the counters of a %d-cell mesh do not fit in LDS", max_cells);
   const bool lds_cnt = lds_counters;
-  // otherwise in an LDS hash table of the cells being counted, or as bytes in global memory
-  a.hash_bits = lds_cnt ? 0 : sweep::kahn_hash_bits(max_cells);
+  // otherwise in an LDS hash table of the cells being counted, or as bytes in global memory.
+  // The memory serves the decrements of a few graphs faster than their compute units get
+  // through the table's instructions, but not those of many: 80^3 lattice cells (3 entries
+  // per row) x 1 direction 4.4 ms by the table and 3.3 by memory, x 48 directions 5.0 and
+  // 5.0, x 84 5.1 and 6.4; 320,000 Voronoi cells (7.3) x 1 direction 4.6 and 4.3, x 16 4.95
+  // and 4.87, x 24 5.1 and 5.2, x 48 5.0 and 5.8
+  const double rows_in_flight = (double)D->n_up * n_meshes / (double)D->C_total;
+  a.hash_bits = lds_cnt || rows_in_flight < 150.0 ? 0 : sweep::kahn_hash_bits(max_cells);
   a.hash_big = a.hash_bits > 0 && n_big > 0;
   if (!lds_cnt && D->max_up > 254)
     return fail(SWEEP_ERR_UNSUPPORTED, "a cell with %d upwind dependencies in one direction "

@@ -539,7 +539,8 @@ __device__ __forceinline__ int zero_byte(uint32_t w) {
 //               table's counts hold (kHashMaxDeps): their entries are flagged beforehand
 //               (k_mark), and they are always counted in global memory.
 //  kKahnGlobal  bytes in global memory, four to a word: meshes too large for the
-//               table's keys.
+//               table's keys, and few graphs at a time (the rule stands where the host
+//               chooses).
 //
 // What bounds it: narrow levels, the chain from a level's barrier to the next (the
 // rows come from HBM); wider ones, the instructions of 16 wavefronts (about 90 per
