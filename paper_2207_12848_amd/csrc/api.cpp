@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -1284,7 +1285,16 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   std::memcpy(final_units.data() + o_order + sizeof(int32_t) * n_units, D->identity.data(), sizeof(int32_t) * n_units);
   HIP_TRY(hipMemcpyAsync(tables + o_units, final_units.data(), final_units.size(), hipMemcpyHostToDevice, s));
   {
-    // LDS a sweep workgroup may use: the device limit less the kernel's static LDS
+    // (how the kernels were compiled: looked up once)
+    static std::atomic<bool> lds_checked{false};
+    if (!lds_checked.load(std::memory_order_relaxed)) {
+      size_t bytes = 0;
+      HIP_TRY(sweep::sweep_static_lds(&bytes));
+      if (bytes != 0)
+        return fail(SWEEP_ERR_UNSUPPORTED, "the sweep kernels were compiled with %zu bytes of static LDS", bytes);
+      lds_checked.store(true, std::memory_order_relaxed);
+    }
+    // LDS a sweep workgroup may use: the device limit less a reserve
     int lds_max = 65536;
     (void)hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, D->device);
     D->lds_max = std::max(65536, std::min(lds_max, kMaxLds)) - 256;

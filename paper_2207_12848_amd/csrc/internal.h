@@ -365,6 +365,8 @@ hipError_t launch_adj_reduce(const AdjReduceArgs& a, double* dk, double* de, hip
 hipError_t launch_d2f_pair(const double* a, const double* b, float* oa, float* ob, int64_t n,
                            hipStream_t s);
 hipError_t set_sweep_lds_limit(int32_t bytes);
+// The most static LDS of any sweep kernel: their addresses need it to be 0.
+hipError_t sweep_static_lds(size_t* bytes);
 // Largest sweep workgroup for gn packed groups: one group fits 1024 threads'
 // registers (128 VGPRs each), more groups need the 256 VGPRs of 512 threads.
 constexpr int kSweepMaxBlock(int gn) { return gn == 1 ? 1024 : 512; }

@@ -15,6 +15,7 @@
 #include <float.h>
 #include <limits.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "internal.h"
@@ -186,8 +187,8 @@ struct Entries {
 template <int GN>
 __device__ __forceinline__ int slot_of(int x, int mask4) { return (x & mask4) * GN; }
 
-// The sweep's LDS is dynamic only, so it starts at LDS address 0 and slot offsets
-// are addresses: GN consecutive floats read or written there in one access.
+// The sweep's LDS is dynamic only (sweep_static_lds), so it starts at LDS address 0 and
+// slot offsets are addresses: GN consecutive floats read or written there in one access.
 template <int GN>
 struct LdsVec {
   using type = float __attribute__((ext_vector_type(GN)));
@@ -1325,28 +1326,39 @@ hipError_t launch_prep(const PrepArgs& a, int32_t n_blocks, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int GN, bool REVERSE>
-hipError_t set_lds_g(int32_t bytes) {
-  for (auto kernel : {k_sweep<GN, REVERSE, 2>, k_sweep<GN, REVERSE, kPairs>}) {
-    const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+// Calls f(kernel) for the sweep kernels of GN groups until one fails.
+template <int GN, class F>
+hipError_t each_sweep_g(F&& f) {
+  for (auto kernel : {k_sweep<GN, false, 2>, k_sweep<GN, false, kPairs>, k_sweep<GN, true, 2>, k_sweep<GN, true, kPairs>}) {
+    const hipError_t e = f((const void*)kernel);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
-template <int GN>
-hipError_t set_lds_gn(int32_t bytes) {
+template <class F>
+hipError_t each_sweep(F&& f) {
   hipError_t e;
-  if ((e = set_lds_g<GN, false>(bytes)) != hipSuccess) return e;
-  return set_lds_g<GN, true>(bytes);
+  if ((e = each_sweep_g<1>(f)) != hipSuccess) return e;
+  if ((e = each_sweep_g<2>(f)) != hipSuccess) return e;
+  if ((e = each_sweep_g<3>(f)) != hipSuccess) return e;
+  return each_sweep_g<4>(f);
 }
 
 hipError_t set_sweep_lds_limit(int32_t bytes) {
-  hipError_t e;
-  if ((e = set_lds_gn<1>(bytes)) != hipSuccess) return e;
-  if ((e = set_lds_gn<2>(bytes)) != hipSuccess) return e;
-  if ((e = set_lds_gn<3>(bytes)) != hipSuccess) return e;
-  return set_lds_gn<4>(bytes);
+  return each_sweep([&](const void* kernel) {
+    return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  });
+}
+
+hipError_t sweep_static_lds(size_t* bytes) {
+  *bytes = 0;
+  return each_sweep([&](const void* kernel) {
+    hipFuncAttributes at;
+    const hipError_t e = hipFuncGetAttributes(&at, kernel);
+    if (e == hipSuccess) *bytes = std::max(*bytes, at.sharedSizeBytes);
+    return e;
+  });
 }
 
 hipError_t launch_pin(const PinArgs& a, hipStream_t s) {
