@@ -13,9 +13,10 @@ constexpr int32_t kErrCell = 4;      // a task's denominator (Aperp + kappa V) n
 constexpr int32_t kErrGrad = 8;      // dL/dJ or dL/dabsorbed not finite
 constexpr int32_t kErrStall = 16;    // a sweep's wait for earlier slices did not end (never expected)
 
-// Reads of a sweep's LDS counter before a wait gives up (about 0.2 s; a wait lasts
-// microseconds).
-constexpr int kSpinLimit = 1 << 22;
+// Reads of a sweep's LDS counters before a wait gives up (about 0.8 s).  A wait lasts
+// microseconds, or as long as the longest rows of a slice take: 6 ms for 64 rows of 20,000
+// entries and four groups, and 15 times that for the most that a cell can have.
+constexpr int kSpinLimit = 1 << 24;
 
 // One slice of the sweep: at most 64 consecutive schedule positions of one level.
 // One table per sweep direction; positions, dependencies and level bounds are

@@ -232,15 +232,17 @@ using lds_int = int __attribute__((address_space(3)));
 // stands still for millions of reads raises the error flag instead of hanging).
 __device__ __forceinline__ void wait_count(lds_int* counter, int need, int& seen, int32_t* flag) {
   if (seen >= need) return;
-  for (int it = 0;; ++it) {
-    seen = uni(__hip_atomic_load(counter, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
-    if (seen >= need) return;
-    if (it >= kSpinLimit) {
-      atomicOr(flag, kErrStall);
-      seen = INT_MAX;
-      return;
+  // (five reads in a row: with a loop's branches behind every read, each link of the chain
+  // of levels is longer, 4,096 cells x 8 directions 82.8 instead of 75.7 us)
+  for (int it = 0; it < kSpinLimit; it += 5) {
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      seen = uni(__hip_atomic_load(counter, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
+      if (seen >= need) return;
     }
   }
+  atomicOr(flag, kErrStall);
+  seen = INT_MAX;
 }
 
 // Waits until every wavefront has stored its slices before `need`: last[w] is the slice
