@@ -158,8 +158,8 @@ __global__ __launch_bounds__(kTileThreads) void k_count(DagBuildArgs a) {
   int64_t* s_fp = reinterpret_cast<int64_t*>(smem);
   int32_t* s_code = reinterpret_cast<int32_t*>(s_fp + kTileCells + 2);
   int32_t* srow = s_code + (kTileDirs + 1) * kTileCap;
-  // directions at a time: fewer for a tile of many faces
-  const int kd = min(kTileDirs, (kTileDirs + 1) * kTileCap / nf - 1);
+  // directions at a time: fewer for a tile of many faces (its cells may have none at all)
+  const int kd = nf > 0 ? min(kTileDirs, (kTileDirs + 1) * kTileCap / nf - 1) : kTileDirs;
   const bool in_lds = kd > 0;
   const int nd = in_lds ? kd : kTileDirs;
   float* s_w = reinterpret_cast<float*>(s_code + nf);  // [direction][face]

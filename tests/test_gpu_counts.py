@@ -28,3 +28,25 @@ def test_entries_are_counted(scheme, sizes):
         for m, got in zip(meshes, dag.split(indeg)):
             assert np.array_equal(got, oracle.build_dag(m, dirs)[2])
     dag.close()
+
+
+def test_tiles_of_cells_without_faces():
+    """Cells without faces, enough of them for whole tiles: a cell's phi is its source over
+    kappa V; the others' results are theirs alone, bit for bit."""
+    import torch
+
+    import paper_2207_12848_amd as sw
+    w = W.small_random(200, 9, seed=12)
+    m = w["meshes"][0]
+    n = 100
+    more = dict(m, face_ptr=np.concatenate([m["face_ptr"], np.full(n, m["face_ptr"][-1])]),
+                cell_volume=np.concatenate([m["cell_volume"], np.full(n, 0.5)]))
+    k, e = (np.concatenate([w[x], np.full((n, 1), 0.25, np.float32)]) for x in ("kappa", "emission"))
+    out = []
+    for mesh, kk, ee in ((m, w["kappa"], w["emission"]), (more, k, e)):
+        dag = sw.build_dag([mesh], w["dirs"])
+        out.append(sw.forward(dag, *(torch.tensor(x, device="cuda") for x in (kk, ee)), check=True)[0].cpu().numpy())
+        dag.close()
+    C = len(m["cell_volume"])
+    assert np.array_equal(out[1][:C], out[0])
+    assert np.allclose(out[1][C:], 0.25 / (0.25 * 0.5) / (4 * np.pi), rtol=1e-6, atol=0.0)
