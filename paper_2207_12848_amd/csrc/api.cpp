@@ -1368,8 +1368,8 @@ sweep_status_t sweep_dag_export(sweep_dag_t d, int32_t* level, int32_t* order, i
     HIP_TRY(hipMemcpyAsync(lp.data(), d->lp.p, 4 * lp.size(), hipMemcpyDeviceToHost, s));
   }
   ST_TRY(take_device_error(d, s));
-  // the schedule groups every unit's cells by level (level k = slots [lp[k], lp[k+1]));
-  // the canonical order sorts each level by cell id
+  // the schedule groups every unit's cells by level (level k = slots [lp[k], lp[k+1])), in
+  // the canonical order, by cell id; wider levels than the device sorts are sorted here
   for (const Unit& U : d->units) {
     if (!order && !level) break;
     const int32_t* l = lp.data() + U.lp_base;
@@ -1380,7 +1380,7 @@ sweep_status_t sweep_dag_export(sweep_dag_t d, int32_t* level, int32_t* order, i
       if (order) {
         int32_t* o = order + U.task_base;
         std::memcpy(o + l[k], sc + l[k], 4 * (size_t)(l[k + 1] - l[k]));
-        std::sort(o + l[k], o + l[k + 1]);
+        if (l[k + 1] - l[k] > sweep::kSortCap) std::sort(o + l[k], o + l[k + 1]);
       }
     }
   }

@@ -978,10 +978,10 @@ __global__ __launch_bounds__(1024) void k_kahn(DagBuildArgs a) {
 // level wider than kSortCap keeps its order.  64^3 cells x 84 directions (levels of
 // about 230, up to 500): 641 us, and 708 with the bitonic sort alone; 50 K cells x 48 directions
 // (57): 47 and 257; 4096 cells x 8 directions (18): 6.7 and 43.
-constexpr int kSortCap = 4096;
 constexpr int kSortBlock = 256;
 constexpr int kSortPerUnit = 16;  // workgroups per unit
 constexpr int kSortWave = 256;
+static_assert(kSortBlock / 64 * kSortWave <= kSortCap, "the wavefronts' cells share the keys' LDS");
 
 __global__ __launch_bounds__(kSortBlock) void k_sort_levels(DagBuildArgs a) {
   __shared__ __align__(16) int key[kSortCap];

@@ -322,7 +322,9 @@ hipError_t launch_face_stats(const int64_t* face_ptr, int32_t n_cells, int32_t r
 // *bad is set if the mesh may violate a condition of the host's check
 hipError_t launch_check_mesh(const MeshDev& m, int32_t* bad, hipStream_t s);
 hipError_t launch_face_codes(const MeshDev& m, int32_t* fcode, uint8_t* edge, hipStream_t s);
-// Sorts every level of the schedule by cell id and writes the inverse schedule.
+// Sorts every level of the schedule of up to kSortCap cells by cell id and writes the
+// inverse schedule.
+constexpr int kSortCap = 4096;
 hipError_t launch_sort_levels(const DagBuildArgs& a, hipStream_t s);
 // Slices per unit (n_unit_slices); then, with the slices' place known, the slice
 // tables, and per task in schedule order the row lengths, Aperp and volume.
