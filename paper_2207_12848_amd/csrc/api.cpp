@@ -184,7 +184,7 @@ struct Buf {
   T* as() const { return static_cast<T*>(p); }
 };
 
-// Host tables gathered into one upload: add() each, then copy() and at() their places.
+// Host tables gathered into one upload: add() returns a table's place in it.
 struct Tables {
   std::vector<unsigned char> host;
   size_t add(const void* src, size_t n) {
@@ -517,27 +517,12 @@ std::vector<GroupLaunch> group_plan(sweep_dag_t d, int G, bool plain, int pack) 
   return ch;
 }
 
-// The largest ring (a power of two) of gn packed groups that leaves room for
-// `per_cu` workgroups on a compute unit; 0 if none does.
-int default_ring(sweep_dag_t d, int gn, int per_cu) {
+// The largest ring (a power of two) of gn packed groups that fits the LDS; 0 if none does.
+int default_ring(sweep_dag_t d, int gn) {
   int best = 0;
   for (int r = 64; r <= (1 << 20); r *= 2)
-    if (sweep::sweep_lds_bytes(gn, r) <= (size_t)d->lds_max &&
-        (sweep::sweep_lds_bytes(gn, r) + 256) * per_cu <= (size_t)kMaxLds)
-      best = r;
+    if (sweep::sweep_lds_bytes(gn, r) <= (size_t)d->lds_max) best = r;
   return best;
-}
-
-// Launch shape of a sweep: threads per workgroup and ring.
-struct SweepShape {
-  int block, ring;
-};
-
-// With at most one work item per compute unit, a workgroup takes the whole unit
-// (as many wavefronts as the registers allow, the largest ring).
-SweepShape sweep_shape(sweep_dag_t d, int gn, int64_t items) {
-  (void)items;
-  return {sweep::kSweepMaxBlock(gn), default_ring(d, gn, 1)};
 }
 
 // Per-task denominators and sources for one sweep (schedule order).
@@ -665,22 +650,19 @@ sweep_status_t run_sweep(sweep_dag_t d, bool reverse, const FwdPlan& p, int32_t 
   a.tsrc = d->tsrc.as<float>();
   HIP_TRY(d->out_s.alloc(4 * (size_t)d->T * G));
   a.out_s = d->out_s.as<float>();
-  a.C_total = d->C_total;
   a.G = G;
-  a.D = d->D;
   a.flag = d->flag.as<int32_t>();
   a.max_row = reverse ? d->max_dn : d->max_up;
   const int n_units = (int)d->units.size();
   for (const GroupLaunch& c : group_plan(d, G, p.form == SWEEP_FORM_PLAIN, p.pack)) {
     const int gn = c.gn;
     const bool plain = p.form == SWEEP_FORM_PLAIN;
-    const int64_t items = plain ? 1 : (int64_t)n_units * c.n_chunks;
-    const SweepShape sh = sweep_shape(d, gn, items);
-    const int block = p.block > 0 ? p.block : sh.block;
+    // as many wavefronts as the registers allow, and the largest ring
+    const int block = p.block > 0 ? p.block : sweep::kSweepMaxBlock(gn);
     if (block > sweep::kSweepMaxBlock(gn))
       return fail(SWEEP_ERR_INVALID_ARG, "block %d: at most %d threads with %d packed groups", block,
                   sweep::kSweepMaxBlock(gn), gn);
-    const int ring = p.ring > 0 ? p.ring : sh.ring;
+    const int ring = p.ring > 0 ? p.ring : default_ring(d, gn);
     const size_t lds = sweep::sweep_lds_bytes(gn, ring);
     if (ring == 0 || lds > (size_t)d->lds_max)
       return fail(p.ring > 0 ? SWEEP_ERR_INVALID_ARG : SWEEP_ERR_UNSUPPORTED,
@@ -704,7 +686,7 @@ sweep_status_t run_sweep(sweep_dag_t d, bool reverse, const FwdPlan& p, int32_t 
       int per_cu = std::max(1, (int)((size_t)kMaxLds / (lds + 256)));
       per_cu = std::min(per_cu, std::max(1, sweep::kSweepMaxBlock(gn) / block));
       a.n_chunks = c.n_chunks;
-      int grid = (int)std::min<int64_t>(items, (int64_t)d->cu_count * per_cu);
+      int grid = (int)std::min<int64_t>((int64_t)n_units * c.n_chunks, (int64_t)d->cu_count * per_cu);
       if (p.grid > 0) grid = std::min(grid, p.grid);
       a.work_counter = d->counter.as<int32_t>();
       a.unit_order = d->order_d.as<int32_t>();
@@ -1244,8 +1226,9 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
       if (md[m].face_shift != nullptr) HIP_TRY(sweep::launch_pdir(a, md[m], m, s));
     HIP_TRY(hipStreamSynchronize(s));  // the local counts and scans are released here
   }
-  // a unit whose rows are too long for 32-bit offsets (possible only if its mesh has that
-  // many half-faces)
+  // a unit of more row entries than are supported (possible only if its mesh has that many
+  // half-faces; the sweep addresses rows slice by slice and would take more, but no mesh of
+  // that size has been run, and the periodic lists number half-faces with 32 bits)
   int64_t most_faces = 0;
   for (int m = 0; m < n_meshes; ++m) most_faces = std::max(most_faces, meshes[m].n_half_faces);
   if (8 * most_faces > sweep::kMaxBufBytes) {
@@ -1258,9 +1241,9 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
     HIP_TRY(hipStreamSynchronize(s));
     for (int u = 0; u < n_units; ++u)
       if (8 * std::max(ue[2 * u], ue[2 * u + 1]) > sweep::kMaxBufBytes)
-        return fail(SWEEP_ERR_UNSUPPORTED, "mesh %d, direction %d: %lld row entries exceed the sweep's "
-                    "32-bit buffer range", D->units[u].mesh, D->units[u].dir,
-                    (long long)std::max(ue[2 * u], ue[2 * u + 1]));
+        return fail(SWEEP_ERR_UNSUPPORTED, "mesh %d, direction %d: %lld row entries (at most %lld)",
+                    D->units[u].mesh, D->units[u].dir, (long long)std::max(ue[2 * u], ue[2 * u + 1]),
+                    (long long)(sweep::kMaxBufBytes / 8));
   }
   D->max_cells = max_cells;
   HIP_TRY(D->flag.alloc(4));
@@ -1874,7 +1857,7 @@ sweep_status_t sweep_tune(sweep_dag_t d, int32_t G, const float* kappa, const fl
   sweep_status_t st = SWEEP_OK;
   for (int block : {256, 512, 1024}) {
     if (block > sweep::kSweepMaxBlock(gn)) continue;
-    const int r0 = default_ring(d, gn, 1);
+    const int r0 = default_ring(d, gn);
     for (int ring : {r0 / 4, r0 / 2, r0}) {
       if (ring < 64) continue;
       FwdPlan q = p;

@@ -16,6 +16,7 @@
 
 #include <type_traits>
 
+#include "device.h"
 #include "internal.h"
 #include "sweep.h"
 
@@ -53,17 +54,6 @@ __device__ __forceinline__ float signed_w(double A, double s, double eps) {
   return copysignf(A >= 0.0 ? face_w(A, s) : __int_as_float(kBadFace), (float)s);
 }
 __device__ __forceinline__ bool carries(float w) { return __float_as_int(w) != kNoFace; }
-
-// Workgroups are dispatched round-robin over the 8 XCDs, each with its own L2
-// cache: this renumbering gives each XCD one contiguous range of the grid, so
-// the workgroups an XCD runs together belong to few units and share those
-// units' arrays in its L2.
-__device__ __forceinline__ int xcd_block(int b, int nb) {
-  constexpr int kXcd = 8;
-  const int per = nb / kXcd, rem = nb % kXcd;
-  const int x = b % kXcd;
-  return x * per + min(x, rem) + b / kXcd;
-}
 
 // The cell-order kernel stages a tile of kTileCells consecutive cells' faces
 // in LDS with coalesced loads (room for kTileFaces faces per cell on average,
@@ -490,11 +480,6 @@ static_assert(kHashMaxDeps < (int)kHashBias - 4, "counts stay above 0 while they
 constexpr int kMissCap = 2048;  // a level's decrements that did not find their cell, listed in LDS
 
 using lds_int = int __attribute__((address_space(3)));
-
-// Lanes of `m` below this one.
-__device__ __forceinline__ int rank_in(unsigned long long m) {
-  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
 
 // First byte of w that is 0, as its bit offset (0, 8, 16, 24); -1 if there is none.
 // (The bytes above a zero byte may be marked wrongly, the lowest mark is exact.)
@@ -1265,8 +1250,8 @@ __global__ __launch_bounds__(kCountBlock) void k_gather_tasks(DagBuildArgs a) {
   }
 }
 
-// Row entries of the units for the check of the 32-bit buffer range (meshes
-// with very many faces only), one workgroup per unit.
+// Row entries of the units for the check of their number (meshes with very many
+// faces only), one workgroup per unit.
 __global__ __launch_bounds__(256) void k_unit_entries(const Unit* units, const int32_t* len_up,
                                                       const int32_t* len_dn, unsigned long long* out) {
   const Unit U = units[blockIdx.x];
@@ -1671,8 +1656,7 @@ hipError_t launch_gather_tasks(const DagBuildArgs& a, hipStream_t s) {
 hipError_t launch_fill(const DagBuildArgs& a, hipStream_t s) {
   if (a.n_slices <= 0) return hipSuccess;
   const dim3 grid(grid1d(a.n_slices, kFillBlock / 64));
-  size_t lds = kFillBlock / 64 * sizeof(int2) * (size_t)a.fill_faces * (kFillTasks + 1);
-  
+  const size_t lds = kFillBlock / 64 * sizeof(int2) * (size_t)a.fill_faces * (kFillTasks + 1);
   auto kernel = a.scheme == SWEEP_SCHEME_ALIGNED ? k_fill<true> : k_fill<false>;
   const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;

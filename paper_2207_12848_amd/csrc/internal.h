@@ -174,10 +174,8 @@ struct SweepArgs {
   const float* tsrc;       // [T][G] schedule order: source of the task (periodic
                            // coupling included, see PinArgs)
   float* out_s;            // phi (forward) or lambda (adjoint) in schedule order, [T][G]
-  int64_t C_total;
   int32_t G;       // group stride
   int32_t g0;      // first group handled by this launch (see n_chunks)
-  int32_t D;
   int32_t ring_mask;
   int32_t* flag;   // device error bits: kErrStall
   int32_t max_row;  // entries of this walk's longest row

@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "device.h"
 #include "internal.h"
 #include "sweep.h"
 
@@ -51,19 +52,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const T* p, int64_t bytes
 constexpr int kStream = 2;
 
 template <int POL = 0>
-__device__ __forceinline__ int2 ld_b64(__amdgpu_buffer_rsrc_t r, uint32_t vo, uint32_t so) {
-  return __builtin_bit_cast(int2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)vo, (int)so, POL));
-}
-template <int POL = 0>
 __device__ __forceinline__ int4 ld_b128(__amdgpu_buffer_rsrc_t r, uint32_t vo, uint32_t so) {
   return __builtin_bit_cast(int4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)vo, (int)so, POL));
-}
-template <int POL = 0>
-__device__ __forceinline__ int ld_b32(__amdgpu_buffer_rsrc_t r, uint32_t vo, uint32_t so) {
-  return __builtin_amdgcn_raw_buffer_load_b32(r, (int)vo, (int)so, POL);
-}
-__device__ __forceinline__ float ld_f32(__amdgpu_buffer_rsrc_t r, uint32_t vo, uint32_t so) {
-  return __int_as_float(ld_b32(r, vo, so));
 }
 template <int POL = 0>
 __device__ __forceinline__ void st_f32(float v, __amdgpu_buffer_rsrc_t r, uint32_t vo) {
@@ -121,11 +111,6 @@ using global_ptr = const T __attribute__((address_space(1)))*;
 template <class T>
 __device__ __forceinline__ global_ptr<T> uniform_ptr(const T* p) {
   return (global_ptr<T>)(uint64_t)uniform64((int64_t)(uint64_t)p);
-}
-
-// Lanes of `m` below this one.
-__device__ __forceinline__ int rank_in(uint64_t m) {
-  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
 // Values of other lanes: lane `from` mod 64 (__shfl without its width, which takes
@@ -798,15 +783,6 @@ __device__ __forceinline__ int unit_of_block(const int32_t* blk_base, int n_unit
     if (blk_base[mid] <= b) lo = mid; else hi = mid - 1;
   }
   return lo;
-}
-
-// Workgroups are dispatched round-robin over the 8 XCDs, each with its own L2
-// cache: this renumbering gives each XCD one contiguous range of the grid.
-__device__ __forceinline__ int xcd_block(int b, int nb) {
-  constexpr int kXcd = 8;
-  const int per = nb / kXcd, rem = nb % kXcd;
-  const int x = b % kXcd;
-  return x * per + min(x, rem) + b / kXcd;
 }
 
 // Results in schedule order -> cell order, [D][C][G]: one thread per (cell, VEC
