@@ -1103,7 +1103,8 @@ sweep_status_t sweep_build_dag(const sweep_mesh_t* meshes, int32_t n_meshes, con
   // per row) x 1 direction 4.4 ms by the table and 3.3 by memory, x 48 directions 5.0 and
   // 5.0, x 84 5.1 and 6.4; 320,000 Voronoi cells (7.3) x 1 direction 4.6 and 4.3, x 16 4.95
   // and 4.87, x 24 5.1 and 5.2, x 48 5.0 and 5.8
-  const double rows_in_flight = (double)D->n_up * n_meshes / (double)D->C_total;
+  // (row entries per cell of the largest mesh: its graphs run longest)
+  const double rows_in_flight = (double)D->n_up / max_cells;
   a.hash_bits = lds_cnt || rows_in_flight < 150.0 ? 0 : sweep::kahn_hash_bits(max_cells);
   a.hash_big = a.hash_bits > 0 && n_big > 0;
   if (!lds_cnt && D->max_up > 254)

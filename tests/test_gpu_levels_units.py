@@ -1,6 +1,6 @@
 """GPU levels, order and in-degrees against the oracle where the counters of large meshes lie:
-in global memory with few graphs in flight, in the hash table from about 150 row entries per
-step of all graphs on (directions x meshes x the mean row).  Small meshes with the counters
+in global memory with few graphs in flight, in the hash table from about 150 row entries of
+all graphs per cell of the largest mesh on (directions x the mean row, for one mesh).  Small meshes with the counters
 kept out of LDS by the option, on either side of that line: tables whose buckets overflow,
 levels wider than the frontier's and the table's lists, cells of more dependencies than the
 table counts.  Bit-exact."""
