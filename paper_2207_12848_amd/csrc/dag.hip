@@ -1275,7 +1275,7 @@ __global__ __launch_bounds__(256) void k_unit_entries(const Unit* units, const i
 // 2 j, in task order, then pair j + 1 of those longer than 2 j + 2, and so on,
 // so that a wavefront with one task per lane reads each column with one
 // coalesced 128-bit load and no padding but the second half of an odd row's
-// last pair (factor 0).  An entry is (position code, w): 4 (p + 1), p the
+// last pair (no entry).  An entry is (position code, w): 4 (p + 1), p the
 // neighbour's position in the walk that reads the row (upwind rows: its
 // schedule position; downwind rows, walked backwards: the unit's last position
 // minus it), so 0 means no entry and the code with the low bits masked is the
@@ -1393,11 +1393,13 @@ __global__ __launch_bounds__(kFillBlock) __attribute__((amdgpu_waves_per_eu(5)))
             float w;
             classify(f0 + q, true, code, wf[f0 + q], up, dn, w);
             if (!(side == 0 ? up : dn)) continue;
-            pair.z = code_of(up, inv[code]);
-            pair.w = k == 0 ? 0 : __float_as_int(w);
+            const int at = code_of(up, inv[code]);
             if (k++ == 0) {
-              pair.x = pair.z;
+              pair.x = at;
               pair.y = __float_as_int(w);
+            } else {
+              pair.z = at;
+              pair.w = __float_as_int(w);
             }
           }
           out[__popcll(m & ((1ull << lane) - 1ull))] = pair;
@@ -1469,7 +1471,7 @@ __global__ __launch_bounds__(kFillBlock) __attribute__((amdgpu_waves_per_eu(5)))
         const bool odd = n == 2 * j + 1;
         const int2 y = row[(odd ? 2 * j : 2 * j + 1) * step];
         typedef int v4 __attribute__((ext_vector_type(4)));
-        const v4 pair = {x.x, x.y, y.x, odd ? 0 : y.y};
+        const v4 pair = {x.x, x.y, odd ? 0 : y.x, odd ? 0 : y.y};  // (no entry: 0 times it is 0)
         __builtin_nontemporal_store(pair, reinterpret_cast<v4*>(out) + __popcll((dside ? md : mu) & low));
       }
       out += dside ? __popcll(md) : __popcll(mu);
