@@ -688,12 +688,20 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
       float acc[GN], v[GN];
 #pragma unroll
       for (int g = 0; g < GN; ++g) acc[g] = 0.0f;
-      // (the slow path by itself behind the others: in one chain with them it makes these
-      // up to 4 % slower, 4,096 cells x 8 directions 78.7 instead of 75.9 us; with two pairs
-      // it is the other way round, 64^3 lattice cells along an axis 262 and 276)
+      // (The same choice three times, as the branches' order and nesting decide how the
+      // compiler lays the ways out, and with them the sweep's time.  Eight pairs, one group:
+      // 4,096 cells x 8 directions 74.5 us, 78.7 in one chain with the slow path.  Packed
+      // groups: 64^3 cells x 84 directions x 2 groups 843 us in one chain, 902 with the slow
+      // path behind it.  Two pairs: 64^3 lattice cells along an axis 262 us, 272 and 276.)
       if constexpr (P <= 4) {
         if (__builtin_expect(mode < kOlder, 1)) gather(E, ring, c0, c4, acc);
         else if (__builtin_expect(mode == kOlder, 1)) gather_older(S0, E, acc);
+        else gather_slow(i, S0, E, acc);
+      } else if constexpr (GN > 1) {
+        if (mode == kUpTo6) gather(E, ring, c0, c6, acc);
+        else if (mode == kUpTo4) gather(E, ring, c0, c4, acc);
+        else if (mode == kUpTo8) gather(E, ring, c0, c8, acc);
+        else if (mode == kOlder) gather_older(S0, E, acc);
         else gather_slow(i, S0, E, acc);
       } else {
         if (mode == kUpTo6) gather(E, ring, c0, c6, acc);
