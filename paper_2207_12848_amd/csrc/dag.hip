@@ -45,15 +45,13 @@ __device__ __forceinline__ double orient(double ox, double oy, double oz, const 
 __device__ __forceinline__ float face_w(double A, double s) { return (float)(A * fabs(s)); }
 
 // Signed weight of a face: its class, by the orientation, in the sign (outflow +, inflow -,
-// also of a zero weight); kNoFace, a NaN, for neither.  A negative or undefined area (meshes
-// that were not checked) gives another NaN with the class in its sign: the face still orders
-// its cells, and makes its cell's Aperp NaN, which the sweep reports.
-constexpr int kNoFace = 0x7fc00000, kBadFace = 0x7fc00001;
+// also of a zero weight); NaN for neither.  A negative or undefined area (meshes that were
+// not checked) gives an infinite weight of that class: the face still orders its cells, and
+// makes its cell's Aperp infinite, which the sweep reports.
 __device__ __forceinline__ float signed_w(double A, double s, double eps) {
-  if (!(s > eps || s < -eps)) return __int_as_float(kNoFace);
-  return copysignf(A >= 0.0 ? face_w(A, s) : __int_as_float(kBadFace), (float)s);
+  if (!(s > eps || s < -eps)) return __int_as_float(0x7fc00000);
+  return copysignf(A >= 0.0 ? face_w(A, s) : INFINITY, (float)s);
 }
-__device__ __forceinline__ bool carries(float w) { return __float_as_int(w) != kNoFace; }
 
 // The cell-order kernel stages a tile of kTileCells consecutive cells' faces
 // in LDS with coalesced loads (room for kTileFaces faces per cell on average,
@@ -191,10 +189,10 @@ __global__ __launch_bounds__(kTileThreads) void k_count(DagBuildArgs a) {
         for (int f = fb; f < fe; ++f) {
           const float w = weights[f];
           const int code = codes[f];
-          if (!carries(w)) continue;
+          if (isnan(w)) continue;
           if (signbit(w)) {
             nup += code >= 0 ? 1 : 0;
-            if (isnan(w)) ap = w;
+            if (isinf(w)) ap = -w;
             continue;
           }
           ap += w;
@@ -336,7 +334,7 @@ __global__ __launch_bounds__(kCountThreads) void k_count_aligned(DagBuildArgs a)
         bool chosen = false;
 #pragma unroll
         for (int k = 0; k < kMaxAligned; ++k) chosen |= k < n && bf[k] == f;
-        wf[f] = chosen ? wb : __int_as_float(kNoFace);
+        wf[f] = chosen ? wb : __int_as_float(0x7fc00000);
         if (!chosen) continue;
         const int nb = nbr[f];
         if (nb < 0) wall += wb;
@@ -1350,7 +1348,7 @@ __global__ __launch_bounds__(kFillBlock) __attribute__((amdgpu_waves_per_eu(5)))
       dn = has && !isnan(ws);
       w = up ? wi : ws;
     } else {
-      has = has && carries(ws);
+      has = has && !isnan(ws);
       up = has && signbit(ws);   // interior inflow
       dn = has && !signbit(ws);  // interior outflow
       w = fabsf(ws);
@@ -1534,7 +1532,7 @@ __global__ void k_pdir(DagBuildArgs a, MeshDev M, int mesh) {
       aw = isnan(ws) ? 0.0f : ws;
     } else {
       const float ws = wf[f];
-      const bool has = carries(ws);
+      const bool has = !isnan(ws);
       const bool in = has && signbit(ws);
       fw = in ? fabsf(ws) : 0.0f;
       aw = has && !in ? fabsf(ws) : 0.0f;

@@ -112,7 +112,7 @@ struct DagBuildArgs {
   float* vol_s;    // the cell's volume per task, schedule order (written by k_gather_tasks)
   // per (direction, face) of every mesh, at D * face_off + d * n_faces + f: the face
   // weight w = A |Omega . n| rounded once to FP32 from FP64, with the face's class
-  // in its sign: outflow +w, inflow -w; a NaN for neither (signed_w)
+  // in its sign: outflow +w, inflow -w, neither NaN (signed_w)
   float* wface;
   float2* bnd;  // (sum of w over wall outflow faces, over periodic outflow faces)
   int32_t* cnt;    // [T] words: Kahn's counters kept in global memory
