@@ -116,8 +116,9 @@ __device__ __forceinline__ FaceTile stage_tile(const MeshDev& M, int c0, unsigne
 //
 // Bound by its writes, in runs of 128 bytes to 2 KB (3.2 GB at 64^3 cells and 84
 // directions, 2.4 TB/s; a third of the issue slots are used).  64^3 cells, 84 directions:
-// 1.33 ms, and 1.45 with the orientations taken in the cells' loop from normals in LDS and
-// again for the weights; 2 M cells: 11.7 ms, and 13.3.
+// 1.29 ms, and 1.45 with the orientations taken in the cells' loop from normals in LDS and
+// again for the weights; 2 M cells: 11.5 ms, and 13.3.  With few directions a tile's fixed
+// part counts, its totals above all (CountTotals).
 constexpr int kTileDirs = 8;
 constexpr int kTileThreads = kTileDirs * kTileCells;
 constexpr int kTileCap = kTileCells * kTileFaces;
@@ -530,9 +531,9 @@ __device__ __forceinline__ int zero_byte(uint32_t w) {
 // row's lane and batch).  Per launch, against one lane per row of 16 entries and
 // counters of larger meshes decremented in global memory (1.1 G atomics there at 2M
 // cells): 4,096 cells x 8 directions 0.63 -> 0.21 ms, 64^3 jittered cells x 84
-// directions 4.0 -> 2.3 ms, 2M clustered cells x 84 directions 69 -> 41 ms.  Loading
-// a word of each newly ready cell's row at once, so that the next level finds it in
-// L2, made it 7 to 9 % slower.
+// directions 4.0 -> 2.3 ms, 2M clustered cells x 84 directions 69 -> 41 ms (43 with a few
+// cells of more than 123 dependencies).  Loading a word of each newly ready cell's row at
+// once, so that the next level finds it in L2, made it 7 to 9 % slower.
 template <int MODE>
 __global__ __launch_bounds__(1024) void k_kahn(DagBuildArgs a) {
   constexpr bool HASH = MODE == kKahnHash || MODE == kKahnHashBig;
@@ -1088,9 +1089,9 @@ __global__ __launch_bounds__(256) void k_face_stats(const int64_t* face_ptr, int
 // face_twin and face_shift when given; *bad is set if one may be violated (the host then
 // looks for the first and words the message).  16 lanes per cell, one face each;
 // nothing is read through an index before it has been found in range.  Bound by
-// memory: a checked build of 50 K cells takes 2.9 ms, and took 13.7 with the mesh copied
-// to the host and checked there (4096 cells and 8 directions, built and swept: 1.06 ms
-// and 1.54).
+// memory, the twins' gathers above all: 64^3 cells 0.14 ms, 2 M 1.09.  (With the mesh
+// copied to the host and checked there, a build of 50 K cells took 13.7 ms; a build and a
+// sweep take 2.2.)
 __global__ __launch_bounds__(256) void k_check_mesh(MeshDev M, int32_t* bad) {
   const int c = blockIdx.x * 16 + (threadIdx.x >> 4);
   if (c >= M.n_cells) return;
@@ -1291,7 +1292,7 @@ __global__ __launch_bounds__(256) void k_unit_entries(const Unit* units, const i
 //
 // Bound by the requests that the L1 keeps in flight: about 28 per task, of which 15
 // find the neighbours' positions (2.2 TB/s).  64^3 cells, 84 directions: 2.18 ms, and
-// 3.25 with 16 lanes per task and stores of single entries; 2 M cells: 19.8 ms, and
+// 3.25 with 16 lanes per task and stores of single entries; 2 M cells: 20.6 ms, and
 // 29.1.
 constexpr int kFillBlock = 256;
 constexpr int kFillTasks = 32;  // tasks assembled in LDS at a time

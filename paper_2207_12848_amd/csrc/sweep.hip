@@ -128,7 +128,9 @@ __device__ __forceinline__ float lane_below(float v) {
 // Entry pairs of a row held in registers, the kernel's P: kPairs (16 entries), or 2 where no
 // row of the walk is longer (regular grids, tetrahedra), which leaves out the loads and the
 // work for columns that nobody has.  128^3 lattice cells x 84 directions: 2.70 ms with 2
-// pairs, 4.14 with 8; 32^3: 56 and 86 us.
+// pairs, 4.14 with 8; 32^3: 57 and 86 us.  One longer row is enough for 8, although the
+// pairs past the registers have a path of their own: a choice by how many rows are that long
+// would also serve scheme (b), with 2.7 entries per row on average and 10 at most.
 constexpr int kPairs = 8;
 
 // The unit's arrays (uniform over the workgroup).
@@ -295,9 +297,9 @@ __device__ __forceinline__ void wait_stored(lds_int* last, int nw, int lane, int
 // slots' addresses, the reads of the row's tail).  Wide levels, the line requests of one
 // compute unit's L1 (a unit runs on one) and its instruction issue.  Against steps of a
 // level with one barrier each, whose wavefronts loaded, staged through LDS and solved by
-// turns (forward sweep per launch): 64^3 cells x 84 directions 2.27 -> 0.72 ms; 4,096 cells
+// turns (forward sweep per launch): 64^3 cells x 84 directions 2.27 -> 0.71 ms; 4,096 cells
 // x 8 directions 0.288 -> 0.075 ms; 2M clustered cells x 84 directions x 4 groups 27.0 ->
-// 11.9 ms (+ 1.5 ms for k_to_cells; with the results stored in cell order from here, 26.4).
+// 12.0 ms (+ 1.5 ms for k_to_cells; with the results stored in cell order from here, 26.4).
 // A division with the reciprocal taken before the wait, and a test whether that is exact,
 // was slower: the test's branch costs more than the divide's dependent steps.
 template <int GN, bool REVERSE, int P>
@@ -543,7 +545,7 @@ __global__ __launch_bounds__(kSweepMaxBlock(GN)) void k_sweep(SweepArgs a) {
     // The same sum after the wait for the stores of the earlier levels, when every older
     // result can be loaded, of slice `at`: the columns in registers by halves, then the pairs
     // past them 64 at a time, the next ones on their way meanwhile.  (All pairs one after the
-    // other, from memory, took five times as long: 400 cells that all border each other x 8
+    // other, from memory, took three to six times as long: 400 cells that all border each other x 8
     // directions 8.9 ms, now 1.5; 8,000 cells x 24 directions with a ring of 64 results 0.93
     // and 0.34.)
     auto gather_slow = [&](int at, const Slice<GN>& S, Entries<P>& E, float* acc) {
